@@ -149,6 +149,7 @@ int launch_assembly(petgem_system* sys, hipStream_t s) {
     PG_HIP(hipGetLastError());
     sys->cached_freq = -1.0;   // operators derived from K, Ms are stale
     sys->have32 = false;
+    sys->res[0].values = sys->res[1].values = false;
     return PETGEM_OK;
 }
 

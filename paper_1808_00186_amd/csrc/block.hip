@@ -56,6 +56,7 @@
 
 #include <hip/hip_ext.h>
 
+#include "cocg.h"
 #include "device.h"
 #include "internal.h"
 
@@ -72,90 +73,9 @@ constexpr int kSnapRing = 32;            // host snapshot slots of the fused ste
 constexpr int kStepTiles = 8;   // tiles per block of the fused single-column step (2, 4, 16: 12, 2.5, 3.5 % slower)
 constexpr int kMaxGroups = 6;   // iteration groups between two host checks (4, 8: 0.5, 1.5 % slower on a 434k-DOF mesh)
 
-__device__ __forceinline__ float2 f2(float x, float y) { return make_float2(x, y); }
-
 template <typename T> struct V2;
 template <> struct V2<float> { using t = float2; };
 template <> struct V2<double> { using t = double2; };
-
-struct ColState {
-    double2 rho, alpha, beta;
-    double rn2;        // inner |r|^2 (relative to the normalised start)
-    double rn2_0;      // |r|^2 at the start of the inner solve the tolerance is relative to (1, or the
-                       // split residual's of an Eisenstat solve)
-    double rn2_best;   // least inner |r|^2 of the current refinement step
-    double scale;      // |r64| of the current refinement step
-    double bnorm;      // |b|
-    double rnorm64;    // true residual norm
-    double tol_abs;    // rtol |b|
-    double inner_tol2; // squared inner tolerance of the current refinement step
-    double inner_rtol; // requested inner tolerance
-    int active;        // inner iteration running
-    int outer;         // not yet converged in double precision
-    int breakdown;
-    int iters;         // inner iterations (all refinement steps)
-    int kin;           // inner iterations of the current refinement step
-    int stepped;       // this iteration's alpha was applied to r (set at the beta step)
-    int k_best;        // inner iteration of rn2_best
-    int stalled;       // inner steps ended by the stagnation guard (all refinement steps)
-    // symmetric QMR (sqmr): the quasi-minimal-residual smoothing of the iterate
-    double tau2;       // tau^2, the smoothed residual's estimate (same norm as rn2)
-    double cq;         // c^2 of the latest beta step: x_Q = (1 - c^2) x_Q + c^2 x
-    double tmark;      // tau^2 at the last halving of tau (the plateau rule)
-    int sqmr;          // this solve is SQMR
-};
-
-// Stagnation guard of the inner COCG, which has no minimisation property: a
-// column whose inner |r|^2 has not improved on its best of this refinement
-// step for twice the iterations the best took plus kStallIters stops its
-// inner solve; the refinement step applies its correction and the next step
-// restarts from the true residual. Without it one column of a 32-source block
-// on the 6.9M-DOF marine mesh, after a last-bit change of its starting scale,
-// wandered at inner |r| ~ 1 for 18,000 iterations instead of converging.
-// (A guard that also stopped a column on a 1000-fold rise of |r|, with 500
-// instead of 3000 iterations, fired on ordinary spikes of converging columns:
-// their corrections raised the true residual 50-fold and the block needed
-// 4-6 refinement steps instead of 3.)
-constexpr int kStallIters = 3000;
-__device__ __forceinline__ bool stalled_now(ColState& S, double r2) {
-    if (r2 < S.rn2_best) {
-        S.rn2_best = r2;
-        S.k_best = S.kin;
-        return false;
-    }
-    return S.kin - S.k_best > 2 * S.k_best + kStallIters;
-}
-
-// The last refinement step of a column solves its correction only as far as
-// the target needs, with a factor 0.3 to spare (res_step). A column whose
-// inner |r| hovers just above that target without a new best for half the
-// iterations its best took (at least kRelaxIters) gives the margin up: it
-// stops once |r| is within the target without the factor. (With a quarter,
-// columns that were still converging gave the margin up, missed rtol and
-// needed a fourth refinement step.) (On the
-// 6.9M-unknown survey one 0.25 Hz column reached 1.04 times its target of
-// 2.2e-2 at iteration 576 of its third step, then wandered for 4,000
-// iterations until the guard above stopped it.)
-constexpr int kRelaxIters = 100;
-// In any refinement step, a column whose |r| has had no new best for as many
-// iterations as its best took (at least kPlateauIters) stops at the first
-// iterate whose |r| is at most 0.1 of the step's start: its correction
-// still reduces the true residual tenfold, and the next refinement step
-// restarts from it. (The same 0.25 Hz survey had a column reach 1.4 times the
-// inner target 3e-5 at iteration 365 of its first step and wander between
-// 2e-4 and 7e-3 until the guard stopped it at 4,096.) A plateau as long as
-// the whole descent before it does not occur in a column that still
-// converges.
-constexpr int kPlateauIters = 200;
-__device__ __forceinline__ bool plateau_now(const ColState& S, double r2) {
-    const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;   // that one has its own rule
-    return !last_step && S.kin - S.k_best >= max(kPlateauIters, S.k_best) && r2 <= 0.01 * S.rn2_0;
-}
-__device__ __forceinline__ bool relaxed_now(const ColState& S, double r2) {
-    const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;
-    return last_step && r2 <= S.inner_tol2 * S.rn2_0 / (0.3 * 0.3) &&
-           S.kin - S.k_best >= max(kRelaxIters, S.k_best / 2);
-}
 
 // Operator view shared by the kernels.
 struct Op {
@@ -193,9 +113,6 @@ __device__ __forceinline__ int tile_of(const Op& op, int b) { return op.tmap ? o
 
 // ------------------------------------------------------------ reductions
 enum RedMode { RED_INIT = 0, RED_ALPHA = 1, RED_BETA = 2, RED_RES = 3, RED_X0 = 4, RED_INIT_REL = 5 };
-
-__device__ __forceinline__ bool cfinite(double2 a) { return isfinite(a.x) && isfinite(a.y); }
-__device__ __forceinline__ bool czero(double2 a) { return a.x == 0.0 && a.y == 0.0; }
 
 // alpha = rho / p^T q (or breakdown) for an active column
 __device__ __forceinline__ void step_alpha(ColState& S, double2 pq) {
@@ -963,10 +880,6 @@ k_spmm_sp(Op op, const ColState* __restrict__ st, const float2* __restrict__ X, 
         const int u = threadIdx.x;
         partial[(size_t)tile * C + u] = cadd(cadd(red[0][u], red[1][u]), cadd(red[2][u], red[3][u]));
     }
-}
-
-__device__ __forceinline__ float2 cmulf(float2 a, float2 b) {
-    return f2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
 // Single-column form of k_spmm_sp for the fused COCG step: besides y = A x
@@ -1905,59 +1818,6 @@ k_pupdate_p(Op op, int CP, int tpb, const ColState* __restrict__ s0, ColState* _
     }
 }
 
-// The scalar step of the fused step for one column, from the five sums t:
-// the product's p^T q, q^T D^-1 r, q^T D^-1 q and the previous step's r^T z,
-// |r|^2. kin == 0 (just started): rho and |r|^2 are the state's own;
-// otherwise the convergence test (with the stagnation guard) runs first.
-__device__ __forceinline__ void fused_scalars(ColState& S, const double2* t) {
-    if (S.active && S.kin > 0) {   // the r left by the previous step
-        const double2 rz = t[3];
-        const double r2 = t[4].x;
-        S.rn2 = r2;
-        if (!isfinite(r2) || !cfinite(rz)) {
-            S.active = 0;
-            S.breakdown = 1;
-        } else if (r2 <= S.inner_tol2) {
-            S.active = 0;
-        } else if (stalled_now(S, r2)) {
-            S.active = 0;
-            S.stalled += 1;
-        } else if (relaxed_now(S, r2)) {
-            S.active = 0;
-        } else if (plateau_now(S, r2)) {
-            S.active = 0;
-            S.stalled += 1;
-        } else if (czero(rz)) {
-            S.active = 0;
-            S.breakdown = 1;
-        } else {
-            S.rho = rz;
-        }
-    }
-    if (S.active) {
-        const double2 pq = t[0];
-        if (!cfinite(pq) || czero(pq)) {
-            S.active = 0;
-            S.breakdown = 1;
-        } else {
-            const double2 al = cdiv(S.rho, pq);
-            // rho - 2 alpha q^T D^-1 r + alpha^2 q^T D^-1 q
-            const double2 next =
-                cadd(cadd(S.rho, cscale(cmul(al, t[1]), -2.0)), cmul(cmul(al, al), t[2]));
-            const double2 be = cdiv(next, S.rho);
-            if (!cfinite(be)) {
-                S.active = 0;
-                S.breakdown = 1;
-            } else {
-                S.alpha = al;
-                S.beta = be;
-                S.iters += 1;
-                S.kin += 1;
-            }
-        }
-    }
-}
-
 // ------------------------------------------- fused single-column step
 // One mesh, one column, D^-1 precomputed: after the product q = A p a single
 // vector kernel takes the whole COCG step. The next rho is known before r is
@@ -2601,6 +2461,7 @@ struct BlockWork {
     hipGraphExec_t graphs[kMaxGroups] = {};
     hipStream_t graph_stream = nullptr;
     std::vector<char> graph_sig;   // bytes of every argument baked into the graphs
+    ResWork res;                   // tables and exchange buffers of the resident COCG
     ~BlockWork() { release(); }
     void release_graph() {
         for (auto& g : graphs) {
@@ -2622,6 +2483,7 @@ struct BlockWork {
         dfree(XQ);
         xq_cap = 0;
         dfree(seg_tile); dfree(tile_seg);
+        res.release();
         dfree(rp); dfree(col); dfree(K64); dfree(M64); dfree(Kd); dfree(Md); dfree(K32); dfree(M32);
         cat_sell.release();
         if (st_h) (void)hipHostFree(st_h);
@@ -3147,6 +3009,10 @@ int cp_of(int C) {
 // Autotuner of the complex64 SpMM tile shape: every candidate (lanes per row x
 // columns per lane, or lanes sharing a row's nonzeros) runs 3 times on this
 // operator and block width; the fastest is kept per (rows, nnz, columns).
+bool spmm_tuned(const BlockWork* w, const Op& op, int64_t nnz) {
+    return w->tuned.count(std::make_tuple(op.n, nnz, op.C)) != 0;
+}
+
 int tune_spmm(BlockWork* w, const Op& op, int64_t nnz, hipStream_t s, SpmmTuned& out, bool verbose) {
     auto key = std::make_tuple(op.n, nnz, op.C);
     auto it = w->tuned.find(key);
@@ -3218,9 +3084,13 @@ int tune_spmm(BlockWork* w, const Op& op, int64_t nnz, hipStream_t s, SpmmTuned&
 // On entry B64 holds the right-hand sides, X64 the initial guesses (or zero).
 // has_x0: which (segment, column) pairs came with an initial guess (null:
 // all of them when have_x0); only those can be rejected.
+// resident: the inner solves run in w->res's launches (planned by the caller)
+// instead of kernel by kernel; returns kResAborted, with nothing said about
+// the columns, if one of their waits ran out.
+constexpr int kResAborted = 1;
 int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hipStream_t s,
                std::vector<petgem_stats*>& stv, bool have_x0, const std::vector<int>* seg_tile_h = nullptr,
-               const std::vector<char>* has_x0 = nullptr, const Ssor* sq = nullptr) {
+               const std::vector<char>* has_x0 = nullptr, const Ssor* sq = nullptr, bool resident = false) {
     const int C = op.C, nsc = op.nseg * C, CP = cp_of(C);
     // multicolour SSOR instead of Jacobi (one mesh): the five-kernel
     // iteration with the two sweeps and an r^T z pass between the r update
@@ -3297,7 +3167,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
     // batch keeps the double-precision diagonal: its hardest models need a few
     // percent more iterations with the rounded D^-1)
     const float2* dinv = nullptr;
-    if ((in_consumer && C == 1) || fused) {
+    if (!resident && ((in_consumer && C == 1) || fused)) {
         const size_t rows = (size_t)op.ntiles * kTR;
         if (w->dinv_rows < rows) {
             dfree(w->Dinv);
@@ -3351,7 +3221,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
     const int seg_u = force_kind == 5 ? o.spmm_shape % 100
                       : (ch.kind == 2 || ch.kind == 3) && ch.a == 1 && ch.b == 8 ? 8 : 4;
     int64_t groups_done = 0;   // groups launched since the fused step's group count was cleared
-    if (fused) {
+    if (fused && !resident) {
         if (!w->snap_ring)
             PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&w->snap_ring), sizeof(ColState) * kSnapRing));
         if (!w->gcount) PG_TRY(dalloc(&w->gcount, 1));
@@ -3582,6 +3452,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         return PETGEM_OK;
     };
 
+    std::vector<char> live(nsc, 0);   // columns the current refinement step solves
     int total_inner = 0, steps = 0, strikes = 0;
     const char* why = "";
     int status = PETGEM_OK;
@@ -3596,6 +3467,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         }
         if (nonfinite) { status = PETGEM_NONFINITE; break; }
         if (n_outer == 0) break;
+        for (int k = 0; k < nsc; ++k) live[k] = w->st_h[k].outer != 0;
         // stagnation: the worst relative residual must at least halve per step
         double worst = 0.0;
         for (int k = 0; k < nsc; ++k)
@@ -3613,6 +3485,11 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
             why = steps >= max_steps ? "reached its refinement step limit" : "reached max_iter";
             break;
         }
+        int inner = 0;
+        if (resident) {
+            PG_TRY(res_run(w->res, o.max_iter - total_inner, s));
+            PG_HIP(hipMemcpyAsync(w->res.abort_h, w->res.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+        } else {
         // inner complex64 COCG on A d = r64 / |r64|
         hipLaunchKernelGGL(k_inner_init, dim3(op.ntiles), dim3(256), 0, s, op, CP, w->R64, w->st, dinv, w->Xi,
                            w->R, w->Z, w->P, w->p1, w->p2);
@@ -3631,7 +3508,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         // groups in a row follows the observed decrease of the worst active
         // residual (half the predicted need, at most kMaxGroups), so that the
         // readbacks are few while little runs past convergence.
-        int inner = 0, groups = 1, next_print = 512;
+        int groups = 1, next_print = 512;
         double prev_gap = -1.0;
         uncompact();
         // A single system keeps one more batch of iteration groups queued while
@@ -3723,11 +3600,17 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
             PG_TRY(launch_batch(groups, cur));
             queued = groups;
         }
-        total_inner += inner;
+        }
         hipLaunchKernelGGL(k_ir_update, dim3(op.ntiles), dim3(256), 0, s, op, CP, w->st, w->Xi,
                            (const float2*)xq, eis ? 1 : 0, w->X64);
         PG_TRY(residual(0));
         PG_TRY(read_state());
+        if (resident) {
+            if (*w->res.abort_h) return kResAborted;
+            for (int k = 0; k < nsc; ++k)
+                if (live[k]) inner = std::max(inner, w->st_h[k].kin);
+        }
+        total_inner += inner;
         ++steps;
         if (o.verbose) {
             double worst = 0.0;
@@ -3778,7 +3661,9 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         st->t_solve_ms = t_solve;
         st->spmv_ms = spmv_ms;
         st->spmv_launches = spmv_n;
-        st->spmv_shape = fused ? 40100 + fused_u : fused_seg ? 50100 + seg_u
+        // the resident kernel runs the fused step's recurrence and reports its shape
+        st->spmv_shape = resident && C == 1 ? (op.nseg == 1 ? 40104 : 50100 + seg_u)
+                         : fused ? 40100 + fused_u : fused_seg ? 50100 + seg_u
                          : eis ? 70000 + 100 * eis_lpr(C) + (C <= 64 ? 1 : C <= 128 ? 2 : 4)
                                : 10000 * ch.kind + 100 * ch.a + ch.b;
         st->status = S.outer ? (std::isfinite(S.rnorm64) ? PETGEM_NOT_CONVERGED : PETGEM_NONFINITE) : PETGEM_OK;
@@ -4265,12 +4150,16 @@ int bcocg_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, h
 
 }  // namespace
 
+// Options under which the inner solves may run in the resident kernel.
+bool resident_opts(const petgem_opts& o) {
+    return o.precond == PETGEM_JACOBI && o.spmm_shape == 0 && o.profile == 0;
+}
+
 int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, const petgem_opts& o,
                 const double2* x0, double2* x_out, hipStream_t s, petgem_stats* st) {
     const int n = sys->n_dof, C = n_src;
     const int ntiles = ceil_div(n, kTR);
     const size_t rows = (size_t)ntiles * kTR;
-    PG_TRY(ensure_fp32(sys, s));
     PG_TRY(ensure_work(sys->bw, rows, C, C, ntiles));
     BlockWork* w = sys->bw;
     std::vector<double> wmu(C);
@@ -4288,24 +4177,38 @@ int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, con
     op.seg_tile = w->seg_tile;
     op.rp = sys->row_ptr;
     op.col = sys->col;
-    op.K32 = sys->K32;
-    op.M32 = sys->Ms32;
     op.K64 = sys->K;
     op.M64 = sys->Ms;
     op.Kd = sys->Kd;
     op.Md = sys->Msd;
     op.wmu = w->wmu;
     op.nrow_valid = n;
-    if (C <= 4) {   // the sliced-ELLPACK shapes serve up to four columns
-        Sell& S = sys->sell32;
-        if (!S.ptr || !S.values) PG_TRY(build_sell(S, (int)rows, n, sys->row_ptr, sys->col, sys->K32, sys->Ms32, false, s));
-        op.sp = S.ptr;
-        op.sw = S.w;
-        op.srow = S.row;
-        op.scol = S.col;
-        op.sK = S.K;
-        op.sM = S.M;
-    }
+    // Jacobi columns of a mesh that fits run their inner solves in the resident
+    // kernel (a caller-chosen SpMM shape and profiling keep the kernels of
+    // each phase)
+    bool resident = false;
+    if (o.method == PETGEM_COCG && resident_opts(o))
+        PG_TRY(res_plan(w->res, {ResItem{sys, 0, 0, C}}, ResVectors{w->R64, w->Xi, w->st, w->wmu}, s, &resident));
+    // the complex64 operator of the kernels of each phase: not needed by a
+    // resident solve once its shapes are tuned
+    auto need_fp32 = [&]() -> int {
+        PG_TRY(ensure_fp32(sys, s));
+        op.K32 = sys->K32;
+        op.M32 = sys->Ms32;
+        if (C <= 4) {   // the sliced-ELLPACK shapes serve up to four columns
+            Sell& S = sys->sell32;
+            if (!S.ptr || !S.values)
+                PG_TRY(build_sell(S, (int)rows, n, sys->row_ptr, sys->col, sys->K32, sys->Ms32, false, s));
+            op.sp = S.ptr;
+            op.sw = S.w;
+            op.srow = S.row;
+            op.scol = S.col;
+            op.sK = S.K;
+            op.sM = S.M;
+        }
+        return PETGEM_OK;
+    };
+    if (!resident || !spmm_tuned(w, op, sys->nnz)) PG_TRY(need_fp32());
     // right-hand sides into the block layout (padding rows stay zero)
     Timer t_rhs;
     hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows * C, 256)), dim3(256), 0, s, rows * C, w->B64);
@@ -4320,10 +4223,13 @@ int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, con
         return PETGEM_SOURCE_SINGULAR;
     }
     const double trhs = t_rhs.ms();
-    hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows * C, 256)), dim3(256), 0, s, rows * C, w->X64);
-    if (x0)
-        hipLaunchKernelGGL(k_cols_in, dim3(ceil_div((size_t)n * C, 256)), dim3(256), 0, s, n, C, (size_t)0,
-                           x0, (size_t)n, w->X64);
+    auto start = [&]() {
+        hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows * C, 256)), dim3(256), 0, s, rows * C, w->X64);
+        if (x0)
+            hipLaunchKernelGGL(k_cols_in, dim3(ceil_div((size_t)n * C, 256)), dim3(256), 0, s, n, C, (size_t)0,
+                               x0, (size_t)n, w->X64);
+    };
+    start();
     std::vector<petgem_stats*> stv(C, nullptr);
     if (st)
         for (int c = 0; c < C; ++c) { stv[c] = st + c; st[c].t_rhs_ms = trhs; }
@@ -4361,7 +4267,12 @@ int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, con
         PG_TRY(ensure_ssor(sys, s));
         sq = &sys->ssor32;
     }
-    int rc = mrhs_solve(w, op, sys->nnz, o, s, stv, x0 != nullptr, nullptr, nullptr, sq);
+    int rc = mrhs_solve(w, op, sys->nnz, o, s, stv, x0 != nullptr, nullptr, nullptr, sq, resident);
+    if (rc == kResAborted) {
+        PG_TRY(need_fp32());
+        start();
+        rc = mrhs_solve(w, op, sys->nnz, o, s, stv, x0 != nullptr);
+    }
     if (rc != PETGEM_OK && rc != PETGEM_NOT_CONVERGED && rc != PETGEM_NONFINITE) return rc;
     hipLaunchKernelGGL(k_cols_out, dim3(ceil_div((size_t)n * C, 256)), dim3(256), 0, s, n, C, (size_t)0,
                        w->X64, x_out, (size_t)n);
@@ -4452,25 +4363,39 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
     op.Md = w->Md;
     op.wmu = w->wmu;
     op.nrow_valid = (int)rows;
-    PG_TRY(build_sell(w->cat_sell, (int)rows, (int)rows, w->rp, w->col, w->K32, w->M32, true, s));
-    op.sp = w->cat_sell.ptr;
-    op.sw = w->cat_sell.w;
-    op.srow = w->cat_sell.row;
-    op.scol = w->cat_sell.col;
-    op.sK = w->cat_sell.K;
-    op.sM = w->cat_sell.M;
+    bool resident = false;
+    if (resident_opts(o)) {
+        std::vector<ResItem> items(n_sys);
+        for (int k = 0; k < n_sys; ++k) items[k] = ResItem{systems[k], (size_t)row_off[k], k, 1};
+        PG_TRY(res_plan(w->res, items, ResVectors{w->R64, w->Xi, w->st, w->wmu}, s, &resident));
+    }
+    auto need_sell = [&]() -> int {
+        PG_TRY(build_sell(w->cat_sell, (int)rows, (int)rows, w->rp, w->col, w->K32, w->M32, true, s));
+        op.sp = w->cat_sell.ptr;
+        op.sw = w->cat_sell.w;
+        op.srow = w->cat_sell.row;
+        op.scol = w->cat_sell.col;
+        op.sK = w->cat_sell.K;
+        op.sM = w->cat_sell.M;
+        return PETGEM_OK;
+    };
+    if (!resident || !spmm_tuned(w, op, nnz)) PG_TRY(need_sell());
     Timer t_rhs;
     hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows, 256)), dim3(256), 0, s, rows, w->B64);
-    hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows, 256)), dim3(256), 0, s, rows, w->X64);
     bool have_x0 = false;
     std::vector<char> has_x0(n_sys, 0);
-    for (int k = 0; x0 && k < n_sys; ++k)
-        if (x0[k]) {
-            has_x0[k] = 1;
-            PG_HIP(hipMemcpyAsync(w->X64 + row_off[k], x0[k], sizeof(double2) * systems[k]->n_dof,
-                                  hipMemcpyDeviceToDevice, s));
-            have_x0 = true;
-        }
+    auto start = [&]() -> int {
+        hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows, 256)), dim3(256), 0, s, rows, w->X64);
+        for (int k = 0; x0 && k < n_sys; ++k)
+            if (x0[k]) {
+                has_x0[k] = 1;
+                PG_HIP(hipMemcpyAsync(w->X64 + row_off[k], x0[k], sizeof(double2) * systems[k]->n_dof,
+                                      hipMemcpyDeviceToDevice, s));
+                have_x0 = true;
+            }
+        return PETGEM_OK;
+    };
+    PG_TRY(start());
     for (int k = 0; k < n_sys; ++k) PG_TRY(launch_rhs(systems[k], src[k], w->B64 + row_off[k], 1, s));
     for (int k = 0; k < n_sys; ++k) {
         int flag = 0;
@@ -4488,7 +4413,12 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
     std::vector<petgem_stats*> stv(n_sys, nullptr);
     if (st)
         for (int k = 0; k < n_sys; ++k) { stv[k] = st + k; st[k].t_rhs_ms = trhs; }
-    int rc = mrhs_solve(w, op, nnz, o, s, stv, have_x0, &seg_tile, &has_x0);
+    int rc = mrhs_solve(w, op, nnz, o, s, stv, have_x0, &seg_tile, &has_x0, nullptr, resident);
+    if (rc == kResAborted) {
+        PG_TRY(need_sell());
+        PG_TRY(start());
+        rc = mrhs_solve(w, op, nnz, o, s, stv, have_x0, &seg_tile, &has_x0);
+    }
     if (rc != PETGEM_OK && rc != PETGEM_NOT_CONVERGED && rc != PETGEM_NONFINITE) return rc;
     for (int k = 0; k < n_sys; ++k)
         PG_HIP(hipMemcpyAsync(sols[k]->x, w->X64 + row_off[k], sizeof(double2) * systems[k]->n_dof,

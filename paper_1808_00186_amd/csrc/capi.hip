@@ -84,6 +84,8 @@ void release_system(petgem_system* sys) {
     dfree(sys->Kst); dfree(sys->Mst); dfree(sys->K); dfree(sys->Ms); dfree(sys->Kd); dfree(sys->Msd);
     sys->sell32.release();
     sys->ssor32.release();
+    sys->res[0].release();
+    sys->res[1].release();
     dfree(sys->K32); dfree(sys->Ms32); dfree(sys->Ahat); dfree(sys->dvec); dfree(sys->dinv);
     dfree(sys->Rst); dfree(sys->dflag); dfree(sys->tmp);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);

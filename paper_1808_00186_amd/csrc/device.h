@@ -40,6 +40,45 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// Sums over lanes without LDS traffic: within 16 lanes by DPP, across them by
+// the row and half-wave swaps. dpp_add adds the value of the lane that the DPP
+// control pairs this one with.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+// a over lanes l and l + 32 in the lower half-wave, b's in the upper
+__device__ __forceinline__ double swap32_add(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// likewise over rows of 16 lanes: a's pairs in the even rows, b's in the odd
+__device__ __forceinline__ double swap16_add(double a, double b) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// a over the two halves of each row in its lower eight lanes, b's in the upper
+__device__ __forceinline__ double swap8_add(double a, double b, bool upper) {
+    const double send = upper ? a : b, keep = upper ? b : a;
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(send), 0x128, 0xf, 0xf, true);   // row_ror:8
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(send), 0x128, 0xf, 0xf, true);
+    return keep + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double sum8(double v) {    // over eight lanes, in each of them
+    v = dpp_add<0x141>(v);    // row_half_mirror
+    v = dpp_add<0x4e>(v);     // quad_perm [2,3,0,1]
+    return dpp_add<0xb1>(v);  // quad_perm [1,0,3,2]
+}
+__device__ __forceinline__ double sum16(double v) { return sum8(dpp_add<0x128>(v)); }
+__device__ __forceinline__ double sum32(double v) {
+    v = sum16(v);
+    return swap16_add(v, v);
+}
+
 // Primary field of a unit-direction dipole p with moment `mom` at src in a
 // whole space of conductivity sigma (e^{-iwt}). With kappa = sqrt(w mu0 sigma/2)
 // the wavenumber is k = (1+i) kappa, so e^{ikr} = e^{-kappa r} e^{i kappa r},

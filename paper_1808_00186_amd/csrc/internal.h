@@ -103,6 +103,25 @@ struct Ssor {
     }
 };
 
+// A mesh's operator laid out for the resident COCG (resident.hip): G
+// workgroups of rw consecutive rows each, their rows ordered by length, the
+// entries in the order the registers take them (chunks of four per lane, LDS
+// indices of 16 bits) and each workgroup's outer neighbours.
+struct Resident {
+    int state = 0;                // 0 not built, 1 usable, -1 the mesh does not fit
+    int G = 0, rw = 0, rwcap = 0; // workgroups; rows of each; their LDS slots
+    int hcap = 0, hmax = 0;       // most outer neighbours of a workgroup; stride of halo
+    int32_t* rows = nullptr;      // [G][rwcap] matrix row of each slot (-1: none)
+    int32_t* wend = nullptr;      // [G][8][4] chunks of a wave's row slots, cumulative
+    int32_t* halo = nullptr;      // [G][hmax] exchange place of each outer neighbour
+    int32_t* nh = nullptr;        // [G]
+    uint64_t* idx = nullptr;      // [G][8][chunks][64] four LDS indices
+    float* K = nullptr;           // [G][8][chunks][64][4]
+    float* M = nullptr;
+    bool values = false;          // K, M current
+    void release();
+};
+
 // Background of the primary field: the whole space sigma_bg, or two
 // half-spaces meeting at z = z0 (s_up above, holding the sources).
 struct Layers {
@@ -141,6 +160,32 @@ struct GmresWork {
     hipGraphExec_t graph = nullptr;  // one captured cycle
     hipStream_t graph_stream = nullptr;
     void release();
+};
+
+// ------------------------------------------------------- resident COCG
+// Device tables and exchange buffers of one solve's resident launches.
+struct ResWork {
+    struct Round { int blk0 = 0, nblk = 0; size_t lds = 0; };
+    std::vector<Round> rounds;    // one launch each
+    char* doms = nullptr;
+    int* blk = nullptr;           // domain of each logical block
+    unsigned long long *words = nullptr, *pex = nullptr;
+    int *abort = nullptr, *abort_h = nullptr;
+    size_t cap_doms = 0, cap_blk = 0, cap_words = 0, cap_pex = 0, n_words = 0, n_pex = 0;
+    void release();
+};
+// One mesh of a solve: its rows start at row_off of the block vectors, its C
+// columns have the states and frequencies from seg * C on.
+struct ResItem {
+    petgem_system* sys;
+    size_t row_off;
+    int seg, C;
+};
+struct ResVectors {
+    const double2* R64;
+    float2* Xi;
+    void* st;                     // ColState
+    const double* wmu;
 };
 
 // ------------------------------------------------------- multi-RHS workspace
@@ -195,6 +240,7 @@ struct petgem_system {
     float* Ms32 = nullptr;
     bool have32 = false;
     petgem::Sell sell32;     // sliced-ELLPACK copy of K32 / Ms32 (built on first use)
+    petgem::Resident res[2]; // finer and coarser split for the resident COCG (built on first use)
     petgem::Ssor ssor32;     // multicolour L / U split of K32 / Ms32 (built on first SSOR use)
     // frequency-specific operator of the FP64 GMRES: Ahat = A D^{-1}
     double cached_freq = -1.0;
@@ -263,6 +309,12 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
                 const petgem_opts& o, const void* const* x0, petgem_solution** sols, hipStream_t s,
                 petgem_stats* st);
 int ensure_fp32(petgem_system* sys, hipStream_t s);
+// Resident COCG: lays the meshes out and fills the launch tables (*fits false:
+// some mesh is too large, use the kernel-per-phase form); then one inner solve
+// of every column whose state is `outer`, at most max_inner iterations. After
+// it *W.abort is non-zero if a wait ran out.
+int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits);
+int res_run(ResWork& W, int max_inner, hipStream_t s);
 // the multicolour split of the operator (pattern built once, values gathered
 // again after every reassembly); ssor_apply: z = M^-1 r of one complex64
 // column at one frequency (device vectors of n_dof)

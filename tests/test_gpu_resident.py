@@ -1,0 +1,117 @@
+"""The resident COCG (one kernel per inner solve) against the library's own
+double-precision right-hand side and product, and its iteration counts
+against the kernel-per-phase form. Marked `gpu`.
+
+The true residual |b - A x| / |b| of every column is formed from
+``System.rhs`` and ``System.spmv``, each pinned to the oracle by its own test,
+so its bound is the solve's tolerance itself (1 % for the rounding of the
+residual's own evaluation). The two forms run the same recurrence in exact
+arithmetic; their roundings moved iteration counts by up to 10 %, so the
+bound on them is 25 % and one check interval.
+"""
+import numpy as np
+import pytest
+
+from paper_1808_00186_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+RTOL = 1e-10
+
+
+@pytest.fixture(scope="module")
+def pg():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1808_00186_amd import petgem
+    petgem.lib()
+    return petgem
+
+
+def _model(n, seed=5, f=1.0, box=3000.0):
+    xyz, tets = synth.kuhn_mesh(n, -box, box, seed + n)
+    sig = synth.marine_sigma(synth.centroids(xyz, tets), ((-0.4 * box, 0.4 * box), (-0.4 * box, 0.4 * box),
+                                                          (-0.6 * box, -0.2 * box)), 0.02)
+    return synth.Model(f"resident-{n}", xyz, tets, sig, 3.3, [synth.Dipole((30.0, 0.0, 50.0), f)],
+                       np.zeros((1, 3)), n, (-box, box))
+
+
+def _residuals(S, srcs, x):
+    b = S.rhs(srcs)
+    r = [b[k] - S.spmv(d.freq, x[k].contiguous()) for k, d in enumerate(srcs)]
+    return [float(r[k].norm() / b[k].norm()) for k in range(len(srcs))]
+
+
+# 2: 26 unknowns, most lanes idle; 5: 665, two workgroups, the second partly
+# filled; 8: 6 workgroups; 16: 52, two levels of sums; 23: 158 (nine columns
+# of it: the coarser split, in turn on its domains)
+@pytest.mark.parametrize("n", [2, 5, 8, 16, 23])
+@pytest.mark.parametrize("cols", [1, 2, 9])
+def test_resident_columns_reach_the_true_residual(pg, n, cols):
+    print(f"[case] resident n={n} cols={cols}", flush=True)
+    m = _model(n)
+    S = pg.System.from_model(m)
+    srcs = [synth.Dipole((-200.0 + 90.0 * k, 10.0, 50.0 + 5 * k), (0.5, 1.3, 2.0)[k % 3]) for k in range(cols)]
+    o = pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL)
+    sol, st, rc = S.solve(srcs, o)
+    assert rc == pg.OK
+    res = _residuals(S, srcs, sol.x())
+    print(f"  iters {[s['iters'] for s in st]} residual {max(res):.1e}", flush=True)
+    assert max(res) <= 1.01 * RTOL
+    again, _, _ = S.solve(srcs, o)
+    assert np.array_equal(sol.x().cpu().numpy(), again.x().cpu().numpy())
+    # a chosen shape runs kernel by kernel
+    k = pg.spmm_candidates(cols, cols <= 4)[-1]
+    _, stk, _ = S.solve(srcs, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL, spmm_shape=k))
+    for a, b in zip(st, stk):
+        assert a["iters"] <= 1.25 * b["iters"] + 8
+
+
+def test_more_columns_than_resident_domains(pg):
+    """70 columns of a mesh that the coarser split gives 12 workgroups: 21 are
+    resident together, the others follow on the same workgroups."""
+    m = _model(14)
+    S = pg.System.from_model(m)
+    srcs = [synth.Dipole((-700.0 + 20.0 * k, 0.0, 60.0), (0.7, 1.9)[k % 2]) for k in range(70)]
+    sol, st, rc = S.solve(srcs, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL))
+    assert rc == pg.OK
+    assert max(_residuals(S, srcs, sol.x())) <= 1.01 * RTOL
+
+
+def test_resident_batch_in_several_rounds(pg):
+    """Meshes that need more workgroups than the GPU has compute units run in
+    rounds; with one too large for the resident form the batch runs kernel by
+    kernel. A converged guess takes no iteration, a non-finite one none of the
+    others' results."""
+    import torch
+    models = [_model(n, seed=k, f=0.4 + 0.3 * k) for k, n in enumerate([26, 4, 25, 9, 24, 22])]
+    systems = [pg.System.from_model(m) for m in models]
+    srcs = [m.sources[0] for m in models]
+    o = pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL)
+    sols, st, rc = pg.solve_many(systems, srcs, o)
+    assert rc == pg.OK
+    for S, src, sol in zip(systems, srcs, sols):
+        assert max(_residuals(S, [src], sol.x())) <= 1.01 * RTOL
+    x0 = [s.x()[0] for s in sols]
+    x0[2] = torch.full_like(x0[2], float("nan"))
+    sols2, st2, _ = pg.solve_many(systems, srcs, o, x0=x0)
+    assert [s["iters"] > 0 for s in st2] == [False, False, True, False, False, False]
+    assert [s["used_fallback"] for s in st2] == [0, 0, 1, 0, 0, 0]
+    assert max(_residuals(systems[2], [srcs[2]], sols2[2].x())) <= 1.01 * RTOL
+    big = _model(43)
+    systems.append(pg.System.from_model(big))
+    sols3, st3, rc = pg.solve_many(systems, srcs + [big.sources[0]], o)
+    assert rc == pg.OK
+    for S, src, sol in zip(systems, srcs + [big.sources[0]], sols3):
+        assert max(_residuals(S, [src], sol.x())) <= 1.01 * RTOL
+
+
+def test_resident_iteration_limit(pg):
+    m = _model(8)
+    S = pg.System.from_model(m)
+    sol, st, rc = S.solve(m.sources, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL, max_iter=16),
+                          allow_not_converged=True)
+    assert rc == pg.NOT_CONVERGED and st[0]["status"] == pg.NOT_CONVERGED and st[0]["iters"] <= 16
+    sol, st, rc = S.solve(m.sources, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL))
+    assert rc == pg.OK and max(_residuals(S, m.sources, sol.x())) <= 1.01 * RTOL
