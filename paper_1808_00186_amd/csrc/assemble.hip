@@ -3,11 +3,14 @@
 //
 // k_elem_km: one thread per tetrahedron computes the 21 unique entries of the
 //   symmetric 6x6 curl-curl matrix K^e and of sigma_e M^e in closed form and
-//   stores them structure-of-arrays ([21][T]) so that both the writes here and
-//   the per-entry reads of the gather are coalesced in element order.
+//   stores them as pairs {K^e, sigma_e M^e}, structure-of-arrays ([21][T]):
+//   the writes here are coalesced and the gather fetches both values of a
+//   contribution with one 16-byte load (two arrays: twice the gathers, and
+//   the gathers bound it). It also keeps the conductivities it used.
 // k_gather: one thread per nonzero sums its element contributions in
 //   increasing element order (fixed lists built on the host), so the assembled
 //   values are bitwise reproducible and bitwise symmetric, without atomics.
+//   The threads of the diagonal also write it to its own arrays.
 #include "device.h"
 #include "internal.h"
 
@@ -20,7 +23,7 @@ constexpr int kE1[6] = {1, 2, 3, 2, 1, 3};
 
 __global__ void __launch_bounds__(256)
 k_elem_km(int T, const double* __restrict__ xyz, const int4* __restrict__ tets,
-          const double* __restrict__ sigma, double* __restrict__ Kst, double* __restrict__ Mst) {
+          const double* __restrict__ sigma, double* __restrict__ sigma_kept, double2* __restrict__ st) {
     int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= T) return;
     TetGeom G;
@@ -47,7 +50,8 @@ k_elem_km(int T, const double* __restrict__ xyz, const int4* __restrict__ tets,
             gg[q][p] = v;
         }
     const double V = G.vol;
-    const double sV = sigma[t] * V * (1.0 / 20.0);
+    const double sg = sigma[t], sV = sg * V * (1.0 / 20.0);
+    if (sigma_kept != sigma) sigma_kept[t] = sg;
     int k = 0;
 #pragma unroll
     for (int i = 0; i < 6; ++i) {
@@ -58,49 +62,48 @@ k_elem_km(int T, const double* __restrict__ xyz, const int4* __restrict__ tets,
             const int a = kE0[i], b = kE1[i], c = kE0[j], d = kE1[j];
             double m = (1.0 + (a == c)) * gg[b][d] - (1.0 + (a == d)) * gg[b][c]
                      - (1.0 + (b == c)) * gg[a][d] + (1.0 + (b == d)) * gg[a][c];
-            Kst[(size_t)k * T + t] = kij;
-            Mst[(size_t)k * T + t] = sV * G.sl[i] * G.sl[j] * m;
+            st[(size_t)k * T + t] = make_double2(kij, sV * G.sl[i] * G.sl[j] * m);
         }
     }
 }
 
+// Packed entries (i, i) of an element matrix: a bit for each.
+constexpr unsigned kDiagEntries = 1u << 0 | 1u << 6 | 1u << 11 | 1u << 15 | 1u << 18 | 1u << 20;
+
 __global__ void __launch_bounds__(256)
-k_gather(int64_t nnz, const int32_t* __restrict__ cptr, const int32_t* __restrict__ cidx,
-         const double* __restrict__ Kst, const double* __restrict__ Mst,
-         double* __restrict__ K, double* __restrict__ Ms) {
+k_gather(int64_t nnz, int T, const int32_t* __restrict__ cptr, const int32_t* __restrict__ cidx,
+         const int32_t* __restrict__ col, const double2* __restrict__ st, double* __restrict__ K,
+         double* __restrict__ Ms, double* __restrict__ Kd, double* __restrict__ Msd) {
     int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= nnz) return;
     double sk = 0.0, sm = 0.0;
-    const int32_t c1 = cptr[k + 1];
+    const int32_t c0 = cptr[k], c1 = cptr[k + 1];
+    int32_t first = 0;
     // four contribution indices, then their values, in flight at a time; the
     // sums keep the list order
-    for (int32_t c = cptr[k]; c < c1; c += 4) {
+    for (int32_t c = c0; c < c1; c += 4) {
         int32_t idx[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) idx[q] = c + q < c1 ? cidx[c + q] : -1;
-        double kv[4], mv[4];
+        if (c == c0) first = idx[0];
+        double2 v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            kv[q] = idx[q] >= 0 ? Kst[idx[q]] : 0.0;
-            mv[q] = idx[q] >= 0 ? Mst[idx[q]] : 0.0;
-        }
+        for (int q = 0; q < 4; ++q) v[q] = idx[q] >= 0 ? st[idx[q]] : make_double2(0.0, 0.0);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
             if (idx[q] >= 0) {
-                sk += kv[q];
-                sm += mv[q];
+                sk += v[q].x;
+                sm += v[q].y;
             }
     }
     K[k] = sk;
     Ms[k] = sm;
-}
-
-__global__ void k_diag(int n, const int32_t* __restrict__ dpos, const double* __restrict__ K,
-                       const double* __restrict__ Ms, double* __restrict__ Kd, double* __restrict__ Msd) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    Kd[r] = K[dpos[r]];
-    Msd[r] = Ms[dpos[r]];
+    // a nonzero that gathers diagonal element entries is its row's diagonal
+    if (kDiagEntries >> ((unsigned)first / (unsigned)T) & 1u) {
+        const int32_t r = col[k];
+        Kd[r] = sk;
+        Msd[r] = sm;
+    }
 }
 
 // D = diag(A) = Kd - i w mu0 Msd and its inverse.
@@ -136,16 +139,13 @@ __global__ void k_to_f32(int64_t n, const double* __restrict__ a, const double* 
 
 }  // namespace
 
-int launch_assembly(petgem_system* sys, hipStream_t s) {
+int launch_assembly(petgem_system* sys, const double* sigma, hipStream_t s) {
     const int T = sys->n_tets;
     hipLaunchKernelGGL(k_elem_km, dim3(ceil_div(T, 256)), dim3(256), 0, s, T, sys->xyz,
-                       reinterpret_cast<const int4*>(sys->tets), sys->sigma, sys->Kst, sys->Mst);
+                       reinterpret_cast<const int4*>(sys->tets), sigma, sys->sigma, sys->KMst);
     PG_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gather, dim3(ceil_div(sys->nnz, 256)), dim3(256), 0, s, sys->nnz,
-                       sys->cptr, sys->cidx, sys->Kst, sys->Mst, sys->K, sys->Ms);
-    PG_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_diag, dim3(ceil_div(sys->n_dof, 256)), dim3(256), 0, s, sys->n_dof,
-                       sys->diag_pos, sys->K, sys->Ms, sys->Kd, sys->Msd);
+    hipLaunchKernelGGL(k_gather, dim3(ceil_div(sys->nnz, 256)), dim3(256), 0, s, sys->nnz, T, sys->cptr, sys->cidx,
+                       sys->col, sys->KMst, sys->K, sys->Ms, sys->Kd, sys->Msd);
     PG_HIP(hipGetLastError());
     sys->cached_freq = -1.0;   // operators derived from K, Ms are stale
     sys->have32 = false;

@@ -44,13 +44,11 @@ int upload_topology(petgem_system* sys, const HostTopology& t, const double* sig
     PG_TRY(dalloc(&sys->sigma, (size_t)T));
     PG_TRY(dalloc(&sys->row_ptr, (size_t)n + 1));
     PG_TRY(dalloc(&sys->col, (size_t)t.nnz));
-    PG_TRY(dalloc(&sys->diag_pos, (size_t)n));
     PG_TRY(dalloc(&sys->cptr, (size_t)t.nnz + 1));
     PG_TRY(dalloc(&sys->cidx, t.contrib_idx.size()));
     PG_TRY(dalloc(&sys->iptr, (size_t)n + 1));
     PG_TRY(dalloc(&sys->islot, t.inc_slot.size()));
-    PG_TRY(dalloc(&sys->Kst, 21 * (size_t)T));
-    PG_TRY(dalloc(&sys->Mst, 21 * (size_t)T));
+    PG_TRY(dalloc(&sys->KMst, 21 * (size_t)T));
     PG_TRY(dalloc(&sys->K, (size_t)t.nnz));
     PG_TRY(dalloc(&sys->Ms, (size_t)t.nnz));
     PG_TRY(dalloc(&sys->Kd, (size_t)n));
@@ -65,7 +63,6 @@ int upload_topology(petgem_system* sys, const HostTopology& t, const double* sig
     PG_TRY(up(sys->sigma, sigma, (size_t)T * sizeof(double)));
     PG_TRY(up(sys->row_ptr, t.row_ptr.data(), t.row_ptr.size() * sizeof(int32_t)));
     PG_TRY(up(sys->col, t.col.data(), t.col.size() * sizeof(int32_t)));
-    PG_TRY(up(sys->diag_pos, t.diag_pos.data(), t.diag_pos.size() * sizeof(int32_t)));
     PG_TRY(up(sys->cptr, t.contrib_ptr.data(), t.contrib_ptr.size() * sizeof(int32_t)));
     PG_TRY(up(sys->cidx, t.contrib_idx.data(), t.contrib_idx.size() * sizeof(int32_t)));
     PG_TRY(up(sys->iptr, t.inc_ptr.data(), t.inc_ptr.size() * sizeof(int32_t)));
@@ -80,8 +77,8 @@ int upload_topology(petgem_system* sys, const HostTopology& t, const double* sig
 void release_system(petgem_system* sys) {
     if (!sys) return;
     dfree(sys->xyz); dfree(sys->tets); dfree(sys->sigma); dfree(sys->row_ptr); dfree(sys->col);
-    dfree(sys->diag_pos); dfree(sys->cptr); dfree(sys->cidx); dfree(sys->iptr); dfree(sys->islot);
-    dfree(sys->Kst); dfree(sys->Mst); dfree(sys->K); dfree(sys->Ms); dfree(sys->Kd); dfree(sys->Msd);
+    dfree(sys->cptr); dfree(sys->cidx); dfree(sys->iptr); dfree(sys->islot);
+    dfree(sys->KMst); dfree(sys->K); dfree(sys->Ms); dfree(sys->Kd); dfree(sys->Msd);
     sys->sell32.release();
     sys->ssor32.release();
     sys->res[0].release();
@@ -213,7 +210,7 @@ int petgem_assemble(const petgem_mesh* mesh, const double* sigma, double sigma_b
         rc = upload_topology(sys, topo, sigma, s);
     }
     sys->setup_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
-    if (rc == PETGEM_OK) rc = launch_assembly(sys, s);
+    if (rc == PETGEM_OK) rc = launch_assembly(sys, sys->sigma, s);
     if (rc != PETGEM_OK) {
         release_system(sys);
         delete sys;
@@ -230,10 +227,8 @@ int petgem_reassemble(petgem_system* sys, const double* sigma_dev, double sigma_
         return PETGEM_INVALID_ARG;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_HIP(hipMemcpyAsync(sys->sigma, sigma_dev, sizeof(double) * (size_t)sys->n_tets,
-                          hipMemcpyDeviceToDevice, s));
     sys->sigma_bg = sigma_bg;
-    return launch_assembly(sys, s);
+    return launch_assembly(sys, sigma_dev, s);
 }
 
 int petgem_set_background(petgem_system* sys, const petgem_background* bg) {

@@ -223,14 +223,12 @@ struct petgem_system {
     double* sigma = nullptr;              // [T]
     int32_t* row_ptr = nullptr;           // [n+1]
     int32_t* col = nullptr;               // [nnz]
-    int32_t* diag_pos = nullptr;          // [n]
     int32_t* cptr = nullptr;              // [nnz+1]
     int32_t* cidx = nullptr;              // contributions
     int32_t* iptr = nullptr;              // [n+1]
     int32_t* islot = nullptr;             // incidence slots
     // assembled real matrices (frequency independent)
-    double* Kst = nullptr;                // [21][T] staging
-    double* Mst = nullptr;                // [21][T] staging (sigma-weighted)
+    double2* KMst = nullptr;              // [21][T] staging: {K^e, sigma_e M^e} entries
     double* K = nullptr;                  // [nnz]
     double* Ms = nullptr;                 // [nnz]
     double* Kd = nullptr;                 // [n]
@@ -278,7 +276,8 @@ struct petgem_solution {
 namespace petgem {
 
 // Launchers implemented in the .hip units; all ordered on `s`.
-int launch_assembly(petgem_system* sys, hipStream_t s);
+// sigma: device [n_tets], kept in sys->sigma by the launch
+int launch_assembly(petgem_system* sys, const double* sigma, hipStream_t s);
 int launch_freq_prep(petgem_system* sys, double freq, hipStream_t s);
 // allocation-free scratch of this device (looked up once per device) and the
 // right-hand side that uses it

@@ -308,15 +308,12 @@ int build_topology(int32_t n_nodes, int32_t n_tets, const double* xyz,
     }
     topo.nnz = topo.row_ptr[n];
     topo.col.resize(topo.nnz);
-    topo.diag_pos.resize(n);
     std::vector<int32_t> ccount(topo.nnz + 1, 0);
     parallel_for(n, [&](int64_t b, int64_t e) {
         std::vector<int32_t> cols;
         for (int64_t r = b; r < e; ++r) {
             row_columns(int32_t(r), cols);
             std::copy(cols.begin(), cols.end(), topo.col.begin() + topo.row_ptr[r]);
-            topo.diag_pos[r] = topo.row_ptr[r] +
-                int32_t(std::lower_bound(cols.begin(), cols.end(), int32_t(r)) - cols.begin());
             // contributions per nonzero: one per shared element
             for (int32_t k = topo.inc_ptr[r]; k < topo.inc_ptr[r + 1]; ++k) {
                 int32_t t = topo.inc_slot[k] / 6;

@@ -35,7 +35,6 @@ struct HostTopology {
     // CSR of the interior-edge system
     std::vector<int32_t> row_ptr;            // [n_dof + 1]
     std::vector<int32_t> col;                // [nnz]
-    std::vector<int32_t> diag_pos;           // [n_dof]
     // nnz -> element-matrix entries: staging index k * T + t (k = packed
     // index of the local pair), in increasing element order
     std::vector<int32_t> contrib_ptr;        // [nnz + 1]
