@@ -4212,7 +4212,7 @@ int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, con
     // right-hand sides into the block layout (padding rows stay zero)
     Timer t_rhs;
     hipLaunchKernelGGL(k_fill_z, dim3(ceil_div(rows * C, 256)), dim3(256), 0, s, rows * C, w->B64);
-    for (int c = 0; c < C; ++c) PG_TRY(launch_rhs(sys, src[c], w->B64 + c, C, s));
+    PG_TRY(launch_rhs(sys, src, C, w->B64, 1, C, s));
     int flag = 0;
     PG_HIP(hipMemcpyAsync(&flag, sys->dflag, sizeof(int), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
@@ -4396,19 +4396,23 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
         return PETGEM_OK;
     };
     PG_TRY(start());
-    for (int k = 0; k < n_sys; ++k) PG_TRY(launch_rhs(systems[k], src[k], w->B64 + row_off[k], 1, s));
+    hipLaunchKernelGGL(k_fill_rp, dim3(ceil_div(n_sys, 256)), dim3(256), 0, s, n_sys, 0, w->flags);
+    std::vector<RhsTask> tasks(n_sys);
     for (int k = 0; k < n_sys; ++k) {
-        int flag = 0;
-        PG_HIP(hipMemcpyAsync(&flag, systems[k]->dflag, sizeof(int), hipMemcpyDeviceToHost, s));
-        PG_HIP(hipStreamSynchronize(s));
-        if (flag) {
-            int zero = 0;
-            PG_HIP(hipMemcpy(systems[k]->dflag, &zero, sizeof(int), hipMemcpyHostToDevice));
+        int copies = 0;
+        PG_TRY(rhs_staging(systems[k], 1, &copies));
+        tasks[k] = RhsTask{systems[k], src + k, 1, w->B64 + row_off[k], 0, 1, 1, systems[k]->Rst, w->flags + k};
+    }
+    PG_TRY(launch_rhs_tasks(tasks.data(), n_sys, s));
+    std::vector<int> singular(n_sys, 0);
+    PG_HIP(hipMemcpyAsync(singular.data(), w->flags, sizeof(int) * n_sys, hipMemcpyDeviceToHost, s));
+    PG_HIP(hipStreamSynchronize(s));
+    for (int k = 0; k < n_sys; ++k)
+        if (singular[k]) {
             set_error("source within 1e-9 h of a quadrature point of an element with dsigma != 0 (system " +
                       std::to_string(k) + ")");
             return PETGEM_SOURCE_SINGULAR;
         }
-    }
     const double trhs = t_rhs.ms();
     std::vector<petgem_stats*> stv(n_sys, nullptr);
     if (st)

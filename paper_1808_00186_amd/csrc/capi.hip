@@ -250,10 +250,8 @@ int petgem_rhs(petgem_system* sys, const petgem_source* src, int32_t n_src, void
     PG_TRY(check_sys(sys));
     if (!src || n_src <= 0 || !b_dev) { set_error("sources and output are required"); return PETGEM_INVALID_ARG; }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    for (int32_t k = 0; k < n_src; ++k) {
-        PG_TRY(valid_source(src[k]));
-        PG_TRY(launch_rhs(sys, src[k], static_cast<double2*>(b_dev) + (size_t)k * sys->n_dof, 1, s));
-    }
+    for (int32_t k = 0; k < n_src; ++k) PG_TRY(valid_source(src[k]));
+    PG_TRY(launch_rhs(sys, src, n_src, static_cast<double2*>(b_dev), (size_t)sys->n_dof, 1, s));
     int flag = 0;
     PG_HIP(hipMemcpyAsync(&flag, sys->dflag, sizeof(int), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));

@@ -246,7 +246,8 @@ struct petgem_system {
     double2* dvec = nullptr;              // [n] D = diag(A)
     double2* dinv = nullptr;              // [n]
     // right-hand-side staging and error flag
-    double2* Rst = nullptr;               // [6][T]
+    double2* Rst = nullptr;               // [rst_copies][6][T]
+    int rst_copies = 0;
     int* dflag = nullptr;                 // device error flags
     double2* tmp = nullptr;               // [n] scratch of petgem_spmv
     // voxel grid of the learned initial guess (cached at first use)
@@ -283,16 +284,32 @@ int launch_freq_prep(petgem_system* sys, double freq, hipStream_t s);
 // right-hand side that uses it
 int noalloc_scratch(int dev, char** out);
 int rhs_noalloc(petgem_system* sys, const petgem_source* src, int32_t n_src, double2* b, hipStream_t s);
-int launch_rhs_into(petgem_system* sys, const petgem_source& src, double2* b, int b_stride, double2* Rst,
-                    int* flag, hipStream_t s);
+// one or two right-hand sides (src[0 .. ns - 1] into b + c * step); fresh: the
+// staging holds nothing of these conductivities yet
+constexpr int kRhsJobs = 8;       // tasks of a launch
+struct RhsTask {
+    petgem_system* sys;
+    const petgem_source* src;
+    int ns;
+    double2* b;
+    size_t step;
+    int stride, fresh;
+    double2* Rst;                 // [6][n_tets][ns]
+    int* flag;
+};
+int launch_rhs_tasks(const RhsTask* tasks, int n, hipStream_t s);
+int rhs_staging(petgem_system* sys, int n_src, int* copies);
+int launch_rhs_into(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,
+                    double2* Rst, int copies, int* flag, hipStream_t s);
 // time per round of a graph-replayed kernel boundary (mode 0) or of a grid
 // barrier in one cooperative kernel (mode 1), probe.hip
 int sync_probe(int32_t rounds, int32_t mode, int32_t* blocks_out, float* us_per_round, hipStream_t s);
 // layered background (layered.hip)
-int launch_rhs_layered(petgem_system* sys, const petgem_source& src, double2* Rst, int* flag, hipStream_t s);
+// into Rst[(i n_tets + t) ns]
+int launch_rhs_layered(petgem_system* sys, const petgem_source& src, double2* Rst, int ns, int* flag, hipStream_t s);
 int launch_receivers_layered(const petgem_solution* sol, int k, int32_t n_rx, double2* E, double2* Es,
                              hipStream_t s);
-int launch_rhs(petgem_system* sys, const petgem_source& src, double2* b, int b_stride,
+int launch_rhs(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,
                hipStream_t s);
 int launch_spmv_ahat(petgem_system* sys, const double2* x, double2* y, hipStream_t s);
 int tune_spmv(petgem_system* sys, hipStream_t s);

@@ -597,7 +597,7 @@ int gmres_solve(petgem_system* sys, const petgem_source& src, const petgem_opts&
 
     // right-hand side
     Timer t_rhs;
-    PG_TRY(launch_rhs(sys, src, w.b, 1, s));
+    PG_TRY(launch_rhs(sys, &src, 1, w.b, 0, 1, s));
     if (st) st->t_rhs_ms = t_rhs.ms();
 
     auto residual = [&]() -> int {   // V0 = b - Ahat u, rnorm, g, flags

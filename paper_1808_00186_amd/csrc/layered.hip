@@ -165,7 +165,7 @@ __device__ void layered_E(const double x[3], const LSrc& sp, const Layers L, con
 // into Rst[i][t] (element-major planes, as the whole-space kernel).
 __global__ void __launch_bounds__(64)
 k_rhs_layered(int T, const double* __restrict__ xyz, const int4* __restrict__ tets, const double* __restrict__ sigma,
-              Layers L, LSrc sp, GL16 gl, double r_min, double2* __restrict__ Rst, int* __restrict__ flag) {
+              Layers L, LSrc sp, GL16 gl, double r_min, double2* __restrict__ Rst, int ns, int* __restrict__ flag) {
     const int t = blockIdx.x;
     TetGeom G;
     tet_geometry(xyz, tets[t], G);
@@ -213,7 +213,7 @@ k_rhs_layered(int T, const double* __restrict__ xyz, const int4* __restrict__ te
     // i w mu0 (V/4) R  ->  multiply by i: (x, y) -> (-y, x)
     const double f = sp.w * kMu0 * G.vol * 0.25;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) Rst[(size_t)i * T + t] = make_double2(-f * R[i].y, f * R[i].x);
+    for (int i = 0; i < 6; ++i) Rst[((size_t)i * T + t) * ns] = make_double2(-f * R[i].y, f * R[i].x);
 }
 
 // Receivers: one wavefront per receiver (the layered E_p), lane 0 adds the
@@ -299,14 +299,14 @@ LSrc make_lsrc(const petgem_source& s) {
 
 }  // namespace
 
-int launch_rhs_layered(petgem_system* sys, const petgem_source& src, double2* Rst, int* flag, hipStream_t s) {
+int launch_rhs_layered(petgem_system* sys, const petgem_source& src, double2* Rst, int ns, int* flag, hipStream_t s) {
     if (!(src.pos[2] > sys->layers.z0)) {
         set_error("layered background: the source must lie above the interface");
         return PETGEM_INVALID_ARG;
     }
     hipLaunchKernelGGL(k_rhs_layered, dim3(sys->n_tets), dim3(64), 0, s, sys->n_tets, sys->xyz,
                        reinterpret_cast<const int4*>(sys->tets), sys->sigma, sys->layers, make_lsrc(src), gl16(),
-                       1e-9 * sys->h_mean, Rst, flag);
+                       1e-9 * sys->h_mean, Rst, ns, flag);
     PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }

@@ -1249,7 +1249,7 @@ int petgem_learned_x0(petgem_system* sys, petgem_net* n, const petgem_source* sr
     double2* b = n->bbuf;
     double* bn = n->bn;
     for (int k = 0; k < B; ++k) {
-        PG_TRY(launch_rhs(sys, src[k], b, 1, s));
+        PG_TRY(launch_rhs(sys, &src[k], 1, b, 0, 1, s));
         hipLaunchKernelGGL(k_vnorm, dim3(1), dim3(256), 0, s, b, sys->n_dof, bn + k);
     }
     std::vector<double> h(B);
@@ -1296,7 +1296,7 @@ int petgem_learned_x0_many(petgem_system* const* systems, petgem_net* n, const p
     }
     // |b| of every system's source
     for (int k = 0; k < n_sys; ++k) {
-        PG_TRY(launch_rhs(systems[k], src[k], n->bbuf, 1, s));
+        PG_TRY(launch_rhs(systems[k], &src[k], 1, n->bbuf, 0, 1, s));
         hipLaunchKernelGGL(k_vnorm, dim3(1), dim3(256), 0, s, n->bbuf, systems[k]->n_dof, n->bn + k);
     }
     std::vector<double> h(n_sys);

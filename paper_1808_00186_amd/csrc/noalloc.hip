@@ -14,6 +14,7 @@
 // cleared by a fill kernel at the start of each call, the staging is fully
 // overwritten before it is read, and calls that overlap on one GPU (other
 // streams, other threads) race.
+#include <algorithm>
 #include <mutex>
 
 #include "device.h"
@@ -84,8 +85,8 @@ int rhs_noalloc(petgem_system* sys, const petgem_source* src, int32_t n_src, dou
     double2* Rst = reinterpret_cast<double2*>(base + kFlagBytes);
     hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(64), 0, s, flag);
     PG_HIP(hipGetLastError());
-    for (int32_t k = 0; k < n_src; ++k)
-        PG_TRY(launch_rhs_into(sys, src[k], b + (size_t)k * sys->n_dof, 1, Rst, flag, s));
+    const size_t fit = (kScratchBytes - kFlagBytes) / ((size_t)6 * sys->n_tets * sizeof(double2));
+    PG_TRY(launch_rhs_into(sys, src, n_src, b, (size_t)sys->n_dof, 1, Rst, (int)std::min<size_t>(fit, 2 * kRhsJobs), flag, s));
     int flag_h = 0;
     PG_HIP(hipMemcpyAsync(&flag_h, flag, sizeof(int), hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));

@@ -6,12 +6,22 @@
 //   degree-2 rule and integrate it against the 6 edge basis functions.
 // k_rhs_gather: one thread per DOF sums its incident element entries in
 //   increasing element order (deterministic, no atomics).
+//   Both take up to kRhsJobs jobs (sources of one system, or systems of a
+//   batch) in one launch, a row of blocks each: one at a time they leave the
+//   chip partly idle (9 sources on 56,000 elements took 18 launches of 5 to
+//   9 us each) and pay a kernel boundary per launch. A job is one source, or
+//   two of one system with their entries side by side: the gather is bound by
+//   its requests, which then fetch 32 bytes each (26.1 -> 20.5 us a source on
+//   750,000 elements). The element kernel is bound by its double-precision
+//   arithmetic.
 // k_receivers: one thread per receiver evaluates the 6 basis functions of its
 //   element at the receiver and adds the primary field.
 // k_receivers_h: the magnetic field H = curl E / (i w mu0) (Faraday's law of
 //   Section 2 with e^{-iwt}): the curl of the secondary field is constant in
 //   an element, sum_i e_i 2 s_i l_i grad lambda_a x grad lambda_b, and the
 //   primary part is the dipole's analytic H.
+#include <algorithm>
+
 #include "device.h"
 #include "internal.h"
 
@@ -31,6 +41,24 @@ struct SrcParams {
     double inv_wmu; // 1 / (w mu0)
 };
 
+// One or two right-hand sides of a system: sources, staging and outputs.
+struct RhsJob {
+    int T, n, stride, fresh;      // fresh: the staging holds no zeros yet where dsigma = 0
+    const double* xyz;
+    const int4* tets;
+    const double* sigma;
+    double sigma_bg, r_min;
+    SrcParams sp[2];
+    double wmu[2];
+    double2* Rst;                 // [6][T][sources]
+    int* flag;
+    const int32_t *iptr, *islot;
+    double2* b[2];
+};
+struct RhsJobs {                  // by value: 2.5 KB of kernel arguments
+    RhsJob j[kRhsJobs];
+};
+
 SrcParams make_src(const petgem_source& s, double sigma_bg) {
     SrcParams p;
     for (int k = 0; k < 3; ++k) { p.pos[k] = s.pos[k]; p.dir[k] = s.dir[k]; }
@@ -42,62 +70,85 @@ SrcParams make_src(const petgem_source& s, double sigma_bg) {
     return p;
 }
 
-__global__ void __launch_bounds__(256)
-k_rhs_elem(int T, const double* __restrict__ xyz, const int4* __restrict__ tets,
-           const double* __restrict__ sigma, double sigma_bg, SrcParams sp, double wmu,
-           double r_min, double2* __restrict__ Rst, int* __restrict__ flag) {
-    int t = blockIdx.x * blockDim.x + threadIdx.x;
+// (256, 3): 136 registers, three waves per SIMD; the four points unrolled
+// without the bound take 256 and two.
+__global__ void __launch_bounds__(256, 3)
+k_rhs_elem(RhsJobs jobs, int ns) {
+    const int c = (int)blockIdx.y % ns;
+    const RhsJob& job = jobs.j[blockIdx.y / ns];
+    const int T = job.T;
+    const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= T) return;
-    const double ds = sigma[t] - sigma_bg;
+    double2* __restrict__ Rst = job.Rst + c;
+    const double r_min = job.r_min;
+    const double ds = job.sigma[t] - job.sigma_bg;
     if (ds == 0.0) {
+        if (!job.fresh) return;
 #pragma unroll
-        for (int i = 0; i < 6; ++i) Rst[(size_t)i * T + t] = make_double2(0.0, 0.0);
+        for (int i = 0; i < 6; ++i) Rst[((size_t)i * T + t) * ns] = make_double2(0.0, 0.0);
         return;
     }
     TetGeom G;
-    tet_geometry(xyz, tets[t], G);
-    // 4-point degree-2 rule: barycentric (a,b,b,b) and permutations, weights V/4
+    tet_geometry(job.xyz, job.tets[t], G);
+    // 4-point degree-2 rule: barycentric (a,b,b,b) and permutations, weights
+    // V/4. N_i = s_i l_i (lambda_a grad lambda_b - lambda_b grad lambda_a), so
+    // sum_q N_i(x_q) . E_q = s_i l_i (grad lambda_b . S_a - grad lambda_a . S_b)
+    // with S_v = sum_q lambda_v(x_q) E_q = qb sum_q E_q + (qa - qb) E_v
     const double qa = 0.58541019662496845446;   // (5 + 3 sqrt 5) / 20
     const double qb = 0.13819660112501051518;   // (5 - sqrt 5) / 20
-    double2 R[6];
+    double xs[3];
 #pragma unroll
-    for (int i = 0; i < 6; ++i) R[i] = make_double2(0.0, 0.0);
+    for (int k = 0; k < 3; ++k) xs[k] = qb * (G.X[0][k] + G.X[1][k] + G.X[2][k] + G.X[3][k]);
     bool singular = false;
+    const SrcParams& sp = job.sp[c];
+    double2 S[4][3], sum[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sum[k] = make_double2(0.0, 0.0);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        double lam[4] = {qb, qb, qb, qb};
-        lam[q] = qa;
         double x[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k)
-            x[k] = lam[0] * G.X[0][k] + lam[1] * G.X[1][k] + lam[2] * G.X[2][k] + lam[3] * G.X[3][k];
-        double d0 = x[0] - sp.pos[0], d1 = x[1] - sp.pos[1], d2 = x[2] - sp.pos[2];
+        for (int k = 0; k < 3; ++k) x[k] = xs[k] + (qa - qb) * G.X[q][k];
+        const double d0 = x[0] - sp.pos[0], d1 = x[1] - sp.pos[1], d2 = x[2] - sp.pos[2];
         if (d0 * d0 + d1 * d1 + d2 * d2 <= r_min * r_min) singular = true;
-        double2 E[3];
-        dipole_E(x, sp.pos, sp.dir, sp.kappa, sp.pref, E);
+        dipole_E(x, sp.pos, sp.dir, sp.kappa, sp.pref, S[q]);
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const int a = kE0[i], b = kE1[i];
-            double n0 = G.sl[i] * (lam[a] * G.g[b][0] - lam[b] * G.g[a][0]);
-            double n1 = G.sl[i] * (lam[a] * G.g[b][1] - lam[b] * G.g[a][1]);
-            double n2 = G.sl[i] * (lam[a] * G.g[b][2] - lam[b] * G.g[a][2]);
-            R[i].x += n0 * E[0].x + n1 * E[1].x + n2 * E[2].x;
-            R[i].y += n0 * E[0].y + n1 * E[1].y + n2 * E[2].y;
-        }
+        for (int k = 0; k < 3; ++k) sum[k] = cadd(sum[k], S[q][k]);
     }
-    if (singular) atomicOr(flag, 1);
-    // i w mu0 dsigma (V/4) R  ->  multiply by i: (x, y) -> (-y, x)
-    const double f = wmu * ds * G.vol * 0.25;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) Rst[(size_t)i * T + t] = make_double2(-f * R[i].y, f * R[i].x);
+    for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) S[v][k] = cadd(cscale(sum[k], qb), cscale(S[v][k], qa - qb));
+    // i w mu0 dsigma (V/4) R  ->  multiply by i: (x, y) -> (-y, x)
+    const double f = job.wmu[c] * ds * G.vol * 0.25;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const int a = kE0[i], b = kE1[i];
+        double2 R = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            R.x += G.g[b][k] * S[a][k].x - G.g[a][k] * S[b][k].x;
+            R.y += G.g[b][k] * S[a][k].y - G.g[a][k] * S[b][k].y;
+        }
+        const double fl = f * G.sl[i];
+        Rst[((size_t)i * T + t) * ns] = make_double2(-fl * R.y, fl * R.x);
+    }
+    if (singular) atomicOr(job.flag, 1);
 }
 
+template <int NS>
 __global__ void __launch_bounds__(256)
-k_rhs_gather(int n, int T, const int32_t* __restrict__ iptr, const int32_t* __restrict__ islot,
-             const double2* __restrict__ Rst, double2* __restrict__ b, int stride) {
-    int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    double2 acc = make_double2(0.0, 0.0);
+k_rhs_gather(RhsJobs jobs) {
+    const RhsJob& job = jobs.j[blockIdx.y];
+    const int r = blockIdx.x * 256 + threadIdx.x;
+    if (r >= job.n) return;
+    const int T = job.T;
+    const int32_t* __restrict__ iptr = job.iptr;
+    const int32_t* __restrict__ islot = job.islot;
+    const double2* __restrict__ Rst = job.Rst;
+    double2 acc[NS];
+#pragma unroll
+    for (int c = 0; c < NS; ++c) acc[c] = make_double2(0.0, 0.0);
     const int32_t k1 = iptr[r + 1];
     // four incidences, then their entries, in flight at a time; the sum keeps
     // the list order
@@ -105,17 +156,22 @@ k_rhs_gather(int n, int T, const int32_t* __restrict__ iptr, const int32_t* __re
         int32_t sl[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) sl[q] = k + q < k1 ? islot[k + q] : -1;
-        double2 v[4];
+        double2 v[4][NS];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int32_t t = sl[q] / 6, i = sl[q] - 6 * t;
-            v[q] = sl[q] >= 0 ? Rst[(size_t)i * T + t] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int c = 0; c < NS; ++c)
+                v[q][c] = sl[q] >= 0 ? Rst[((size_t)i * T + t) * NS + c] : make_double2(0.0, 0.0);
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            if (sl[q] >= 0) acc = cadd(acc, v[q]);
+            if (sl[q] >= 0)
+#pragma unroll
+                for (int c = 0; c < NS; ++c) acc[c] = cadd(acc[c], v[q][c]);
     }
-    b[(size_t)r * stride] = acc;
+#pragma unroll
+    for (int c = 0; c < NS; ++c) job.b[c][(size_t)r * job.stride] = acc[c];
 }
 
 __global__ void k_receivers(int n_rx, const double* __restrict__ rxyz, const int32_t* __restrict__ rtet,
@@ -194,32 +250,113 @@ __global__ void k_receivers_h(int n_rx, const double* __restrict__ rxyz, const i
 
 }  // namespace
 
-// The element staging and the singular-source flag of one right-hand side,
-// written where the caller says (the system's buffers, or the scratch of the
-// allocation-free entry point).
-int launch_rhs_into(petgem_system* sys, const petgem_source& src, double2* b, int b_stride, double2* Rst,
-                    int* flag, hipStream_t s) {
-    const int T = sys->n_tets;
-    SrcParams sp = make_src(src, sys->sigma_bg);
-    const double wmu = 2.0 * kPi * src.freq_hz * kMu0;
-    if (sys->layers.on) {
-        PG_TRY(launch_rhs_layered(sys, src, Rst, flag, s));
-    } else {
-        hipLaunchKernelGGL(k_rhs_elem, dim3(ceil_div(T, 256)), dim3(256), 0, s, T, sys->xyz,
-                           reinterpret_cast<const int4*>(sys->tets), sys->sigma, sys->sigma_bg, sp, wmu,
-                           1e-9 * sys->h_mean, Rst, flag);
+// The element staging and the singular-source flag of every right-hand side
+// are where the task says (the system's buffers, or the scratch of the
+// allocation-free entry point). Tasks run in order, kRhsJobs to a launch, or
+// fewer where the next one has another number of sources or shares its
+// staging with one of them (a batch may name a system twice).
+int launch_rhs_tasks(const RhsTask* tasks, int n, hipStream_t s) {
+    for (int k0 = 0, nj = 0; k0 < n; k0 += nj) {
+        const int ns = tasks[k0].ns;
+        auto apart = [&](int k) {
+            for (int q = k0; q < k; ++q)
+                if (tasks[q].Rst == tasks[k].Rst) return false;
+            return tasks[k].ns == ns;
+        };
+        for (nj = 1; nj < kRhsJobs && k0 + nj < n && apart(k0 + nj);) ++nj;
+        RhsJobs jobs{};
+        int most_t = 0, most_n = 0;
+        for (int k = 0; k < nj; ++k) {
+            const RhsTask& t = tasks[k0 + k];
+            const petgem_system* sys = t.sys;
+            RhsJob& j = jobs.j[k];
+            j.n = sys->n_dof;
+            j.T = sys->n_tets;
+            j.stride = t.stride;
+            j.fresh = t.fresh;
+            j.xyz = sys->xyz;
+            j.tets = reinterpret_cast<const int4*>(sys->tets);
+            j.sigma = sys->sigma;
+            j.sigma_bg = sys->sigma_bg;
+            j.r_min = 1e-9 * sys->h_mean;
+            for (int c = 0; c < ns; ++c) {
+                j.sp[c] = make_src(t.src[c], sys->sigma_bg);
+                j.wmu[c] = 2.0 * kPi * t.src[c].freq_hz * kMu0;
+                j.b[c] = t.b + c * t.step;
+            }
+            j.Rst = t.Rst;
+            j.flag = t.flag;
+            j.iptr = sys->iptr;
+            j.islot = sys->islot;
+            most_n = std::max(most_n, j.n);
+            if (!sys->layers.on) most_t = std::max(most_t, j.T);
+        }
+        const dim3 ge(ceil_div(most_t, 256), nj * ns), gg(ceil_div(most_n, 256), nj);
+        if (most_t > 0) {
+            RhsJobs whole = jobs;
+            for (int k = 0; k < nj; ++k)
+                if (tasks[k0 + k].sys->layers.on) whole.j[k].T = 0;
+            hipLaunchKernelGGL(k_rhs_elem, ge, dim3(256), 0, s, whole, ns);
+            PG_HIP(hipGetLastError());
+        }
+        for (int k = 0; k < nj; ++k) {
+            const RhsTask& t = tasks[k0 + k];
+            for (int c = 0; c < ns && t.sys->layers.on; ++c)
+                PG_TRY(launch_rhs_layered(t.sys, t.src[c], t.Rst + c, ns, t.flag, s));
+        }
+        if (ns == 2) hipLaunchKernelGGL(k_rhs_gather<2>, gg, dim3(256), 0, s, jobs);
+        else hipLaunchKernelGGL(k_rhs_gather<1>, gg, dim3(256), 0, s, jobs);
         PG_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_rhs_gather, dim3(ceil_div(sys->n_dof, 256)), dim3(256), 0, s, sys->n_dof,
-                       T, sys->iptr, sys->islot, Rst, b, b_stride);
-    PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }
 
-int launch_rhs(petgem_system* sys, const petgem_source& src, double2* b, int b_stride,
+// Staging of one system's right-hand sides side by side: a pair, and as many
+// as fill a launch while they stay within kRhsStage (the Infinity Cache holds 256 MB,
+// and the gather should find what the elements wrote there).
+constexpr size_t kRhsStage = (size_t)128 << 20;
+int rhs_staging(petgem_system* sys, int n_src, int* copies) {
+    const size_t one = (size_t)6 * sys->n_tets;
+    const int fit = (int)std::max<size_t>(2, kRhsStage / (one * sizeof(double2)));
+    *copies = std::min(std::min(n_src, 2 * kRhsJobs), fit);
+    if (sys->rst_copies < *copies) {
+        dfree(sys->Rst);
+        sys->rst_copies = 0;
+        PG_TRY(dalloc(&sys->Rst, one * *copies));
+        sys->rst_copies = *copies;
+    }
+    return PETGEM_OK;
+}
+
+// Right-hand sides of n_src sources of one system into b + k * step with the
+// given row stride, staged in `copies` buffers from Rst on: two sources to a
+// task where two buffers are there.
+int launch_rhs_into(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,
+                    double2* Rst, int copies, int* flag, hipStream_t s) {
+    const size_t one = (size_t)6 * sys->n_tets;
+    copies = std::min(copies, 2 * kRhsJobs);
+    if (copies > 1) copies &= ~1;     // a pair keeps its two buffers from one round to the next
+    for (int k0 = 0; k0 < n_src; k0 += copies) {
+        RhsTask t[2 * kRhsJobs];
+        const int nc = std::min(copies, n_src - k0);
+        int nt = 0;
+        for (int k = 0; k < nc;) {
+            // a single last source finds no zeros of its own layout
+            const int ns = copies > 1 && k + 1 < nc ? 2 : 1;
+            t[nt++] = RhsTask{sys, src + k0 + k, ns, b + (size_t)(k0 + k) * step, step, stride,
+                              k0 == 0 || (ns == 1 && copies > 1), Rst + (size_t)k * one, flag};
+            k += ns;
+        }
+        PG_TRY(launch_rhs_tasks(t, nt, s));
+    }
+    return PETGEM_OK;
+}
+
+int launch_rhs(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,
                hipStream_t s) {
-    if (!sys->Rst) PG_TRY(dalloc(&sys->Rst, (size_t)6 * sys->n_tets));
-    return launch_rhs_into(sys, src, b, b_stride, sys->Rst, sys->dflag, s);
+    int copies = 0;
+    PG_TRY(rhs_staging(sys, n_src, &copies));
+    return launch_rhs_into(sys, src, n_src, b, step, stride, sys->Rst, copies, sys->dflag, s);
 }
 
 int launch_receivers(const petgem_solution* sol, int32_t n_rx, double2* E, double2* Es,
