@@ -340,8 +340,8 @@ int petgem_solution_copy(const petgem_solution* sol, void* x_dev, void* stream);
 int petgem_get_dof_edges(const petgem_system* sys, int32_t* edges);
 int petgem_get_csr(const petgem_system* sys, int32_t* row_ptr, int32_t* col,
                    double* K, double* Ms, void* stream);
-/* y = A(freq) x for device complex128 vectors of length n_dof, with the
- * kernel the double-precision solver uses. */
+/* y = A(freq) x for device complex128 vectors of length n_dof, in double
+ * precision on the assembled K and M_s. */
 int petgem_spmv(petgem_system* sys, double freq, const void* x_dev, void* y_dev,
                 void* stream);
 /* Host-only preprocessing (no GPU call): the interior-edge numbering and the
@@ -357,7 +357,7 @@ int petgem_mesh_pattern(const petgem_mesh* mesh, int32_t* n_dof, int64_t* nnz,
 int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, double tol,
                   int32_t* elem);
 /* Autotuner choices of a system: lanes per row of the double-precision CSR
- * SpMV (4, 8 or 16; 0 before the first solve) and the measured per-launch
+ * SpMV (4, 8 or 16; 0 before the first GMRES solve) and the measured per-launch
  * times of the three variants in ms (host float [3], may be NULL). */
 int petgem_tuning(const petgem_system* sys, int32_t* spmv_group, float* spmv_ms);
 /* Seconds spent in the host preprocessing of the last petgem_assemble. */

@@ -84,7 +84,7 @@ void release_system(petgem_system* sys) {
     sys->res[0].release();
     sys->res[1].release();
     dfree(sys->K32); dfree(sys->Ms32); dfree(sys->Ahat); dfree(sys->dvec); dfree(sys->dinv);
-    dfree(sys->Rst); dfree(sys->dflag); dfree(sys->tmp);
+    dfree(sys->Rst); dfree(sys->dflag);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);
     sys->gw.release();
     release_block_work(sys->bw);
@@ -519,11 +519,7 @@ int petgem_spmv(petgem_system* sys, double freq, const void* x_dev, void* y_dev,
     PG_TRY(check_sys(sys));
     if (!x_dev || !y_dev || !(freq > 0.0)) { set_error("spmv needs x, y and a positive frequency"); return PETGEM_INVALID_ARG; }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_TRY(launch_freq_prep(sys, freq, s));
-    PG_TRY(tune_spmv(sys, s));
-    // A x = Ahat (D x) with the solver's CSR kernel
-    PG_TRY(launch_spmv_unscaled(sys, static_cast<const double2*>(x_dev), static_cast<double2*>(y_dev), s));
-    return PETGEM_OK;
+    return launch_spmv(sys, freq, static_cast<const double2*>(x_dev), static_cast<double2*>(y_dev), s);
 }
 
 void petgem_free_system(petgem_system* sys) {

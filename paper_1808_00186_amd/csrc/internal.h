@@ -249,7 +249,6 @@ struct petgem_system {
     double2* Rst = nullptr;               // [rst_copies][6][T]
     int rst_copies = 0;
     int* dflag = nullptr;                 // device error flags
-    double2* tmp = nullptr;               // [n] scratch of petgem_spmv
     // voxel grid of the learned initial guess (cached at first use)
     int32_t* vox_tet = nullptr;           // [32^3] element containing each voxel centre
     int32_t* vox_dof = nullptr;           // [32^3][6]
@@ -311,9 +310,9 @@ int launch_receivers_layered(const petgem_solution* sol, int k, int32_t n_rx, do
                              hipStream_t s);
 int launch_rhs(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,
                hipStream_t s);
-int launch_spmv_ahat(petgem_system* sys, const double2* x, double2* y, hipStream_t s);
 int tune_spmv(petgem_system* sys, hipStream_t s);
-int launch_spmv_unscaled(petgem_system* sys, const double2* x, double2* y, hipStream_t s);
+// y = A(freq) x, double precision
+int launch_spmv(petgem_system* sys, double freq, const double2* x, double2* y, hipStream_t s);
 int launch_receivers(const petgem_solution* sol, int32_t n_rx, double2* E, double2* Es,
                      hipStream_t s, bool magnetic = false);
 int gmres_solve(petgem_system* sys, const petgem_source& src, const petgem_opts& o,

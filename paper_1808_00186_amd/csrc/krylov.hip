@@ -563,20 +563,6 @@ int tune_spmv(petgem_system* sys, hipStream_t s) {
     return PETGEM_OK;
 }
 
-int launch_spmv_ahat(petgem_system* sys, const double2* x, double2* y, hipStream_t s) {
-    spmv_launch<false>(sys->spmv_group, sys->n_dof, sys->row_ptr, sys->col, sys->Ahat, x, nullptr, y,
-                       nullptr, s);
-    PG_HIP(hipGetLastError());
-    return PETGEM_OK;
-}
-
-int launch_spmv_unscaled(petgem_system* sys, const double2* x, double2* y, hipStream_t s) {
-    const int n = sys->n_dof;
-    if (!sys->tmp) PG_TRY(dalloc(&sys->tmp, (size_t)n));
-    hipLaunchKernelGGL(k_scale_in, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, sys->dvec, x, sys->tmp);
-    return launch_spmv_ahat(sys, sys->tmp, y, s);
-}
-
 int gmres_solve(petgem_system* sys, const petgem_source& src, const petgem_opts& o,
                 const double2* x0, double2* x_out, hipStream_t s, petgem_stats* st) {
     const int n = sys->n_dof;
