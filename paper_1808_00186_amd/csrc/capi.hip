@@ -84,7 +84,7 @@ void release_system(petgem_system* sys) {
     sys->res[0].release();
     sys->res[1].release();
     dfree(sys->K32); dfree(sys->Ms32); dfree(sys->Ahat); dfree(sys->dvec); dfree(sys->dinv);
-    dfree(sys->Rst); dfree(sys->dflag);
+    dfree(sys->Rst); dfree(sys->hot); dfree(sys->dflag);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);
     sys->gw.release();
     release_block_work(sys->bw);
@@ -239,6 +239,8 @@ int petgem_set_background(petgem_system* sys, const petgem_background* bg) {
         set_error("background: layered 0 or 1, positive finite conductivities, finite z0");
         return PETGEM_INVALID_ARG;
     }
+    // allocated here: the right-hand side itself may not (petgem_rhs_noalloc)
+    if (bg->layered && !sys->hot) PG_TRY(dalloc(&sys->hot, (size_t)sys->n_tets + 1));
     sys->layers.on = bg->layered;
     sys->layers.z0 = bg->z0;
     sys->layers.s_up = bg->sigma_above;

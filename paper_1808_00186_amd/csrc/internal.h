@@ -248,6 +248,7 @@ struct petgem_system {
     // right-hand-side staging and error flag
     double2* Rst = nullptr;               // [rst_copies][6][T]
     int rst_copies = 0;
+    int* hot = nullptr;                   // layered background: count, then the elements with dsigma != 0
     int* dflag = nullptr;                 // device error flags
     // voxel grid of the learned initial guess (cached at first use)
     int32_t* vox_tet = nullptr;           // [32^3] element containing each voxel centre
@@ -304,8 +305,9 @@ int launch_rhs_into(petgem_system* sys, const petgem_source* src, int n_src, dou
 // barrier in one cooperative kernel (mode 1), probe.hip
 int sync_probe(int32_t rounds, int32_t mode, int32_t* blocks_out, float* us_per_round, hipStream_t s);
 // layered background (layered.hip)
-// into Rst[(i n_tets + t) ns]
-int launch_rhs_layered(petgem_system* sys, const petgem_source& src, double2* Rst, int ns, int* flag, hipStream_t s);
+// entries of n <= 2 kRhsJobs sources, source c's into Rst[c][(i n_tets + t) ns]
+int launch_rhs_layered(petgem_system* sys, const petgem_source* src, double2* const* Rst, int n, int ns, int fresh,
+                       int* flag, hipStream_t s);
 int launch_receivers_layered(const petgem_solution* sol, int k, int32_t n_rx, double2* E, double2* Es,
                              hipStream_t s);
 int launch_rhs(petgem_system* sys, const petgem_source* src, int n_src, double2* b, size_t step, int stride,

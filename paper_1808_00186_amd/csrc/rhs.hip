@@ -299,10 +299,20 @@ int launch_rhs_tasks(const RhsTask* tasks, int n, hipStream_t s) {
             hipLaunchKernelGGL(k_rhs_elem, ge, dim3(256), 0, s, whole, ns);
             PG_HIP(hipGetLastError());
         }
-        for (int k = 0; k < nj; ++k) {
+        for (int k = 0, m = 0; k < nj; k += m) {   // the layered sources of a system together
             const RhsTask& t = tasks[k0 + k];
-            for (int c = 0; c < ns && t.sys->layers.on; ++c)
-                PG_TRY(launch_rhs_layered(t.sys, t.src[c], t.Rst + c, ns, t.flag, s));
+            for (m = 1; k + m < nj && tasks[k0 + k + m].sys == t.sys;) ++m;
+            if (!t.sys->layers.on) continue;
+            petgem_source src[2 * kRhsJobs];
+            double2* Rst[2 * kRhsJobs];
+            int fresh = 0;
+            for (int c = 0; c < m * ns; ++c) {
+                const RhsTask& u = tasks[k0 + k + c / ns];
+                src[c] = u.src[c % ns];
+                Rst[c] = u.Rst + c % ns;
+                fresh |= u.fresh;
+            }
+            PG_TRY(launch_rhs_layered(t.sys, src, Rst, m * ns, ns, fresh, t.flag, s));
         }
         if (ns == 2) hipLaunchKernelGGL(k_rhs_gather<2>, gg, dim3(256), 0, s, jobs);
         else hipLaunchKernelGGL(k_rhs_gather<1>, gg, dim3(256), 0, s, jobs);
@@ -335,16 +345,19 @@ int launch_rhs_into(petgem_system* sys, const petgem_source* src, int n_src, dou
                     double2* Rst, int copies, int* flag, hipStream_t s) {
     const size_t one = (size_t)6 * sys->n_tets;
     copies = std::min(copies, 2 * kRhsJobs);
-    if (copies > 1) copies &= ~1;     // a pair keeps its two buffers from one round to the next
+    // the layered sources' elements run in one launch however they are staged,
+    // and a launch holds kRhsJobs tasks of the same number of sources
+    const bool pairs = copies > 1 && !sys->layers.on;
+    if (pairs) copies &= ~1;     // a pair keeps its two buffers from one round to the next
     for (int k0 = 0; k0 < n_src; k0 += copies) {
         RhsTask t[2 * kRhsJobs];
         const int nc = std::min(copies, n_src - k0);
         int nt = 0;
         for (int k = 0; k < nc;) {
             // a single last source finds no zeros of its own layout
-            const int ns = copies > 1 && k + 1 < nc ? 2 : 1;
+            const int ns = pairs && k + 1 < nc ? 2 : 1;
             t[nt++] = RhsTask{sys, src + k0 + k, ns, b + (size_t)(k0 + k) * step, step, stride,
-                              k0 == 0 || (ns == 1 && copies > 1), Rst + (size_t)k * one, flag};
+                              k0 == 0 || (ns == 1 && pairs), Rst + (size_t)k * one, flag};
             k += ns;
         }
         PG_TRY(launch_rhs_tasks(t, nt, s));
