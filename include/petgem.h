@@ -119,8 +119,10 @@ typedef struct {
     double  rtol;           /* stop when |b - A x|_2 <= rtol |b|_2 (true
                                residual, double precision)                      */
     double  inner_rtol;     /* MIXED: relative tolerance of each inner solve    */
-    int32_t use_graph;      /* replay captured HIP graphs for the Krylov loop   */
-    int32_t profile;        /* time the sparse-matrix kernels with HIP events   */
+    int32_t use_graph;      /* replay captured HIP graphs for the Krylov loop
+                               (solves that run kernel by kernel)               */
+    int32_t profile;        /* time the sparse-matrix kernels with HIP events
+                               (the solve then runs kernel by kernel)           */
     int32_t verbose;        /* print one progress line per refinement step or
                                per 10 GMRES cycles to stderr; 2 (mixed COCG):
                                also one line per column and refinement step    */
@@ -168,8 +170,9 @@ typedef struct {
                                slice columns in flight), 3 = sliced ELLPACK
                                with the next b slice columns' indices and
                                values loaded during the current b gathers,
-                               4 = the fused step, which one column of one
-                               mesh runs whatever shape is tuned (or when
+                               4 = the fused step (kernel by kernel, or the
+                               whole inner solve in one launch), which one
+                               column of one mesh runs whatever shape is tuned (or when
                                shape 3 is chosen): a shape-3 product that
                                also sums q^T D^-1 r and q^T D^-1 q, then one
                                vector kernel applying alpha and beta;
@@ -183,7 +186,8 @@ typedef struct {
                                per row, b columns per lane) the profile
                                times instead;
                                GMRES: the lanes per row of the complex128
-                               CSR SpMV                                         */
+                               CSR SpMV (1: the whole solve in one launch,
+                               a lane per row)                                  */
     double  b_norm;         /* |b|_2 of the source's right-hand side            */
     int32_t block_iters;    /* PETGEM_BCOCG: iterations of the block phase; when
                                the block recurrence lost conjugacy (a

@@ -175,25 +175,33 @@ int launch_assembly(petgem_system* sys, const double* sigma, hipStream_t s) {
     hipLaunchKernelGGL(k_gather, dim3(ceil_div(sys->nnz, 256)), dim3(256), 0, s, sys->nnz, T, sys->cptr, sys->cidx,
                        sys->col, sys->KMst, sys->K, sys->Ms, sys->Kd, sys->Msd);
     PG_HIP(hipGetLastError());
-    sys->cached_freq = -1.0;   // operators derived from K, Ms are stale
+    sys->cached_freq = sys->diag_freq = -1.0;   // operators derived from K, Ms are stale
     sys->have32 = false;
-    sys->res[0].values = sys->res[1].values = false;
+    for (Resident& L : sys->res) {
+        L.values = false;
+        L.a_freq = -1.0;
+    }
+    return PETGEM_OK;
+}
+
+int launch_diag(petgem_system* sys, double freq, hipStream_t s) {
+    if (sys->diag_freq == freq) return PETGEM_OK;
+    const int n = sys->n_dof;
+    if (!sys->dvec) PG_TRY(dalloc(&sys->dvec, n));
+    if (!sys->dinv) PG_TRY(dalloc(&sys->dinv, n));
+    hipLaunchKernelGGL(k_jacobi, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, 2.0 * kPi * freq * kMu0, sys->Kd,
+                       sys->Msd, sys->dvec, sys->dinv);
+    PG_HIP(hipGetLastError());
+    sys->diag_freq = freq;
     return PETGEM_OK;
 }
 
 int launch_freq_prep(petgem_system* sys, double freq, hipStream_t s) {
+    PG_TRY(launch_diag(sys, freq, s));
     if (sys->cached_freq == freq) return PETGEM_OK;
-    const int n = sys->n_dof;
-    if (!sys->Ahat) {
-        PG_TRY(dalloc(&sys->Ahat, sys->nnz));
-        PG_TRY(dalloc(&sys->dvec, n));
-        PG_TRY(dalloc(&sys->dinv, n));
-    }
-    const double wmu = 2.0 * kPi * freq * kMu0;
-    hipLaunchKernelGGL(k_jacobi, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, wmu, sys->Kd,
-                       sys->Msd, sys->dvec, sys->dinv);
-    hipLaunchKernelGGL(k_ahat, dim3(ceil_div(sys->nnz, 256)), dim3(256), 0, s, sys->nnz, wmu, sys->col, sys->K,
-                       sys->Ms, sys->dinv, sys->Ahat);
+    if (!sys->Ahat) PG_TRY(dalloc(&sys->Ahat, sys->nnz));
+    hipLaunchKernelGGL(k_ahat, dim3(ceil_div(sys->nnz, 256)), dim3(256), 0, s, sys->nnz, 2.0 * kPi * freq * kMu0,
+                       sys->col, sys->K, sys->Ms, sys->dinv, sys->Ahat);
     PG_HIP(hipGetLastError());
     sys->cached_freq = freq;
     return PETGEM_OK;

@@ -87,6 +87,7 @@ void release_system(petgem_system* sys) {
     dfree(sys->Rst); dfree(sys->hot); dfree(sys->dflag);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);
     sys->gw.release();
+    sys->gres.release();
     release_block_work(sys->bw);
     sys->rxc.release();
 }

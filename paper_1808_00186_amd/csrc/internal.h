@@ -116,9 +116,11 @@ struct Resident {
     int32_t* halo = nullptr;      // [G][hmax] exchange place of each outer neighbour
     int32_t* nh = nullptr;        // [G]
     uint64_t* idx = nullptr;      // [G][8][chunks][64] four LDS indices
-    float* K = nullptr;           // [G][8][chunks][64][4]
+    float* K = nullptr;           // [G][8][chunks][64][4] (built when the COCG first needs them)
     float* M = nullptr;
     bool values = false;          // K, M current
+    double2* A = nullptr;         // [G][8][chunks][4][64] A D^-1 of the plain GMRES at a_freq
+    double a_freq = -1.0;
     void release();
 };
 
@@ -163,6 +165,14 @@ struct GmresWork {
 };
 
 // ------------------------------------------------------- resident COCG
+struct GmOut {                    // what a resident GMRES reports
+    double bnorm, rnorm;
+    int iters, cycles, status, pad;
+};
+struct GmHost {
+    GmOut out;
+    int abort, flag;
+};
 // Device tables and exchange buffers of one solve's resident launches.
 struct ResWork {
     struct Round { int blk0 = 0, nblk = 0; size_t lds = 0; };
@@ -171,7 +181,11 @@ struct ResWork {
     int* blk = nullptr;           // domain of each logical block
     unsigned long long *words = nullptr, *pex = nullptr;
     int *abort = nullptr, *abort_h = nullptr;
-    size_t cap_doms = 0, cap_blk = 0, cap_words = 0, cap_pex = 0, n_words = 0, n_pex = 0;
+    double2* V = nullptr;         // GMRES: basis, in the layout's order
+    double2 *b = nullptr, *u = nullptr;
+    GmOut* out = nullptr;
+    GmHost* host = nullptr;       // pinned
+    size_t cap_doms = 0, cap_blk = 0, cap_words = 0, cap_pex = 0, cap_v = 0, n_words = 0, n_pex = 0;
     void release();
 };
 // One mesh of a solve: its rows start at row_off of the block vectors, its C
@@ -241,7 +255,8 @@ struct petgem_system {
     petgem::Resident res[2]; // finer and coarser split for the resident COCG (built on first use)
     petgem::Ssor ssor32;     // multicolour L / U split of K32 / Ms32 (built on first SSOR use)
     // frequency-specific operator of the FP64 GMRES: Ahat = A D^{-1}
-    double cached_freq = -1.0;
+    double cached_freq = -1.0;            // of Ahat
+    double diag_freq = -1.0;              // of dvec, dinv
     double2* Ahat = nullptr;              // [nnz]
     double2* dvec = nullptr;              // [n] D = diag(A)
     double2* dinv = nullptr;              // [n]
@@ -261,6 +276,7 @@ struct petgem_system {
     bool spmv_tuned = false;
     float spmv_tune_ms[3] = {0.f, 0.f, 0.f};  // measured 4/8/16-lane SpMV times
     petgem::GmresWork gw;
+    petgem::ResWork gres;                 // tables and exchange buffers of the resident GMRES
     petgem::BlockWork* bw = nullptr;
     petgem::ReceiverCache rxc;
 };
@@ -279,6 +295,7 @@ namespace petgem {
 // Launchers implemented in the .hip units; all ordered on `s`.
 // sigma: device [n_tets], kept in sys->sigma by the launch
 int launch_assembly(petgem_system* sys, const double* sigma, hipStream_t s);
+int launch_diag(petgem_system* sys, double freq, hipStream_t s);
 int launch_freq_prep(petgem_system* sys, double freq, hipStream_t s);
 // allocation-free scratch of this device (looked up once per device) and the
 // right-hand side that uses it
@@ -332,6 +349,8 @@ int ensure_fp32(petgem_system* sys, hipStream_t s);
 // it *W.abort is non-zero if a wait ran out.
 int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits);
 int res_run(ResWork& W, int max_inner, hipStream_t s);
+int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, const double2* b,
+           double2* u, GmOut* out, hipStream_t s, bool* fits);
 // the multicolour split of the operator (pattern built once, values gathered
 // again after every reassembly); ssor_apply: z = M^-1 r of one complex64
 // column at one frequency (device vectors of n_dof)

@@ -14,12 +14,16 @@
 // Pythagorean norm unreliable (beta^2 <= eta |w|^2) the step requests a
 // second Gram-Schmidt pass, whose kernels otherwise exit at once. All
 // reductions use a fixed partition and order, so the solve is bitwise
-// reproducible. Every kernel reads the cycle's `done` flag and returns early
+// reproducible. A mesh whose rows fit the resident layout runs the same steps
+// in one launch (k_gm_solve in resident.hip); the kernels here serve larger
+// meshes, longer restarts, initial guesses, profiling and progress lines.
+// Every kernel reads the cycle's `done` flag and returns early
 // once the estimate has converged, which lets a whole cycle be captured in a
 // HIP graph and replayed without host round trips; the host reads back one
 // small record per cycle, after the true residual has been recomputed.
 #include <array>
 #include <chrono>
+#include <cmath>
 #include <cstddef>
 #include <cstdio>
 #include <utility>
@@ -563,8 +567,74 @@ int tune_spmv(petgem_system* sys, hipStream_t s) {
     return PETGEM_OK;
 }
 
+namespace {
+
+// The right-hand side's singular-source flag, cleared when it was set.
+int check_flag(petgem_system* sys, int flag) {
+    if (!flag) return PETGEM_OK;
+    int zero = 0;
+    PG_HIP(hipMemcpy(sys->dflag, &zero, sizeof(int), hipMemcpyHostToDevice));
+    set_error("source within 1e-9 h of a quadrature point of an element with dsigma != 0");
+    return PETGEM_SOURCE_SINGULAR;
+}
+
+// The solve in one launch (resident.hip) from a zero guess; *done false: it
+// does not fit, or one of its waits ran out.
+int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_opts& o, double2* x_out, hipStream_t s,
+                   petgem_stats* st, bool* done) {
+    const int n = sys->n_dof;
+    Timer t_all;
+    *done = false;
+    ResWork& w = sys->gres;
+    if (!w.b) PG_TRY(dalloc(&w.b, (size_t)n));
+    if (!w.u) PG_TRY(dalloc(&w.u, (size_t)n));
+    if (!w.out) PG_TRY(dalloc(&w.out, 1));
+    if (!w.host) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.host), sizeof(GmHost)));
+    PG_TRY(launch_diag(sys, src.freq_hz, s));
+    Timer t_rhs;
+    PG_TRY(launch_rhs(sys, &src, 1, w.b, 0, 1, s));
+    const double trhs = t_rhs.ms();
+    bool fits = false;
+    PG_TRY(gm_run(sys, w, src.freq_hz, o.restart, o.max_iter, o.rtol, w.b, w.u, w.out, s, &fits));
+    if (!fits) return PETGEM_OK;
+    PG_HIP(hipMemcpyAsync(&w.host->out, w.out, sizeof(GmOut), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipMemcpyAsync(&w.host->abort, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+    PG_HIP(hipMemcpyAsync(&w.host->flag, sys->dflag, sizeof(int), hipMemcpyDeviceToHost, s));
+    hipLaunchKernelGGL(k_scale_in, dim3(ceil_div(n, 256)), dim3(256), 0, s, n, sys->dinv, w.u, x_out);   // x = D^{-1} u
+    PG_HIP(hipGetLastError());
+    PG_HIP(hipStreamSynchronize(s));
+    PG_TRY(check_flag(sys, w.host->flag));
+    if (w.host->abort) return PETGEM_OK;
+    *done = true;
+    const GmOut& r = w.host->out;
+    const bool bad_b = !std::isfinite(r.bnorm);
+    if (st) {
+        st->t_rhs_ms = trhs;
+        st->b_norm = r.bnorm;
+        st->x0_rel_residual = 1.0;
+        st->iters = r.iters;
+        st->ir_steps = r.cycles;
+        st->spmv_shape = 1;
+        st->rel_residual = bad_b || r.bnorm == 0.0 ? 0.0 : r.rnorm / r.bnorm;
+        st->status = r.status;
+        st->t_solve_ms = t_all.ms();
+    }
+    if (r.status == PETGEM_NOT_CONVERGED) set_error("GMRES reached max_iter before rtol");
+    if (r.status == PETGEM_NONFINITE)
+        set_error(bad_b ? "non-finite right-hand side" : "non-finite value in the GMRES recurrence");
+    return r.status;
+}
+
+}  // namespace
+
 int gmres_solve(petgem_system* sys, const petgem_source& src, const petgem_opts& o,
                 const double2* x0, double2* x_out, hipStream_t s, petgem_stats* st) {
+    // a guess, profiling and progress lines take the kernels of each phase
+    if (!x0 && !o.profile && !o.verbose) {
+        bool done = false;
+        const int rc = gmres_resident(sys, src, o, x_out, s, st, &done);
+        if (done || rc != PETGEM_OK) return rc;
+    }
     const int n = sys->n_dof;
     const int m = o.restart;
     Timer t_all;
@@ -630,12 +700,7 @@ int gmres_solve(petgem_system* sys, const petgem_source& src, const petgem_opts&
     PG_TRY(read_tail());
     int flag_h = 0;
     PG_HIP(hipMemcpy(&flag_h, sys->dflag, sizeof(int), hipMemcpyDeviceToHost));
-    if (flag_h) {
-        int zero = 0;
-        PG_HIP(hipMemcpy(sys->dflag, &zero, sizeof(int), hipMemcpyHostToDevice));
-        set_error("source within 1e-9 h of a quadrature point of an element with dsigma != 0");
-        return PETGEM_SOURCE_SINGULAR;
-    }
+    PG_TRY(check_flag(sys, flag_h));
     const double bnorm = tail->rnorm;
     if (st) {
         st->b_norm = bnorm;

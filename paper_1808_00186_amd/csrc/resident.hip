@@ -1,7 +1,6 @@
-// The inner complex64 COCG of the mixed-precision solve with the operator
-// resident in the register files: one launch runs the whole inner solve of
-// every (mesh, column) pair whose mesh fits, instead of two to five kernels
-// per iteration.
+// Krylov solves in one launch: the inner complex64 COCG of the mixed-precision
+// solve with the operator resident in the register files, instead of two to
+// five kernels per iteration, and the plain GMRES (at the end of the file).
 //
 // What it replaces and why. An iteration of the kernel-per-phase form streams
 // the operator (12 B a nonzero) and five vectors through the Infinity Cache
@@ -564,22 +563,526 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
     }
 }
 
+// ------------------------------------------------ the plain GMRES, resident
+// Right-Jacobi GMRES(m) in double precision (krylov.hip describes the method
+// and holds the kernel-per-phase form) with all its cycles in one launch, over
+// the same layout and exchange. A step of that form is seven launches, three
+// of them normally empty: 26 us on 3k unknowns, of which little is work.
+// The basis and the operator (A D^-1, complex128 in the layout's order) stay
+// in memory: a workgroup reads only its own rows of them, so they come
+// through its caches; v_j with its halo, w and the iterate are in LDS.
+//   step j: w = Ahat v_j; c_k = v_k^H w, |w|^2 (one exchange of 2 j + 3
+//   doubles); v_{j+1} = (w - sum c_k v_k) / beta with beta by Pythagoras,
+//   after a second pass where cancellation makes that unreliable; one thread
+//   of every workgroup runs the Givens recurrence while v_{j+1} travels.
+constexpr int kGmMax = 31;                    // longest restart: 2 m + 1 sums in 64
+constexpr int kGmVals = 64;
+constexpr int kGmArea = kGmVals * 32 + 32;    // words from one area to the next
+constexpr double kGmEta = 1e-2;               // second pass when beta^2 <= eta |w|^2
+
+struct GmArgs {
+    int G, n, rw, rwcap, hcap, hmax, m, max_iter;
+    double rtol;
+    const int32_t *rows, *wend, *halo, *nh;
+    const uint2* idx;
+    const double2 *A, *b;
+    double2 *u, *V;
+    u64 *words, *pex;
+    int* abort;
+    GmOut* out;
+};
+
+// Ahat = A D^-1 in the layout's order, one wave per (workgroup, wave).
+__global__ void __launch_bounds__(256)
+k_gm_vals(int n, int rw, int rwcap, double wmu, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
+          const int32_t* __restrict__ rows, const int32_t* __restrict__ wend, const double* __restrict__ K,
+          const double* __restrict__ Ms, const double2* __restrict__ dinv, double2* __restrict__ A) {
+    const int g = blockIdx.x / 2, wave = (blockIdx.x & 1) * 4 + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int R = min(n - g * rw, rw);
+    const size_t base = ((size_t)g * kResW + wave) * kResCh * 256 + lane;
+    int ch = 0;
+    for (int k = 0; k < kResK; ++k) {
+        const int end = wend[((size_t)g * kResW + wave) * kResK + k];
+        const int s = res_slice(wave, k) * 64 + lane;
+        const int row = s < R ? rows[(size_t)g * rwcap + s] : -1;
+        const int b = row >= 0 ? rp[row] : 0, l = row >= 0 ? rp[row + 1] - b : 0;
+        for (int q = 0; ch < end; ++ch, q += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                A[base + (size_t)ch * 256 + u * 64] =
+                    q + u < l ? cmul(make_double2(K[b + q + u], -wmu * Ms[b + q + u]), dinv[col[b + q + u]])
+                              : make_double2(0.0, 0.0);
+    }
+}
+
+__host__ __device__ constexpr size_t gm_words(int G) {
+    return (size_t)kGmArea * (G > 32 ? 2 * ((G + 31) / 32) : 1);
+}
+
+// RK rows to a thread (at most kResT RK rows to a workgroup); the passes over
+// the basis take kQ vectors at a time, 16 loads of a thread in flight.
+template <int RK>
+__global__ void __launch_bounds__(kResT)
+k_gm_solve(GmArgs a) {
+    constexpr int kQ = 16 / RK;
+    extern __shared__ double2 lds_d[];
+    __shared__ double wsum[kResW][kGmVals];
+    __shared__ double tot[kGmVals];
+    __shared__ double2 coef[kGmMax + 1], hsave[kGmMax + 1], col[kGmMax + 2], cs[kGmMax], gv[kGmMax + 1],
+        yv[kGmMax + 1];
+    __shared__ double sn[kGmMax];
+    __shared__ double scale_s, beta_s, tol_s, rnorm_s;
+    __shared__ int action, done, nonfinite, mdone, fail1, fail2;
+    const int g = xcd_block(blockIdx.x, gridDim.x);
+    const int G = a.G, m = a.m, rwcap = a.rwcap, R = min(a.n - g * a.rw, a.rw);
+    const int ng = (G + 31) / 32, gr = g >> 5, lanes1 = G <= 8 ? 8 : 32;
+    const int t = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
+    double2* const z = lds_d;                           // own rows, then the halo
+    double2* const yl = z + rwcap + a.hcap;
+    double2* const ul = yl + rwcap;
+    double2* const H = ul + rwcap;                      // [m][m + 1]
+    int* const hl = reinterpret_cast<int*>(H + (size_t)m * (m + 1));
+    const int nh = a.nh[g];
+    for (int h = t; h < nh; h += kResT) hl[h] = a.halo[(size_t)g * a.hmax + h];
+    if (t == 0) { fail1 = 0; fail2 = 0; nonfinite = 0; }
+    int end[RK], sb[RK];
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {   // (a workgroup of at most kResT RK rows has no more row slots)
+        end[k] = __builtin_amdgcn_readfirstlane(a.wend[((size_t)g * kResW + wave) * kResK + k]);
+        sb[k] = res_slice(wave, k) * 64;
+    }
+    const size_t ldv = (size_t)G * rwcap, mine = (size_t)g * rwcap;
+    const size_t wstride = gm_words(G), pstride = 2 * ldv;
+    unsigned ep = 0, xc = 0;
+    bool failed = false;
+
+    // own rows of z to the neighbours
+    auto publish = [&]() {
+#pragma unroll
+        for (int k = 0; k < RK; ++k) {
+            const int s = sb[k] + lane;
+            if (s < R && G > 1) {
+                u64* const p = a.pex + (xc % 3) * pstride + 2 * (mine + s);
+                u64* const q = a.pex + ((xc + 1) % 3) * pstride + 2 * (mine + s);
+                put(p, (u64)__double_as_longlong(z[s].x));
+                put(p + 1, (u64)__double_as_longlong(z[s].y));
+                put(q, kResEmpty);
+                put(q + 1, kResEmpty);
+            }
+        }
+        ++xc;
+    };
+    // yl = Ahat z; four chunks of the operator on their way ahead of their use,
+    // the first of them while the halo is awaited
+    const int nch = end[RK - 1];
+    // (until_done: nothing more once the Givens recurrence has said so)
+    auto multiply = [&](bool until_done) {
+        const size_t base = ((size_t)g * kResW + wave) * kResCh;
+        uint2 ib[4];
+        double2 ab[4][4];
+        auto fetch = [&](int c, int u) {
+            if (c >= nch) return;
+            ib[u] = a.idx[(base + c) * 64 + lane];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) ab[u][q] = a.A[(base + c) * 256 + q * 64 + lane];
+        };
+#pragma unroll
+        for (int u = 0; u < 4; ++u) fetch(u, u);
+        if (nh > 0) {
+            const u64* const px = a.pex + ((xc - 1) % 3) * pstride;
+            bool bad = false;
+            for (int h0 = t; h0 < nh; h0 += 2 * kResT) {
+                const int h1 = h0 + kResT;
+                const u64* const p0 = px + 2 * (size_t)hl[h0];
+                const u64* const p1 = h1 < nh ? px + 2 * (size_t)hl[h1] : nullptr;
+                const u64* ad[4] = {p0, p0 + 1, p1, p1 ? p1 + 1 : nullptr};
+                u64 v[4];
+                if (!wait_words<4>(ad, a.abort, v)) bad = true;
+                z[rwcap + h0] = make_double2(__longlong_as_double((long long)v[0]), __longlong_as_double((long long)v[1]));
+                if (p1)
+                    z[rwcap + h1] = make_double2(__longlong_as_double((long long)v[2]), __longlong_as_double((long long)v[3]));
+            }
+            if (bad) fail2 = 1;
+        }
+        __syncthreads();
+        failed = failed || fail2;
+        if (failed || (until_done && done)) return;
+        const char* const zb = reinterpret_cast<const char*>(lds_d);
+        double2 y = make_double2(0.0, 0.0);
+        int slot = 0, stop = end[0], so = sb[0];
+        for (int c0 = 0; c0 < nch; c0 += 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (c0 + u >= nch) continue;
+                const uint2 i = ib[u];
+                const unsigned o[4] = {i.x & 0xffffu, i.x >> 16, i.y & 0xffffu, i.y >> 16};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double2 x = *reinterpret_cast<const double2*>(zb + 2 * o[q]);
+                    y.x += ab[u][q].x * x.x - ab[u][q].y * x.y;
+                    y.y += ab[u][q].x * x.y + ab[u][q].y * x.x;
+                }
+                fetch(c0 + 4 + u, u);
+                if (c0 + u + 1 == stop) {
+                    yl[so + lane] = y;
+                    y = make_double2(0.0, 0.0);
+                    ++slot;
+#pragma unroll
+                    for (int k = 1; k < RK; ++k)
+                        if (slot == k) {
+                            stop = end[k];
+                            so = sb[k];
+                        }
+                }
+            }
+        }
+    };
+    // tot[0 .. nv - 1]: the waves' sums over all workgroups
+    auto exchange = [&](int nv) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // cleared words are out before new ones are
+        __syncthreads();
+        u64* const w2 = a.words + (size_t)(ep % 3) * wstride;
+        u64* const w1 = ng > 1 ? w2 + (size_t)(ng + gr) * kGmArea : w2;
+        if (t < nv) {
+            double v = wsum[0][t];
+#pragma unroll
+            for (int w = 1; w < kResW; ++w) v += wsum[w][t];
+            if (G == 1) tot[t] = v;
+            else put(w1 + t * lanes1 + (g & 31), (u64)__double_as_longlong(v));
+        }
+        if (lanes1 == 8) {   // up to eight workgroups: eight lanes to a value, all values at once
+            const u64* ad[1] = {t < nv * 8 && (t & 7) < G ? w1 + t : nullptr};
+            u64 x[1];
+            if (G > 1 && !wait_words<1>(ad, a.abort, x)) fail1 = 1;
+            const double v = sum8(__longlong_as_double((long long)x[0]));
+            if (G > 1 && t < nv * 8 && (t & 7) == 0) tot[t >> 3] = v;
+        } else if (ng == 1 || (g & 31) == 0) {
+            const int q = t & 31;
+            const u64* ad[4];
+            u64 x[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) ad[r] = 32 * gr + q < G && t + r * kResT < nv * 32 ? w1 + t + r * kResT : nullptr;
+            if (!wait_words<4>(ad, a.abort, x)) fail1 = 1;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double v = sum32(__longlong_as_double((long long)x[r]));
+                const int j = (t + r * kResT) >> 5;
+                if (j >= nv) continue;
+                if (ng == 1) {
+                    if (q == 0) tot[j] = v;
+                } else if (q < ng) {
+                    put(w2 + (size_t)q * kGmArea + j * 8 + gr, (u64)__double_as_longlong(v));
+                }
+            }
+        }
+        if (ng > 1) {
+            const u64* ad[1] = {t < nv * 8 && (t & 7) < ng ? w2 + (size_t)gr * kGmArea + t : nullptr};
+            u64 x[1];
+            if (!wait_words<1>(ad, a.abort, x)) fail1 = 1;
+            const double v = sum8(__longlong_as_double((long long)x[0]));
+            if (t < nv * 8 && (t & 7) == 0) tot[t >> 3] = v;
+        }
+        if (G > 1) {   // the copy of the step before is read by all: clear it for the step after next
+            u64* const c2 = a.words + (size_t)((ep + 2) % 3) * wstride;
+            if (t < kGmVals) put((ng > 1 ? c2 + (size_t)(ng + gr) * kGmArea : c2) + t * lanes1 + (g & 31), kResEmpty);
+            if (ng > 1 && (g & 31) == 0 && (t & 7) < ng)
+                put(c2 + (size_t)(t & 7) * kGmArea + (t >> 3) * 8 + gr, kResEmpty);
+        }
+        ++ep;
+        __syncthreads();
+        failed = failed || fail1;
+    };
+    auto wave_total = [&](double v) {
+        v = sum32(v);
+        return swap32_add(v, v);
+    };
+
+    // u = 0 or the given iterate; r = b - Ahat u, rnorm
+    auto residual = [&]() {
+#pragma unroll
+        for (int k = 0; k < RK; ++k) {
+            const int s = sb[k] + lane;
+            if (s < R) z[s] = ul[s];
+        }
+        publish();
+        multiply(false);
+        if (failed) return;
+        double nn = 0.0;
+#pragma unroll
+        for (int k = 0; k < RK; ++k) {
+            const int s = sb[k] + lane;
+            if (s < R) {
+                const double2 r = csub(a.b[a.rows[mine + s]], yl[s]);
+                yl[s] = r;
+                nn += cabs2(r);
+            }
+        }
+        nn = wave_total(nn);
+        if (lane == 0) wsum[wave][0] = nn;
+        exchange(1);
+    };
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+        const int s = sb[k] + lane;
+        if (s < R) ul[s] = make_double2(0.0, 0.0);
+    }
+    residual();
+    if (t == 0) {
+        tol_s = a.rtol * sqrt(tot[0]);
+        if (g == 0) a.out->bnorm = sqrt(tot[0]);
+    }
+    int iters = 0, cycles = 0, status = PETGEM_OK;
+    while (!failed) {
+        const double r2 = tot[0], rn = sqrt(r2);
+        if (t == 0) {
+            rnorm_s = rn;
+            nonfinite = nonfinite || !isfinite(r2);
+            done = 0;
+            mdone = 0;
+            gv[0] = make_double2(rn, 0.0);
+        }
+        __syncthreads();
+        if (nonfinite) { status = PETGEM_NONFINITE; break; }
+        if (rn <= tol_s || rn == 0.0) break;
+        if (iters >= a.max_iter) { status = PETGEM_NOT_CONVERGED; break; }
+        // v_0 = r / |r|
+#pragma unroll
+        for (int k = 0; k < RK; ++k) {
+            const int s = sb[k] + lane;
+            if (s < R) {
+                const double2 v = cscale(yl[s], 1.0 / rn);
+                z[s] = v;
+                a.V[mine + s] = v;
+            }
+        }
+        publish();
+        for (int j = 0; j < m; ++j) {
+            multiply(true);
+            if (failed || done) break;
+            for (int pass = 0; pass < 2; ++pass) {
+                double2 w[RK];
+                double nn = 0.0;
+#pragma unroll
+                for (int k = 0; k < RK; ++k) {
+                    const int s = sb[k] + lane;
+                    w[k] = s < R ? yl[s] : make_double2(0.0, 0.0);
+                    nn += cabs2(w[k]);
+                }
+                nn = wave_total(nn);
+                if (lane == 0) wsum[wave][2 * (j + 1)] = nn;
+                for (int k0 = 0; k0 <= j; k0 += kQ) {
+                    double2 acc[kQ], v[kQ][RK];
+#pragma unroll
+                    for (int q = 0; q < kQ; ++q)
+#pragma unroll
+                        for (int k = 0; k < RK; ++k) {
+                            const int s = sb[k] + lane;
+                            v[q][k] = s < R && k0 + q <= j ? a.V[(size_t)(k0 + q) * ldv + mine + s]
+                                                           : make_double2(0.0, 0.0);
+                        }
+#pragma unroll
+                    for (int q = 0; q < kQ; ++q) {
+                        acc[q] = make_double2(0.0, 0.0);
+#pragma unroll
+                        for (int k = 0; k < RK; ++k) acc[q] = cadd(acc[q], cmulc(v[q][k], w[k]));
+                    }
+#pragma unroll
+                    for (int q = 0; q < kQ; q += 4) {
+                        if (k0 + q > j) continue;
+                        const double b0 = swap16_add(swap32_add(acc[q].x, acc[q + 2].x),
+                                                     swap32_add(acc[q + 1].x, acc[q + 3].x));
+                        const double b1 = swap16_add(swap32_add(acc[q].y, acc[q + 2].y),
+                                                     swap32_add(acc[q + 1].y, acc[q + 3].y));
+                        const double e = sum8(swap8_add(b0, b1, (lane & 8) != 0));
+                        const int i = 2 * (k0 + q) + (lane >> 3);
+                        if ((lane & 7) == 0 && i < 2 * (j + 1)) wsum[wave][i] = e;
+                    }
+                }
+                exchange(2 * (j + 1) + 1);
+                if (failed) break;
+                if (wave == 0) {
+                    const bool has = lane <= j;
+                    const double2 c = has ? make_double2(tot[2 * lane], tot[2 * lane + 1]) : make_double2(0.0, 0.0);
+                    if (has) coef[lane] = c;
+                    const double hh = sum32(cabs2(c)), nrm2 = tot[2 * (j + 1)];   // j < 32: the lower half-wave
+                    if (has) {
+                        col[lane] = pass == 0 ? c : cadd(hsave[lane], c);
+                        if (pass == 0) hsave[lane] = c;
+                    }
+                    if (lane == 0) {
+                        const double b2 = nrm2 - hh;
+                        if (!isfinite(nrm2) || !isfinite(hh)) {
+                            nonfinite = 1;
+                            action = 0;
+                        } else if (pass == 0 && b2 <= kGmEta * nrm2) {
+                            action = 2;
+                            scale_s = 1.0;
+                        } else {
+                            const double be = b2 > 0.0 ? sqrt(b2) : 0.0;
+                            action = 1;
+                            beta_s = be;
+                            scale_s = be > 0.0 ? 1.0 / be : 0.0;
+                        }
+                    }
+                }
+                __syncthreads();
+                const int act = action;
+                if (act == 0) break;
+                const double sc = scale_s;
+                for (int k0 = 0; k0 <= j; k0 += kQ) {
+                    double2 v[kQ][RK];
+#pragma unroll
+                    for (int q = 0; q < kQ; ++q)
+#pragma unroll
+                        for (int k = 0; k < RK; ++k) {
+                            const int s = sb[k] + lane;
+                            v[q][k] = s < R && k0 + q <= j ? a.V[(size_t)(k0 + q) * ldv + mine + s]
+                                                           : make_double2(0.0, 0.0);
+                        }
+#pragma unroll
+                    for (int q = 0; q < kQ; ++q) {
+                        const double2 h = k0 + q <= j ? coef[k0 + q] : make_double2(0.0, 0.0);
+#pragma unroll
+                        for (int k = 0; k < RK; ++k) w[k] = csub(w[k], cmul(h, v[q][k]));
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < RK; ++k) {
+                    const int s = sb[k] + lane;
+                    if (s < R) {
+                        const double2 v = cscale(w[k], sc);
+                        if (act == 2) {
+                            yl[s] = v;
+                        } else {
+                            z[s] = v;
+                            a.V[(size_t)(j + 1) * ldv + mine + s] = v;
+                        }
+                    }
+                }
+                if (act == 1) break;
+                __syncthreads();   // coef is read before the second pass writes it
+            }
+            if (failed || nonfinite) break;
+            if (j + 1 < m) publish();
+            // the previous rotations on the new column, then the new one, by a
+            // thread whose wave has the least of the halo to read; the others
+            // go on, and see `done` when the halo has come in. s is real, so
+            // the chain from one rotation to the next is a multiply-add
+            if (t == kResT - kWave) {
+                const double be = beta_s;
+                double2* const Hj = H + (size_t)j * (m + 1);
+                double2 x = col[0];
+                for (int i0 = 0; i0 < j; i0 += 8) {
+                    double2 c[8], y[8], o[8];
+                    double r[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const int i = min(i0 + u, j - 1);
+                        c[u] = cs[i];
+                        r[u] = sn[i];
+                        y[u] = col[i + 1];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const double2 cy = cmul(c[u], y[u]);
+                        o[u] = cadd(cmulc(c[u], x), cscale(y[u], r[u]));
+                        if (i0 + u < j) x = csub(cy, cscale(x, r[u]));
+                    }
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+                        if (i0 + u < j) Hj[i0 + u] = o[u];
+                }
+                const double den = sqrt(cabs2(x) + be * be), iden = den > 0.0 ? 1.0 / den : 0.0;
+                const double2 c = den > 0.0 ? cscale(x, iden) : make_double2(1.0, 0.0);
+                const double s1 = den > 0.0 ? be * iden : 0.0;
+                cs[j] = c;
+                sn[j] = s1;
+                Hj[j] = make_double2(den, 0.0);
+                const double2 gj = gv[j], g1 = cscale(gj, -s1);
+                gv[j + 1] = g1;
+                gv[j] = cmulc(c, gj);
+                mdone = j + 1;
+                if (sqrt(cabs2(g1)) <= tol_s || be <= 1e-300) done = 1;
+            }
+        }
+        if (failed) break;
+        __syncthreads();
+        if (done && mdone < m) {
+            // v_{mdone} went out and nobody read it: an exchange separates it
+            // from the iterate that goes out next
+            exchange(1);
+            if (failed) break;
+        }
+        // back substitution on the first half-wave: lane i holds y_i
+        const int md = mdone;
+        if (wave == 0) {
+            double2 s = lane < md ? gv[lane] : make_double2(0.0, 0.0);
+            const double2 inv = lane < md ? cdiv(make_double2(1.0, 0.0), H[(size_t)lane * (m + 1) + lane])
+                                          : make_double2(0.0, 0.0);
+            for (int i = md - 1; i >= 0; --i) {
+                const double2 yi = cmul(s, inv);
+                const double2 y = make_double2(__shfl(yi.x, i), __shfl(yi.y, i));
+                if (lane == i) s = y;
+                else if (lane < i) s = csub(s, cmul(H[(size_t)i * (m + 1) + lane], y));
+            }
+            if (lane < md) yv[lane] = s;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < RK; ++k) {
+            const int s = sb[k] + lane;
+            if (s < R) {
+                double2 u = ul[s];
+                for (int q = 0; q < md; ++q) u = cadd(u, cmul(yv[q], a.V[(size_t)q * ldv + mine + s]));
+                ul[s] = u;
+            }
+        }
+        iters += md;
+        ++cycles;
+        residual();
+        if (!failed && md == 0 && !nonfinite) {   // no progress; the new residual is the last word on it
+            if (t == 0) rnorm_s = sqrt(tot[0]);
+            status = sqrt(tot[0]) <= tol_s ? PETGEM_OK : PETGEM_NOT_CONVERGED;
+            __syncthreads();
+            break;
+        }
+    }
+    if (failed) {
+        if (t == 0) __hip_atomic_store(a.abort, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < RK; ++k) {
+        const int s = sb[k] + lane;
+        if (s < R) a.u[a.rows[mine + s]] = ul[s];
+    }
+    if (g == 0 && t == 0) {
+        a.out->rnorm = rnorm_s;
+        a.out->iters = iters;
+        a.out->cycles = cycles;
+        a.out->status = status;
+    }
+}
+
 }  // namespace
 
 // ------------------------------------------------------------ host side
 void Resident::release() {
     dfree(rows); dfree(wend); dfree(halo); dfree(nh);
-    dfree(idx); dfree(K); dfree(M);
+    dfree(idx); dfree(K); dfree(M); dfree(A);
+    a_freq = -1.0;
     G = 0;
     state = 0;
     values = false;
 }
 
 void ResWork::release() {
-    dfree(doms); dfree(blk); dfree(words); dfree(pex); dfree(abort);
+    dfree(doms); dfree(blk); dfree(words); dfree(pex); dfree(abort); dfree(V); dfree(b); dfree(u); dfree(out);
+    if (host) (void)hipHostFree(host);
+    host = nullptr;
     if (abort_h) (void)hipHostFree(abort_h);
     abort_h = nullptr;
-    cap_doms = cap_blk = cap_words = cap_pex = 0;
+    cap_doms = cap_blk = cap_words = cap_pex = cap_v = 0;
     rounds.clear();
 }
 
@@ -633,8 +1136,6 @@ int res_build(petgem_system* sys, Resident& L, int rw, hipStream_t s) {
         if (got[0] > kResCh || got[1] > hmax) return PETGEM_OK;   // too many entries or outer neighbours
         L.hmax = hmax;
         L.hcap = (got[1] + 63) / 64 * 64;
-        PG_TRY(dalloc(&L.K, 4 * ent));
-        PG_TRY(dalloc(&L.M, 4 * ent));
         L.state = 1;
         return PETGEM_OK;
     };
@@ -678,6 +1179,9 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
         L[k] = &sys->res[which];
         PG_TRY(res_build(sys, *L[k], res_rows(sys->n_dof, which ? kResCoarse : kResFine, ncu), s));
         if (L[k]->state != 1) return PETGEM_OK;
+        const size_t ent = (size_t)L[k]->G * kResW * kResCh * 64;
+        if (!L[k]->K) PG_TRY(dalloc(&L[k]->K, 4 * ent));
+        if (!L[k]->M) PG_TRY(dalloc(&L[k]->M, 4 * ent));
         stale = stale || !L[k]->values;
     }
     // rounds of domains that are resident together, the largest first
@@ -781,6 +1285,83 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
         PG_HIP(hipGetLastError());
         for (Resident* l : L) l->values = true;
     }
+    *fits = true;
+    return PETGEM_OK;
+}
+
+// The whole plain GMRES of one source from a zero guess; *fits false: the mesh
+// or the restart does not fit. D^-1 (sys->dinv) is current and b is set.
+int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, const double2* b,
+           double2* u, GmOut* out, hipStream_t s, bool* fits) {
+    *fits = false;
+    if (restart > kGmMax) return PETGEM_OK;
+    int dev = 0, ncu = 0, coop = 0;
+    PG_HIP(hipGetDevice(&dev));
+    PG_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    PG_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
+    if (!coop) return PETGEM_OK;
+    const int n = sys->n_dof, which = ceil_div(n, kResFine) <= ncu ? 0 : 1;
+    Resident& L = sys->res[which];
+    PG_TRY(res_build(sys, L, res_rows(n, which ? kResCoarse : kResFine, ncu), s));
+    if (L.state != 1) return PETGEM_OK;
+    const size_t lds = (size_t)16 * (L.rwcap + L.hcap) + (size_t)32 * L.rwcap + (size_t)16 * restart * (restart + 1) +
+                       (size_t)4 * L.hcap;
+    if (lds + 9216 > 160 * 1024) return PETGEM_OK;
+    const size_t ent = (size_t)L.G * kResW * kResCh * 256, ldv = (size_t)L.G * L.rwcap;
+    if (!L.A) PG_TRY(dalloc(&L.A, ent));
+    if (L.a_freq != freq) {
+        hipLaunchKernelGGL(k_gm_vals, dim3(2 * L.G), dim3(256), 0, s, n, L.rw, L.rwcap, 2.0 * kPi * freq * kMu0,
+                           sys->row_ptr, sys->col, L.rows, L.wend, sys->K, sys->Ms, sys->dinv, L.A);
+        PG_HIP(hipGetLastError());
+        L.a_freq = freq;
+    }
+    auto grow = [&](auto& p, size_t& cap, size_t need) -> int {
+        if (cap >= need) return PETGEM_OK;
+        dfree(p);
+        cap = 0;
+        PG_TRY(dalloc(&p, need));
+        cap = need;
+        return PETGEM_OK;
+    };
+    W.n_words = 3 * gm_words(L.G);
+    W.n_pex = 6 * ldv;
+    PG_TRY(grow(W.words, W.cap_words, W.n_words));
+    PG_TRY(grow(W.pex, W.cap_pex, W.n_pex));
+    PG_TRY(grow(W.V, W.cap_v, (size_t)(restart + 1) * ldv));
+    if (!W.abort) PG_TRY(dalloc(&W.abort, 1));
+    const size_t m = std::max(W.n_words, W.n_pex);
+    hipLaunchKernelGGL(k_res_clear, dim3(ceil_div(m, 256)), dim3(256), 0, s, W.n_words, W.words, W.n_pex, W.pex,
+                       W.abort);
+    PG_HIP(hipGetLastError());
+    GmArgs a{};
+    a.G = L.G;
+    a.n = n;
+    a.rw = L.rw;
+    a.rwcap = L.rwcap;
+    a.hcap = L.hcap;
+    a.hmax = L.hmax;
+    a.m = restart;
+    a.max_iter = max_iter;
+    a.rtol = rtol;
+    a.rows = L.rows;
+    a.wend = L.wend;
+    a.halo = L.halo;
+    a.nh = L.nh;
+    a.idx = reinterpret_cast<const uint2*>(L.idx);
+    a.A = L.A;
+    a.b = b;
+    a.u = u;
+    a.V = W.V;
+    a.words = W.words;
+    a.pex = W.pex;
+    a.abort = W.abort;
+    a.out = out;
+    void* args[1] = {&a};
+    const void* fn = L.rw <= kResT ? reinterpret_cast<const void*>(k_gm_solve<1>)
+                     : L.rw <= 2 * kResT ? reinterpret_cast<const void*>(k_gm_solve<2>)
+                                         : reinterpret_cast<const void*>(k_gm_solve<4>);
+    PG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    PG_HIP(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
     *fits = true;
     return PETGEM_OK;
 }

@@ -115,3 +115,38 @@ def test_resident_iteration_limit(pg):
     assert rc == pg.NOT_CONVERGED and st[0]["status"] == pg.NOT_CONVERGED and st[0]["iters"] <= 16
     sol, st, rc = S.solve(m.sources, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL))
     assert rc == pg.OK and max(_residuals(S, m.sources, sol.x())) <= 1.01 * RTOL
+
+
+# 2 and 3: one workgroup; 8: 6 workgroups (eight lanes to a sum); 12: 22;
+# 21: two levels of sums; 27: two rows to a thread
+@pytest.mark.parametrize("n,restart", [(2, 30), (3, 5), (8, 30), (8, 31), (8, 1), (12, 13), (21, 30), (27, 20)])
+def test_resident_gmres_takes_the_steps_of_the_kernels(pg, n, restart):
+    """Same cycles, same steps: the two forms differ in the order of their
+    double-precision sums only, which at 1e-9 moves a cycle's last step by at
+    most one. `profile` keeps the kernel-per-phase form."""
+    m = _model(n, box=2000.0)
+    S = pg.System.from_model(m)
+    kw = dict(rtol=1e-9, restart=restart, max_iter=6000)
+    sol, st, rc = S.solve(m.sources, pg.default_opts(**kw), allow_not_converged=True)
+    _, stk, rck = S.solve(m.sources, pg.default_opts(profile=1, **kw), allow_not_converged=True)
+    print(f"[case] gmres n={n} restart={restart} iters {st[0]['iters']} / {stk[0]['iters']}", flush=True)
+    assert rc == rck and st[0]["spmv_shape"] == 1
+    assert abs(st[0]["iters"] - stk[0]["iters"]) <= max(1, stk[0]["iters"] // 50)
+    assert abs(st[0]["b_norm"] - stk[0]["b_norm"]) <= 1e-13 * stk[0]["b_norm"]
+    res = _residuals(S, m.sources, sol.x())[0]
+    if rc == pg.OK:
+        assert res <= 1.01e-9
+    assert abs(res - st[0]["rel_residual"]) <= 1e-12
+
+
+def test_resident_gmres_several_sources_and_frequencies(pg):
+    m = _model(9)
+    S = pg.System.from_model(m)
+    srcs = [synth.Dipole((40.0 * k, 0.0, 60.0), f) for k, f in enumerate((1.0, 0.4, 1.0))]
+    sol, st, rc = S.solve(srcs, pg.default_opts(rtol=1e-9))
+    assert rc == pg.OK and max(_residuals(S, srcs, sol.x())) <= 1.01e-9
+    # after new conductivities the operator is formed anew
+    import torch
+    S.reassemble(torch.tensor(m.sigma * 1.7, device="cuda"), m.sigma_bg)
+    sol, st, rc = S.solve(srcs, pg.default_opts(rtol=1e-9))
+    assert rc == pg.OK and max(_residuals(S, srcs, sol.x())) <= 1.01e-9
