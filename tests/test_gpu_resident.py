@@ -150,3 +150,42 @@ def test_resident_gmres_several_sources_and_frequencies(pg):
     S.reassemble(torch.tensor(m.sigma * 1.7, device="cuda"), m.sigma_bg)
     sol, st, rc = S.solve(srcs, pg.default_opts(rtol=1e-9))
     assert rc == pg.OK and max(_residuals(S, srcs, sol.x())) <= 1.01e-9
+
+
+def _small(rng):
+    """One 8^3 model with a resistive plate: random plate, source, frequency and mesh jitter."""
+    jit = int(rng.integers(1 << 30))
+    box = ((-200.0, 200.0), (-200.0, 200.0), (-250.0 * rng.uniform(0.6, 1.6), 0.0))
+    src = (float(rng.uniform(-40, 40)), 0.0, float(rng.uniform(150.0, 400.0)))
+    xyz, tets = synth.kuhn_mesh(8, -1000.0, 1000.0, jit)
+    c = xyz[tets].mean(axis=1)
+    sig = np.ones(len(c))
+    inside = np.ones(len(c), bool)
+    for k in range(3):
+        inside &= (c[:, k] >= box[k][0]) & (c[:, k] <= box[k][1])
+    sig[inside] = float(np.exp(rng.uniform(np.log(0.005), np.log(0.05))))
+    return xyz, tets, sig, src
+
+
+# Model 17 of this sequence starts its third refinement step with |r^T z| a
+# millionth of |r|^2 on the coarse split: its |r| wandered for 19,000
+# iterations. No limit on the iterations but the one the rule implies: three
+# ordinary steps (under 1,000 in all for these models), at most four stopped
+# ones of a few hundred more each.
+def test_resident_column_that_wanders_restarts(pg):
+    print("[case] wandering column", flush=True)
+    rng = np.random.default_rng([7, 11])
+    models, srcs = [], []
+    for _ in range(96):
+        f = float(rng.uniform(0.1, 2.0))
+        xyz, tets, sig, p = _small(rng)
+        srcs.append(synth.Dipole(p, f))
+        models.append(synth.Model("small", xyz, tets, sig, 1.0, [srcs[-1]], np.zeros((1, 3)), 8, (-1000.0, 1000.0)))
+    sys = [pg.System.from_model(m) for m in models]
+    o = pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=1e-12)
+    sols, st, rc = pg.solve_many(sys, srcs, o)
+    assert rc == pg.OK
+    print(f"  iters {max(s['iters'] for s in st)}", flush=True)
+    assert max(s["iters"] for s in st) < 4000
+    for k in (0, 17, 95):
+        assert _residuals(sys[k], [srcs[k]], sols[k].x())[0] <= 1.01e-12
