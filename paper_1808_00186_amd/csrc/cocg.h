@@ -105,10 +105,10 @@ __device__ __forceinline__ bool plateau_now(const ColState& S, double r2) {
 // of 96 3,032-unknown models, |r^T z| a millionth of |r|^2 at the start of its
 // third step, halved |r| last at iteration 52 and then stayed between 0.1 and
 // 9 for 19,000 iterations, with a new best every few hundred; with this rule
-// it takes 1,182 in all steps together, the slowest of its neighbours 900 to
-// 1,200. Over 3,800 such models no other column took more iterations. At most
-// kWanderStops stops a column, so that one which needs the longer run still
-// gets it.
+// it takes 1,182 in all steps together. The slowest of 96 models takes 811 to
+// 1,212 over 41 such batches (860 to 1,232 kernel by kernel without the rule).
+// At most kWanderStops stops a column, so that one which needs the longer run
+// still gets it.
 constexpr int kWanderIters = 400, kWanderStops = 4;
 constexpr double kWanderRn2 = 0.1;
 __device__ __forceinline__ bool wander_now(ColState& S, double r2) {

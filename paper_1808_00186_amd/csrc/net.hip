@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "device.h"
@@ -33,6 +34,7 @@ namespace petgem {
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 using bf16 = uint16_t;
 
@@ -205,19 +207,271 @@ k_conv(const bf16* __restrict__ in, const bf16* __restrict__ wt, const float* __
     }
 }
 
+// Elementwise kernels move 4 channels (8 bytes of bf16, 16 of f32) per
+// thread; every channel count and offset is a multiple of 4.
+__device__ __forceinline__ float4 bf4(uint2 w) {
+    return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                       __uint_as_float(w.y & 0xffff0000u));
+}
+__device__ __forceinline__ float4 ld_bf4(const bf16* p) { return bf4(*reinterpret_cast<const uint2*>(p)); }
+__device__ __forceinline__ void st_bf4(bf16* p, float4 v) {
+    *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16),
+                                              (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16));
+}
+
+// parent (coarse) voxel of fine voxel vf on a grid of side D
+// (voxel and element counts stay below 2^31 for batch_max <= 256, so the
+// index arithmetic of these kernels is 32-bit)
+__device__ __forceinline__ int parent_of(int vf, int D) {
+    const int Dc = D / 2, V = D * D * D;
+    const int b = vf / V, r = vf % V;
+    const int z = r / (D * D), y = (r / D) % D, x = r % D;
+    return b * Dc * Dc * Dc + ((z / 2) * Dc + y / 2) * Dc + x / 2;
+}
+// q-th of the 8 children of coarse voxel vc (side Dc) on the fine grid
+__device__ __forceinline__ int child_of(int vc, int Dc, int q) {
+    const int D = 2 * Dc, Vc = Dc * Dc * Dc;
+    const int b = vc / Vc, r = vc % Vc;
+    const int z = r / (Dc * Dc), y = (r / Dc) % Dc, x = r % Dc;
+    return b * D * D * D + ((2 * z + (q >> 2)) * D + 2 * y + ((q >> 1) & 1)) * D + 2 * x + (q & 1);
+}
+
+// ---------------------------------------------------------------- conv, sides 16 and 32
+// The same sums for TZ output planes of a column: the block walks the input
+// planes upwards, and a staged plane feeds the outputs above, at and below it,
+// so each plane is staged once (TZ + 2 planes for TZ outputs, not 3 TZ) and
+// each input operand read from LDS is used with the weights of all three z
+// offsets: MT + 3 NTB reads for 3 MT NTB MFMAs instead of 3 (MT + NTB). All
+// 27 taps of the block's output channels stay in LDS. An output still adds its
+// taps in the order of k_conv: results are the same bits. The operands are
+// the other way round (weights as rows), so that a lane holds 4 channels of one voxel
+// and stores them at once. With C1 > 0 the input is the concatenation of the
+// nearest x2 upsampling of `up` (C1 channels) and `in` (CIN - C1): it is
+// gathered while staging and never written.
+// Bound: latency of the staging, which one plane ahead and two blocks a compute
+// unit hide in part. us for 16 samples, with k_conv and its separate concatenation, copy
+// and ReLU passes, and now: 48 -> 16 61 + 25, 31; 96 -> 32 37 + 11, 25; 16 -> 16 18 + 8
+// (copy), 15; 16 -> 16 with the ReLU backward 18 + 12, 16. Matrix cores 9 us, LDS 10 us
+// and memory 8 us of the 48 -> 16.
+// EPI: 0 bias, ReLU, bf16; 1 bias if any, f32; 2 the ReLU backward of the
+// layer below, bf16 (act: its stored activation).
+template <int CIN, int COUT, int C1, int D, int TY, int NTB, int NW, int EPI>
+__global__ void __launch_bounds__(64 * NW)
+k_conv_z(const bf16* __restrict__ in, const bf16* __restrict__ up, const bf16* __restrict__ wt,
+         const float* __restrict__ bias, const bf16* __restrict__ act, void* __restrict__ out, int TZ) {
+    constexpr int NT = 64 * NW, MT = TY * D / (16 * NW), HC = CIN + 8, WK = 9 * CIN + 8, K = 27 * CIN;
+    constexpr int Vs = D * D * D, C2 = CIN - C1, HQ = (TY + 2) * (D + 2) * (CIN / 8), NH = (HQ + NT - 1) / NT;
+    constexpr int KP = 9 * CIN, NK32 = KP / 32, REM = KP % 32 != 0;
+    static_assert(TY * D % (16 * NW) == 0 && 16 * NW % D == 0 && D % TY == 0 && COUT % (16 * NTB) == 0 &&
+                  CIN % 16 == 0 && C1 % 8 == 0, "tile shape");
+    extern __shared__ __align__(16) bf16 lds_h[];
+    bf16* const halo = lds_h;
+    bf16* const wl = lds_h + (TY + 2) * (D + 2) * HC;
+    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
+    const int lb = xcd_block(blockIdx.x, gridDim.x);
+    const int zc = D / TZ, z0 = lb / (D / TY) % zc * TZ, y0 = lb % (D / TY) * TY, b = lb / (D / TY * zc);
+    const int co0 = blockIdx.y * 16 * NTB;
+    // A thread's 16-byte parts of a plane: place in the plane, whether it is
+    // in the grid and which tensor it comes from. Loads are unconditional
+    // (clamped), a part outside is zeroed on its way to LDS.
+    uint4 hreg[NH];
+    int part[NH];
+    unsigned inside = 0, coarse = 0;
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+        const int e = threadIdx.x + NT * j;
+        const int q = e % (CIN / 8), vx = e / (CIN / 8);
+        const int xx = vx % (D + 2) - 1, yy = y0 - 1 + vx / (D + 2);
+        const bool ok = e < HQ && yy >= 0 && yy < D && xx >= 0 && xx < D, cs = C1 > 0 && 8 * q < C1;
+        part[j] = !ok ? 0 : cs ? ((yy / 2) * (D / 2) + xx / 2) * C1 + 8 * q : (yy * D + xx) * C2 + 8 * q - C1;
+        inside |= (unsigned)ok << j;
+        coarse |= (unsigned)cs << j;
+    }
+    auto fetch = [&](int zz) {
+        const int zi = min(max(zz, 0), D - 1);
+        const bf16* pi = in + ((size_t)b * Vs + (size_t)zi * D * D) * C2;
+        const bf16* pu = C1 > 0 ? up + ((size_t)b * (Vs / 8) + (size_t)(zi / 2) * (D * D / 4)) * C1 : pi;
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+            hreg[j] = *reinterpret_cast<const uint4*>((C1 > 0 && (coarse >> j & 1) ? pu : pi) + part[j]);
+    };
+    auto stage = [&](int zz) {
+        const unsigned keep = zz >= 0 && zz < D ? inside : 0u;
+#pragma unroll
+        for (int j = 0; j < NH; ++j) {
+            const int e = threadIdx.x + NT * j;
+            const unsigned k = 0u - (keep >> j & 1);
+            if (e < HQ)
+                *reinterpret_cast<uint4*>(halo + (e / (CIN / 8)) * HC + 8 * (e % (CIN / 8))) =
+                    make_uint4(hreg[j].x & k, hreg[j].y & k, hreg[j].z & k, hreg[j].w & k);
+        }
+    };
+    fetch(z0 - 1);
+    constexpr int WQ = 16 * NTB * K / 8, WB = 8;   // the weights, WB loads in flight
+    for (int e0 = threadIdx.x; e0 < WQ; e0 += WB * NT) {
+        u32x4 w[WB];
+#pragma unroll
+        for (int u = 0; u < WB; ++u) {
+            const int e = min(e0 + u * NT, WQ - 1);
+            w[u] = *reinterpret_cast<const u32x4*>(wt + (size_t)(co0 + e / (K / 8)) * K + 8 * (e % (K / 8)));
+        }
+        // all loads first: the compiler would wait for each in turn
+        asm volatile("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]), "+v"(w[4]), "+v"(w[5]), "+v"(w[6]),
+                          "+v"(w[7]));
+#pragma unroll
+        for (int u = 0; u < WB; ++u) {
+            const int e = min(e0 + u * NT, WQ - 1), k = 8 * (e % (K / 8));
+            *reinterpret_cast<u32x4*>(wl + (k / KP * 16 * NTB + e / (K / 8)) * WK + k % KP) = w[u];
+        }
+    }
+    stage(z0 - 1);
+    f32x4 acc[3][MT][NTB];   // of the outputs below (its last z offset), at and above the staged plane
+#pragma unroll
+    for (int o = 0; o < 3; ++o)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < NTB; ++t) acc[o][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // LDS offset of this lane's voxel of its first M tile (tile wave + NW i:
+    // the others are whole rows further)
+    const int a0 = ((wave * 16 + m) / D * (D + 2) + (wave * 16 + m) % D) * HC;
+    constexpr int AST = 16 * NW / D * (D + 2) * HC;
+    auto shift = [](int idx) {   // of reduction index idx: the tap's (y, x) and the channel
+        const int tap = idx / CIN, ch = idx % CIN;
+        return (tap / 3 * (D + 2) + tap % 3) * HC + ch;
+    };
+    // where a chunk of 32 is within one tap its shift is a constant, else the
+    // lane's own
+    constexpr bool ONE = CIN % 32 == 0;
+    int off[ONE ? 1 : NK32];
+    if (ONE) off[0] = a0 + 8 * kq;
+    else {
+#pragma unroll
+        for (int kk = 0; kk < NK32; ++kk) off[ONE ? 0 : kk] = a0 + shift(32 * kk + 8 * kq);
+    }
+    const int off_rem = a0 + shift(32 * NK32 + 4 * kq);
+    // one staged plane for the z offsets LO .. HI (2: the output below, 0: above)
+    auto plane = [&](auto lo, auto hi) {
+        constexpr int LO = decltype(lo)::value, HI = decltype(hi)::value;
+#pragma unroll
+        for (int kk = 0; kk < NK32; ++kk) {
+            const int sh = ONE ? off[0] + shift(32 * kk) : off[ONE ? 0 : kk];
+            bf16x8 a[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = lds8(halo + sh + i * AST);
+#pragma unroll
+            for (int pz = LO; pz <= HI; ++pz)
+#pragma unroll
+                for (int t = 0; t < NTB; ++t) {
+                    const bf16x8 w = lds8(wl + ((pz * NTB + t) * 16 + m) * WK + 32 * kk + 8 * kq);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+                        acc[pz][i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a[i], acc[pz][i][t], 0, 0, 0);
+                }
+        }
+        if constexpr (REM) {
+            // An accumulator of the 32-wide product taken by the 16-wide one in
+            // the next instruction is read too early (the compiler leaves no
+            // wait between the two sizes; few accumulators a wave: wrong sums):
+            // 16 wait states, as many as the longer of them takes.
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_nop 7\n\ts_nop 7");
+            __builtin_amdgcn_sched_barrier(0);
+            bf16x4 a[MT];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const bf16x4*>(halo + off_rem + i * AST);
+#pragma unroll
+            for (int pz = LO; pz <= HI; ++pz)
+#pragma unroll
+                for (int t = 0; t < NTB; ++t) {
+                    const bf16x4 w = *reinterpret_cast<const bf16x4*>(wl + ((pz * NTB + t) * 16 + m) * WK + 32 * NK32 + 4 * kq);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+                        acc[pz][i][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w, a[i], acc[pz][i][t], 0, 0, 0);
+                }
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    float4 bb[NTB];
+#pragma unroll
+    for (int t = 0; t < NTB; ++t)
+        bb[t] = EPI != 2 && bias ? *reinterpret_cast<const float4*>(bias + co0 + t * 16 + 4 * kq)
+                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+    __syncthreads();
+    for (int zp = z0 - 1; zp <= z0 + TZ; ++zp) {
+        // this lane's place in the plane below, which ends with this one
+        const size_t v0 = ((size_t)b * Vs + ((size_t)(zp - 1) * D + y0) * D + wave * 16 + m) * COUT + co0 + 4 * kq;
+        uint2 av[EPI == 2 ? MT : 1][EPI == 2 ? NTB : 1];
+        if (EPI == 2 && zp > z0) {
+#pragma unroll
+            for (int t = 0; t < NTB; ++t)
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+                    av[EPI == 2 ? i : 0][EPI == 2 ? t : 0] =
+                        *reinterpret_cast<const uint2*>(act + v0 + 16 * NW * i * COUT + 16 * t);
+        }
+        if (zp < z0 + TZ) fetch(zp + 1);
+        // outputs zp - 1, zp, zp + 1 that are this block's
+        if (zp == z0 - 1) plane(I0{}, I0{});
+        else if (zp == z0 + TZ) plane(I2{}, I2{});
+        else if (TZ == 1) plane(I1{}, I1{});
+        else if (zp == z0) plane(I0{}, I1{});
+        else if (zp == z0 + TZ - 1) plane(I1{}, I2{});
+        else plane(I0{}, I2{});
+        __syncthreads();
+        if (zp < z0 + TZ) stage(zp + 1);
+        if (zp > z0) {   // lane: channels 4 kq .. 4 kq + 3 of voxel m of every (M tile, output tile)
+#pragma unroll
+            for (int t = 0; t < NTB; ++t) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    const size_t o = v0 + 16 * NW * i * COUT + 16 * t;
+                    f32x4 v = acc[2][i][t];
+                    if (EPI != 2) v = f32x4{v[0] + bb[t].x, v[1] + bb[t].y, v[2] + bb[t].z, v[3] + bb[t].w};
+                    if (EPI == 0) v = f32x4{fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
+                    if (EPI == 2) {
+                        const float4 a = bf4(av[EPI == 2 ? i : 0][EPI == 2 ? t : 0]);
+                        v = f32x4{a.x > 0.f ? v[0] : 0.f, a.y > 0.f ? v[1] : 0.f, a.z > 0.f ? v[2] : 0.f,
+                                  a.w > 0.f ? v[3] : 0.f};
+                    }
+                    if (EPI == 1) *reinterpret_cast<float4*>(reinterpret_cast<float*>(out) + o) = make_float4(v[0], v[1], v[2], v[3]);
+                    else st_bf4(reinterpret_cast<bf16*>(out) + o, make_float4(v[0], v[1], v[2], v[3]));
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int t = 0; t < NTB; ++t) {
+                acc[2][i][t] = acc[1][i][t];
+                acc[1][i][t] = acc[0][i][t];
+                acc[0][i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        __syncthreads();
+    }
+}
+
 // Voxel-quad interleaved copy of an activation: out[((v/4) C + c) 4 + v%4] =
 // in[v][c]. A lane of the weight pass then reads 4 consecutive voxels of one
 // channel as 8 contiguous bytes, and the 16 channels of a wave's fragment
-// are adjacent. One thread moves 4 voxels x 4 channels.
-template <int C>
+// are adjacent. One thread moves 4 voxels x 4 channels. With C1 > 0 `in` holds
+// channels C1 .. C - 1, and the first C1 are those of the parent voxel of the
+// coarse tensor `up` (D: fine side).
+template <int C, int C1, int D>
 __global__ void __launch_bounds__(256)
-k_to_quads(const bf16* __restrict__ in, int nvox, bf16* __restrict__ out) {
+k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, int nvox, bf16* __restrict__ out) {
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= nvox / 4 * (C / 4)) return;
     const int q = e / (C / 4), c = 4 * (e % (C / 4));
     uint2 w[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = *reinterpret_cast<const uint2*>(in + (size_t)(4 * q + j) * C + c);
+    for (int j = 0; j < 4; ++j) {
+        const bf16* p = in + (size_t)(4 * q + j) * (C - C1) + c - C1;
+        if (C1 > 0 && c < C1) p = up + (size_t)parent_of(4 * q + j, D) * C1 + c;
+        w[j] = *reinterpret_cast<const uint2*>(p);
+    }
     // channel c + i of voxel 4q + j is half (i & 1) of word (i >> 1) of w[j]
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -487,34 +741,6 @@ k_sum_splits(const float* __restrict__ partial, int nsplit, int n, float* __rest
     if (q == 0 && i < n) out[i] = red[0][e];
 }
 
-// Elementwise kernels move 4 channels (8 bytes of bf16, 16 of f32) per
-// thread; every channel count and offset is a multiple of 4.
-__device__ __forceinline__ float4 ld_bf4(const bf16* p) {
-    const uint2 w = *reinterpret_cast<const uint2*>(p);
-    return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
-                       __uint_as_float(w.y & 0xffff0000u));
-}
-__device__ __forceinline__ void st_bf4(bf16* p, float4 v) {
-    *reinterpret_cast<uint2*>(p) = make_uint2((uint32_t)f2bf(v.x) | ((uint32_t)f2bf(v.y) << 16),
-                                              (uint32_t)f2bf(v.z) | ((uint32_t)f2bf(v.w) << 16));
-}
-// parent (coarse) voxel of fine voxel vf on a grid of side D
-// (voxel and element counts stay below 2^31 for batch_max <= 256, so the
-// index arithmetic of these kernels is 32-bit)
-__device__ __forceinline__ int parent_of(int vf, int D) {
-    const int Dc = D / 2, V = D * D * D;
-    const int b = vf / V, r = vf % V;
-    const int z = r / (D * D), y = (r / D) % D, x = r % D;
-    return b * Dc * Dc * Dc + ((z / 2) * Dc + y / 2) * Dc + x / 2;
-}
-// q-th of the 8 children of coarse voxel vc (side Dc) on the fine grid
-__device__ __forceinline__ int child_of(int vc, int Dc, int q) {
-    const int D = 2 * Dc, Vc = Dc * Dc * Dc;
-    const int b = vc / Vc, r = vc % Vc;
-    const int z = r / (Dc * Dc), y = (r / Dc) % Dc, x = r % Dc;
-    return b * D * D * D + ((2 * z + (q >> 2)) * D + 2 * y + ((q >> 1) & 1)) * D + 2 * x + (q & 1);
-}
-
 // 2x2x2 average pooling (fine side D), C channels
 __global__ void k_pool(const bf16* __restrict__ in, int B, int D, int C, bf16* __restrict__ out) {
     const int e = blockIdx.x * 256 + threadIdx.x;
@@ -527,19 +753,6 @@ __global__ void k_pool(const bf16* __restrict__ in, int B, int D, int C, bf16* _
         s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
     st_bf4(out + vc * C + c, make_float4(0.125f * s.x, 0.125f * s.y, 0.125f * s.z, 0.125f * s.w));
-}
-
-// concatenation [nearest x2 upsampling of the coarse tensor (C1 channels) |
-// skip tensor (C2 channels)] on the fine grid of side D
-__global__ void k_up_concat(const bf16* __restrict__ coarse, int C1, const bf16* __restrict__ skip, int C2, int B,
-                            int D, bf16* __restrict__ out) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int W4 = (C1 + C2) / 4;
-    if (e >= B * D * D * D * W4) return;
-    const int c = 4 * (e % W4), vf = e / W4;
-    const uint2 w = c < C1 ? *reinterpret_cast<const uint2*>(coarse + parent_of(vf, D) * C1 + c)
-                           : *reinterpret_cast<const uint2*>(skip + vf * C2 + (c - C1));
-    *reinterpret_cast<uint2*>(out + vf * (C1 + C2) + c) = w;
 }
 
 // ReLU backward of the coarse half of an upsampling concatenation:
@@ -762,7 +975,7 @@ struct petgem_net {
     int step = 0;
     // activations (bf16) and gradients (f32) for batch_max samples
     petgem::bf16 *X0 = nullptr, *A1 = nullptr, *P1 = nullptr, *A2 = nullptr, *P2 = nullptr, *A3 = nullptr,
-                 *A4 = nullptr, *Q2 = nullptr, *A5 = nullptr, *Q1 = nullptr, *A6 = nullptr, *dzb = nullptr;
+                 *A4 = nullptr, *A5 = nullptr, *A6 = nullptr, *dzb = nullptr;
     float* Y = nullptr;
     float *g0 = nullptr, *g1 = nullptr, *g2 = nullptr;   // f32 gradient scratch
     float* wpart = nullptr;                              // backward-weight partials
@@ -806,38 +1019,59 @@ size_t wpart_floats(int cin, int cout, long nvox, int D) {
 }
 
 template <int CIN, int COUT, int D, int TY, int NTB>
-void conv_t(bool relu, bool outf32, const bf16* in, const bf16* wt, const float* bias, void* out, int nvox,
-            hipStream_t s) {
+void conv_t(bool relu, const bf16* in, const bf16* wt, const float* bias, void* out, int nvox, hipStream_t s) {
     const dim3 grid((unsigned)(nvox / (TY * D)), COUT / (16 * NTB));
-    if (outf32) hipLaunchKernelGGL((k_conv<CIN, COUT, D, TY, NTB, false, true>), grid, dim3(256), 0, s, in, wt, bias, out);
-    else if (relu) hipLaunchKernelGGL((k_conv<CIN, COUT, D, TY, NTB, true, false>), grid, dim3(256), 0, s, in, wt, bias, out);
-    else hipLaunchKernelGGL((k_conv<CIN, COUT, D, TY, NTB, false, false>), grid, dim3(256), 0, s, in, wt, bias, out);
+    if (relu) hipLaunchKernelGGL((k_conv<CIN, COUT, D, TY, NTB, true, false>), grid, dim3(256), 0, s, in, wt, bias, out);
+    else hipLaunchKernelGGL((k_conv<CIN, COUT, D, TY, NTB, false, true>), grid, dim3(256), 0, s, in, wt, bias, out);
 }
 
-// forward/backward-data convolution dispatch on the (CIN, COUT, side) triples
-// of the network; nvox = B side^3
-int conv(int cin, int cout, bool relu, bool outf32, const bf16* in, const bf16* wt, const float* bias, void* out,
-         int nvox, int D, hipStream_t s) {
-#define PG_CV(A, B, SIDE, TY, NTB)                                                     \
-    if (cin == A && cout == B && D == SIDE) {                                          \
-        conv_t<A, B, SIDE, TY, NTB>(relu, outf32, in, wt, bias, out, nvox, s);         \
-        return PETGEM_OK;                                                              \
+// forward (bf16 with bias and ReLU) or backward-data (f32) convolution at
+// side 8; nvox = B 512
+int conv8(int cin, int cout, bool relu, const bf16* in, const bf16* wt, const float* bias, void* out, int nvox,
+          hipStream_t s) {
+#define PG_CV(A, B)                                                  \
+    if (cin == A && cout == B) {                                     \
+        conv_t<A, B, 8, 8, 1>(relu, in, wt, bias, out, nvox, s);     \
+        return PETGEM_OK;                                            \
     }
-    PG_CV(16, 16, 32, 8, 1) PG_CV(48, 16, 32, 8, 1) PG_CV(16, 48, 32, 8, 3)
-    PG_CV(16, 32, 16, 8, 2) PG_CV(96, 32, 16, 8, 1) PG_CV(32, 96, 16, 8, 3) PG_CV(32, 16, 16, 8, 1)
-    PG_CV(32, 64, 8, 8, 1) PG_CV(64, 64, 8, 8, 1) PG_CV(64, 32, 8, 8, 1)
+    PG_CV(32, 64) PG_CV(64, 64) PG_CV(64, 32)
 #undef PG_CV
     set_error("unsupported convolution shape");
     return PETGEM_INVALID_ARG;
 }
 
-int to_quads(int c, const bf16* in, int nvox, bf16* out, hipStream_t s) {
-#define PG_TQ(C)                                                                                    \
-    if (c == C) {                                                                                   \
-        hipLaunchKernelGGL((k_to_quads<C>), g1(nvox / 4 * (C / 4)), dim3(256), 0, s, in, nvox, out); \
-        return PETGEM_OK;                                                                           \
+// k_conv_z for B samples. TZ: as many output planes a block as leave blocks
+// for three quarters of the compute units (twice that of 4-wave blocks), at
+// most CAP. us of 48 -> 16 at side 32 with TZ 1, 2, 4, 8: 47, 37, 31, 32 for 16
+// samples, 25, 20, 19, 28 for 7, 14, 12, 17, 28 for 3; of 96 -> 32 at side 16: 41,
+// 31, 25, 38; 21, 16, 22, 36; 11, 15, 22, 36.
+// Tiles, us for 16 samples at the TZ taken (TY rows x waves): 16 -> 48 4 x 4 32, 8 x 8 35,
+// 8 x 4 41; 32 -> 96 16 x 8 21, 8 x 8 23, 4 x 4 32; 96 -> 32 16 x 8 23, 8 x 8 25, 8 x 4 26
+// (for 3 samples 15, 11, 12).
+template <int CIN, int COUT, int C1, int D, int TY, int NTB, int NW, int EPI, int CAP = 4>
+int conv_z(const bf16* in, const bf16* up, const bf16* wt, const float* bias, const bf16* act, void* out, int B,
+           hipStream_t s) {
+    constexpr int lds = 2 * ((TY + 2) * (D + 2) * (CIN + 8) + 48 * NTB * (9 * CIN + 8));
+    static_assert(lds <= 160 * 1024, "one block's LDS");
+    auto kernel = k_conv_z<CIN, COUT, C1, D, TY, NTB, NW, EPI>;
+    static const hipError_t attr =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    PG_HIP(attr);
+    const int rows = B * (D / TY), outs = COUT / (16 * NTB);
+    int TZ = CAP;
+    while (TZ > 1 && rows * outs * (D / TZ) < 192 * 8 / NW) TZ /= 2;
+    hipLaunchKernelGGL(kernel, dim3(rows * (D / TZ), outs), dim3(64 * NW), lds, s, in, up, wt, bias, act, out, TZ);
+    return PETGEM_OK;
+}
+
+// up: null, or the coarse half of an upsampling concatenation
+int to_quads(int c, const bf16* in, const bf16* up, int nvox, bf16* out, hipStream_t s) {
+#define PG_TQ(C, C1, D)                                                                                            \
+    if (c == C && (up != nullptr) == (C1 > 0)) {                                                                   \
+        hipLaunchKernelGGL((k_to_quads<C, C1, D>), g1(nvox / 4 * (C / 4)), dim3(256), 0, s, in, up, nvox, out);      \
+        return PETGEM_OK;                                                                                          \
     }
-    PG_TQ(16) PG_TQ(32) PG_TQ(48) PG_TQ(64) PG_TQ(96)
+    PG_TQ(16, 0, 32) PG_TQ(32, 0, 16) PG_TQ(48, 32, 32) PG_TQ(64, 0, 8) PG_TQ(96, 64, 16)
 #undef PG_TQ
     set_error("unsupported channel count");
     return PETGEM_INVALID_ARG;
@@ -885,7 +1119,7 @@ void release_net(petgem_net* n) {
     for (auto& l : n->L) { dfree(l.wt); dfree(l.wtb); }
     dfree(n->P); dfree(n->Gr); dfree(n->M); dfree(n->Vv);
     dfree(n->X0); dfree(n->A1); dfree(n->P1); dfree(n->A2); dfree(n->P2); dfree(n->A3); dfree(n->A4);
-    dfree(n->Q2); dfree(n->A5); dfree(n->Q1); dfree(n->A6); dfree(n->dzb); dfree(n->Y);
+    dfree(n->A5); dfree(n->A6); dfree(n->dzb); dfree(n->Y);
     dfree(n->g0); dfree(n->g1); dfree(n->g2); dfree(n->wpart); dfree(n->tin); dfree(n->tdz); dfree(n->lpart); dfree(n->T);
     dfree(n->scal); dfree(n->vsrc); dfree(n->bbuf); dfree(n->bn);
     if (n->lpart_h) (void)hipHostFree(n->lpart_h);
@@ -900,32 +1134,33 @@ int cast_weights(petgem_net* n, hipStream_t s) {
     return PETGEM_OK;
 }
 
-// Forward pass on X0 (already filled) for B samples; output Y f32 [B][32^3][16].
-int forward(petgem_net* n, int B, hipStream_t s) {
-    const int v32 = B * kVox, v16 = B * kVox / 8, v8 = B * kVox / 64;
+// Forward pass on X (bf16 [B][32^3][16], 16-byte aligned) for B samples;
+// output Y f32 [B][32^3][16], 16-byte aligned.
+int forward(petgem_net* n, const bf16* X, int B, float* Y, hipStream_t s) {
+    const int v16 = B * kVox / 8, v8 = B * kVox / 64;
     auto& L = n->L;
-    PG_TRY(conv(16, 16, true, false, n->X0, L[0].wt, n->P + L[0].b_off, n->A1, v32, 32, s));
+    const float* P = n->P;
+    PG_TRY((conv_z<16, 16, 0, 32, 8, 1, 8, 0>(X, nullptr, L[0].wt, P + L[0].b_off, nullptr, n->A1, B, s)));
     hipLaunchKernelGGL(k_pool, g1((long)v16 * 4), dim3(256), 0, s, n->A1, B, 32, 16, n->P1);
-    PG_TRY(conv(16, 32, true, false, n->P1, L[1].wt, n->P + L[1].b_off, n->A2, v16, 16, s));
+    PG_TRY((conv_z<16, 32, 0, 16, 8, 2, 8, 0, 1>(n->P1, nullptr, L[1].wt, P + L[1].b_off, nullptr, n->A2, B, s)));
     hipLaunchKernelGGL(k_pool, g1((long)v8 * 8), dim3(256), 0, s, n->A2, B, 16, 32, n->P2);
-    PG_TRY(conv(32, 64, true, false, n->P2, L[2].wt, n->P + L[2].b_off, n->A3, v8, 8, s));
-    PG_TRY(conv(64, 64, true, false, n->A3, L[3].wt, n->P + L[3].b_off, n->A4, v8, 8, s));
-    hipLaunchKernelGGL(k_up_concat, g1((long)v16 * 24), dim3(256), 0, s, n->A4, 64, n->A2, 32, B, 16, n->Q2);
-    PG_TRY(conv(96, 32, true, false, n->Q2, L[4].wt, n->P + L[4].b_off, n->A5, v16, 16, s));
-    hipLaunchKernelGGL(k_up_concat, g1((long)v32 * 12), dim3(256), 0, s, n->A5, 32, n->A1, 16, B, 32, n->Q1);
-    PG_TRY(conv(48, 16, true, false, n->Q1, L[5].wt, n->P + L[5].b_off, n->A6, v32, 32, s));
-    PG_TRY(conv(16, 16, false, true, n->A6, L[6].wt, n->P + L[6].b_off, n->Y, v32, 32, s));
+    PG_TRY(conv8(32, 64, true, n->P2, L[2].wt, P + L[2].b_off, n->A3, v8, s));
+    PG_TRY(conv8(64, 64, true, n->A3, L[3].wt, P + L[3].b_off, n->A4, v8, s));
+    PG_TRY((conv_z<96, 32, 64, 16, 8, 1, 8, 0>(n->A2, n->A4, L[4].wt, P + L[4].b_off, nullptr, n->A5, B, s)));
+    PG_TRY((conv_z<48, 16, 32, 32, 8, 1, 8, 0>(n->A1, n->A5, L[5].wt, P + L[5].b_off, nullptr, n->A6, B, s)));
+    PG_TRY((conv_z<16, 16, 0, 32, 8, 1, 8, 1>(n->A6, nullptr, L[6].wt, P + L[6].b_off, nullptr, Y, B, s)));
     PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }
 
 // weight and bias gradients of layer li from its input `in` and dz (bf16,
-// channels-last); the bias gradient lands right after the weights (b_off =
+// channels-last; up: the coarse half of a concatenated input); the bias gradient lands right after the weights (b_off =
 // w_off + 27 cin cout)
-int layer_grads(petgem_net* n, int li, const bf16* in, const bf16* dz, int nvox, int D, hipStream_t s) {
+int layer_grads(petgem_net* n, int li, const bf16* in, const bf16* up, const bf16* dz, int nvox, int D,
+                hipStream_t s) {
     const NetLayer& l = n->L[li];
-    PG_TRY(to_quads(l.cin, in, nvox, n->tin, s));
-    PG_TRY(to_quads(l.cout, dz, nvox, n->tdz, s));
+    PG_TRY(to_quads(l.cin, in, up, nvox, n->tin, s));
+    PG_TRY(to_quads(l.cout, dz, nullptr, nvox, n->tdz, s));
     const int ns = bwdw_splits(l.cin, nvox, D);
     PG_TRY(conv_bwdw(l.cin, l.cout, n->tin, n->tdz, n->wpart, nvox, D, ns, s));
     const int nw = (27 * l.cin + 1) * l.cout;
@@ -934,56 +1169,67 @@ int layer_grads(petgem_net* n, int li, const bf16* in, const bf16* dz, int nvox,
     return PETGEM_OK;
 }
 
-// Backward pass from dY (bf16 in n->dzb, layout [B][32^3][16]); fills n->Gr.
-int backward(petgem_net* n, int B, hipStream_t s) {
+// Backward pass from dY (bf16 in n->dzb, layout [B][32^3][16]) and the
+// forward's input X; fills n->Gr.
+int backward(petgem_net* n, const bf16* X, int B, hipStream_t s) {
     const int v32 = B * kVox, v16 = B * kVox / 8, v8 = B * kVox / 64;
     auto& L = n->L;
-    bf16* dz = n->dzb;
+    bf16 *dy = n->dzb, *dz = n->dzb + (size_t)v32 * 16;
     float *g0 = n->g0, *g1b = n->g1, *g2 = n->g2;
-    // c7 (linear): dz = dY
-    PG_TRY(layer_grads(n, 6, n->A6, dz, v32, 32, s));
-    PG_TRY(conv(16, 16, false, true, dz, L[6].wtb, nullptr, g0, v32, 32, s));                  // dA6
-    hipLaunchKernelGGL(k_relu_bwd, g1((long)v32 * 4), dim3(256), 0, s, g0, n->A6, v32 * 16, dz);
+    // c7 (linear): dz = dY; its input's gradient through c6's ReLU
+    PG_TRY(layer_grads(n, 6, n->A6, nullptr, dy, v32, 32, s));
+    PG_TRY((conv_z<16, 16, 0, 32, 8, 1, 8, 2>(dy, nullptr, L[6].wtb, nullptr, n->A6, dz, B, s)));
     // c6
-    PG_TRY(layer_grads(n, 5, n->Q1, dz, v32, 32, s));
-    PG_TRY(conv(16, 48, false, true, dz, L[5].wtb, nullptr, g0, v32, 32, s));                  // dQ1 [v32][48]
+    PG_TRY(layer_grads(n, 5, n->A1, n->A5, dz, v32, 32, s));
+    PG_TRY((conv_z<16, 48, 0, 32, 4, 3, 4, 1, 8>(dz, nullptr, L[5].wtb, nullptr, nullptr, g0, B, s)));   // dQ1 [v32][48]
     // dA5 from the upsampled half of dQ1; g0 keeps dQ1's skip half for dA1
     // until c2's backward
     hipLaunchKernelGGL(k_up_bwd_relu, g1((long)v16 * 8), dim3(256), 0, s, g0, 48, B, 16, 32, n->A5, dz);
     // c5
-    PG_TRY(layer_grads(n, 4, n->Q2, dz, v16, 16, s));
-    PG_TRY(conv(32, 96, false, true, dz, L[4].wtb, nullptr, g1b, v16, 16, s));                 // dQ2 [v16][96]
+    PG_TRY(layer_grads(n, 4, n->A2, n->A4, dz, v16, 16, s));
+    PG_TRY((conv_z<32, 96, 0, 16, 16, 3, 8, 1>(dz, nullptr, L[4].wtb, nullptr, nullptr, g1b, B, s)));  // dQ2 [v16][96]
     hipLaunchKernelGGL(k_up_bwd_relu, g1((long)v8 * 16), dim3(256), 0, s, g1b, 96, B, 8, 64, n->A4, dz);   // dA4
     // c4
-    PG_TRY(layer_grads(n, 3, n->A3, dz, v8, 8, s));
-    PG_TRY(conv(64, 64, false, true, dz, L[3].wtb, nullptr, g2, v8, 8, s));                    // dA3
+    PG_TRY(layer_grads(n, 3, n->A3, nullptr, dz, v8, 8, s));
+    PG_TRY(conv8(64, 64, false, dz, L[3].wtb, nullptr, g2, v8, s));                            // dA3
     hipLaunchKernelGGL(k_relu_bwd, g1((long)v8 * 16), dim3(256), 0, s, g2, n->A3, v8 * 64, dz);
     // c3
-    PG_TRY(layer_grads(n, 2, n->P2, dz, v8, 8, s));
+    PG_TRY(layer_grads(n, 2, n->P2, nullptr, dz, v8, 8, s));
     float* dP2 = g2;   // [v8][32]
-    PG_TRY(conv(64, 32, false, true, dz, L[2].wtb, nullptr, dP2, v8, 8, s));
+    PG_TRY(conv8(64, 32, false, dz, L[2].wtb, nullptr, dP2, v8, s));
     // dA2 = skip half of dQ2 (channels 64..95) + pool backward of dP2
     hipLaunchKernelGGL(k_skip_pool_bwd_relu, g1((long)v16 * 8), dim3(256), 0, s, g1b, 96, 64, dP2, B, 16, 32, n->A2,
                        dz);
     // c2
-    PG_TRY(layer_grads(n, 1, n->P1, dz, v16, 16, s));
+    PG_TRY(layer_grads(n, 1, n->P1, nullptr, dz, v16, 16, s));
     float* dP1 = g1b;  // [v16][16]
-    PG_TRY(conv(32, 16, false, true, dz, L[1].wtb, nullptr, dP1, v16, 16, s));
+    PG_TRY((conv_z<32, 16, 0, 16, 4, 1, 4, 1, 2>(dz, nullptr, L[1].wtb, nullptr, nullptr, dP1, B, s)));
     // dA1 = skip half of dQ1 (channels 32..47) + pool backward of dP1
     hipLaunchKernelGGL(k_skip_pool_bwd_relu, g1((long)v32 * 4), dim3(256), 0, s, g0, 48, 32, dP1, B, 32, 16, n->A1,
                        dz);
     // c1
-    PG_TRY(layer_grads(n, 0, n->X0, dz, v32, 32, s));
+    PG_TRY(layer_grads(n, 0, X, nullptr, dz, v32, 32, s));
     PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }
 
-int loss_and_grads(petgem_net* n, const float* T, int B, hipStream_t s, double* loss) {
-    PG_TRY(forward(n, B, s));
+// The caller's input where the kernels' 16-byte loads can read it, else a copy.
+int input_of(petgem_net* n, const void* x_dev, int B, const bf16** X, hipStream_t s) {
+    *X = static_cast<const bf16*>(x_dev);
+    if (reinterpret_cast<uintptr_t>(x_dev) % 16 == 0) return PETGEM_OK;
+    PG_HIP(hipMemcpyAsync(n->X0, x_dev, sizeof(bf16) * (size_t)B * kVox * kIn, hipMemcpyDeviceToDevice, s));
+    *X = n->X0;
+    return PETGEM_OK;
+}
+
+int loss_and_grads(petgem_net* n, const void* x_dev, const float* T, int B, hipStream_t s, double* loss) {
+    const bf16* X = nullptr;
+    PG_TRY(input_of(n, x_dev, B, &X, s));
+    PG_TRY(forward(n, X, B, n->Y, s));
     const long nv = (long)B * kVox;
     const int nb = (int)((nv + 255) / 256);
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, n->Y, T, nv, 1.0 / ((double)nv * kOutUsed), n->dzb, n->lpart);
-    PG_TRY(backward(n, B, s));
+    PG_TRY(backward(n, X, B, s));
     PG_HIP(hipMemcpyAsync(n->lpart_h, n->lpart, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
     double sum = 0.0;
@@ -1098,8 +1344,8 @@ int petgem_net_create(int32_t batch_max, uint64_t seed, petgem_net** out) {
     const size_t v32 = (size_t)batch_max * kVox, v16 = v32 / 8, v8 = v32 / 64;
     if ((rc = dalloc(&n->X0, v32 * 16)) || (rc = dalloc(&n->A1, v32 * 16)) || (rc = dalloc(&n->P1, v16 * 16)) ||
         (rc = dalloc(&n->A2, v16 * 32)) || (rc = dalloc(&n->P2, v8 * 32)) || (rc = dalloc(&n->A3, v8 * 64)) ||
-        (rc = dalloc(&n->A4, v8 * 64)) || (rc = dalloc(&n->Q2, v16 * 96)) || (rc = dalloc(&n->A5, v16 * 32)) ||
-        (rc = dalloc(&n->Q1, v32 * 48)) || (rc = dalloc(&n->A6, v32 * 16)) || (rc = dalloc(&n->dzb, v32 * 48)) ||
+        (rc = dalloc(&n->A4, v8 * 64)) || (rc = dalloc(&n->A5, v16 * 32)) ||
+        (rc = dalloc(&n->A6, v32 * 16)) || (rc = dalloc(&n->dzb, v32 * 48)) ||
         (rc = dalloc(&n->Y, v32 * 16)) || (rc = dalloc(&n->g0, v32 * 48)) || (rc = dalloc(&n->g1, v16 * 96)) ||
         (rc = dalloc(&n->g2, v32 * 16)) || (rc = dalloc(&n->T, v32 * kOutUsed)) ||
         (rc = dalloc(&n->scal, (size_t)batch_max)) || (rc = dalloc(&n->vsrc, (size_t)batch_max)) ||
@@ -1153,9 +1399,12 @@ int petgem_net_set_params(petgem_net* n, const float* host) {
 int petgem_net_forward(petgem_net* n, const void* x_dev, int32_t B, void* y_dev, void* stream) {
     if (!n || !x_dev || !y_dev || B <= 0 || B > n->batch_max) { set_error("net forward: bad arguments"); return PETGEM_INVALID_ARG; }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_HIP(hipMemcpyAsync(n->X0, x_dev, sizeof(bf16) * (size_t)B * kVox * kIn, hipMemcpyDeviceToDevice, s));
-    PG_TRY(forward(n, B, s));
-    PG_HIP(hipMemcpyAsync(y_dev, n->Y, sizeof(float) * (size_t)B * kVox * kOut, hipMemcpyDeviceToDevice, s));
+    const bf16* X = nullptr;
+    PG_TRY(input_of(n, x_dev, B, &X, s));
+    const bool direct = reinterpret_cast<uintptr_t>(y_dev) % 16 == 0;   // the last layer's 16-byte stores
+    PG_TRY(forward(n, X, B, direct ? static_cast<float*>(y_dev) : n->Y, s));
+    if (!direct)
+        PG_HIP(hipMemcpyAsync(y_dev, n->Y, sizeof(float) * (size_t)B * kVox * kOut, hipMemcpyDeviceToDevice, s));
     return PETGEM_OK;
 }
 
@@ -1163,8 +1412,7 @@ int petgem_net_loss_grad(petgem_net* n, const void* x_dev, const void* t_dev, in
                          double* loss, float* grad_host) {
     if (!n || !x_dev || !t_dev || B <= 0 || B > n->batch_max) { set_error("net loss: bad arguments"); return PETGEM_INVALID_ARG; }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_HIP(hipMemcpyAsync(n->X0, x_dev, sizeof(bf16) * (size_t)B * kVox * kIn, hipMemcpyDeviceToDevice, s));
-    PG_TRY(loss_and_grads(n, static_cast<const float*>(t_dev), B, s, loss));
+    PG_TRY(loss_and_grads(n, x_dev, static_cast<const float*>(t_dev), B, s, loss));
     if (grad_host) {
         PG_HIP(hipMemcpyAsync(grad_host, n->Gr, sizeof(float) * n->nparam, hipMemcpyDeviceToHost, s));
         PG_HIP(hipStreamSynchronize(s));
@@ -1179,8 +1427,7 @@ int petgem_net_train_step(petgem_net* n, const void* x_dev, const void* t_dev, i
         return PETGEM_INVALID_ARG;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_HIP(hipMemcpyAsync(n->X0, x_dev, sizeof(bf16) * (size_t)B * kVox * kIn, hipMemcpyDeviceToDevice, s));
-    PG_TRY(loss_and_grads(n, static_cast<const float*>(t_dev), B, s, loss));
+    PG_TRY(loss_and_grads(n, x_dev, static_cast<const float*>(t_dev), B, s, loss));
     n->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float c1 = 1.f - std::pow(b1, (float)n->step), c2 = 1.f - std::pow(b2, (float)n->step);
@@ -1263,7 +1510,7 @@ int petgem_learned_x0(petgem_system* sys, petgem_net* n, const petgem_source* sr
     PG_TRY(upload_vsrc(n, src, B, s));
     hipLaunchKernelGGL(k_voxelize, g1((long)B * kVox), dim3(256), 0, s, sys->sigma, 0L, sys->vox_tet, n->vsrc, B,
                        sys->vox_lo[0], sys->vox_lo[1], sys->vox_lo[2], sys->vox_h, sys->vox_L, n->X0);
-    PG_TRY(forward(n, B, s));
+    PG_TRY(forward(n, n->X0, B, n->Y, s));
     hipLaunchKernelGGL(k_grid_to_edges, g1((long)B * sys->n_dof), dim3(256), 0, s, n->Y, B, sys->n_dof, sys->dof_mid,
                        sys->dof_tan, n->scal, sys->vox_lo[0], sys->vox_lo[1], sys->vox_lo[2], sys->vox_h,
                        static_cast<double2*>(x0_dev));
@@ -1315,7 +1562,7 @@ int petgem_learned_x0_many(petgem_system* const* systems, petgem_net* n, const p
                            sys->vox_lo[0], sys->vox_lo[1], sys->vox_lo[2], sys->vox_h, sys->vox_L,
                            n->X0 + (size_t)k * kVox * kIn);
     }
-    PG_TRY(forward(n, n_sys, s));
+    PG_TRY(forward(n, n->X0, n_sys, n->Y, s));
     for (int k = 0; k < n_sys; ++k) {
         const petgem_system* sys = systems[k];
         hipLaunchKernelGGL(k_grid_to_edges, g1(sys->n_dof), dim3(256), 0, s, n->Y + (size_t)k * kVox * kOut, 1,

@@ -145,3 +145,47 @@ def test_learned_guess_trains_and_solves(env):
     for a, b in zip(rb.E_zero, res.E_zero):
         num = np.sqrt(np.sum(np.abs(a - b) ** 2, axis=-1))
         assert np.max(num / np.sqrt(np.sum(np.abs(b) ** 2, axis=-1))) <= 1e-6
+
+
+# Output planes a block: 1 throughout (1 sample), 2 and 4 at side 32 and 1, 2
+# at side 16 (3, 7), 4 and 4 (12). A sample's sums do not depend on the
+# batch, so its outputs are the same bits.
+@pytest.mark.parametrize("B", [3, 7, 12])
+def test_forward_of_a_batch_is_that_of_its_samples(env, B):
+    torch, petgem, _ = env
+    net = petgem.Net(batch_max=B, seed=3)
+    x, _ = _bf16_input(torch, B, B)
+    y = net.forward(x)
+    for b in range(B):
+        assert torch.equal(y[b], net.forward(x[b:b + 1].contiguous())[0]), b
+
+
+# The gradient of a mean over B samples is the mean of theirs; with B a power
+# of two every bf16 value of the backward pass is scaled exactly, and only the
+# f32 sums of the weight pass are taken in another order: 2^13 additions in a
+# row at most, whose roundings add up like a walk to 2^6.5 2^-24 = 5e-6 of a
+# sum of terms of random sign; 20 times that.
+@pytest.mark.parametrize("B", [2, 8])
+def test_gradient_of_a_batch_is_the_mean_of_its_samples(env, B):
+    torch, petgem, _ = env
+    net = petgem.Net(batch_max=B, seed=3)
+    x, _ = _bf16_input(torch, B, B)
+    t = torch.randn((B, network.SIDE ** 3, 6), generator=torch.Generator().manual_seed(B)).cuda()
+    _, g = net.loss_grad(x, t)
+    one = [np.asarray(net.loss_grad(x[b:b + 1].contiguous(), t[b:b + 1].contiguous())[1], np.float64) for b in range(B)]
+    assert _rel(np.asarray(g, np.float64), sum(one) / B) <= 1e-4
+
+
+def test_unaligned_input_and_output(env):
+    torch, petgem, _ = env
+    net = petgem.Net(batch_max=2, seed=3)
+    x, _ = _bf16_input(torch, 2, 4)
+    y = net.forward(x)
+    xb = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")
+    xb[1:] = x.reshape(-1)
+    yb = torch.zeros(y.numel() + 1, dtype=y.dtype, device="cuda")
+    import ctypes as C
+    rc = petgem.lib().petgem_net_forward(net.handle, C.c_void_p(xb.data_ptr() + 2), 2, C.c_void_p(yb.data_ptr() + 4),
+                                         C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == petgem.OK
+    assert torch.equal(yb[1:], y.reshape(-1))
