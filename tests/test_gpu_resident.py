@@ -189,3 +189,21 @@ def test_resident_column_that_wanders_restarts(pg):
     assert max(s["iters"] for s in st) < 4000
     for k in (0, 17, 95):
         assert _residuals(sys[k], [srcs[k]], sols[k].x())[0] <= 1.01e-12
+
+
+# The concatenation of a batch: a mesh of one tile, one whose rows end in the
+# middle of a tile, one whose entries need several blocks, and the last row
+# pointer with and without padding; a system named twice.
+@pytest.mark.parametrize("ns", [[2], [5, 2], [12, 2, 9], [3, 12, 3]])
+def test_batch_of_unlike_systems_equals_single_solves(pg, ns):
+    print(f"[case] batch {ns}", flush=True)
+    ms = [_model(n, seed=11 + k) for k, n in enumerate(ns)]
+    sys = [pg.System.from_model(m) for m in ms]
+    srcs = [m.sources[0] for m in ms]
+    sys.append(sys[0])
+    srcs.append(synth.Dipole((-120.0, 40.0, 60.0), 0.7))
+    o = pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=RTOL)
+    sols, _, rc = pg.solve_many(sys, srcs, o)
+    assert rc == pg.OK
+    for k, S in enumerate(sys):
+        assert _residuals(S, [srcs[k]], sols[k].x())[0] <= 1.01 * RTOL
