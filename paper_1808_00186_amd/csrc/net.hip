@@ -460,10 +460,8 @@ k_conv_z(const bf16* __restrict__ in, const bf16* __restrict__ up, const bf16* _
 // channels C1 .. C - 1, and the first C1 are those of the parent voxel of the
 // coarse tensor `up` (D: fine side).
 template <int C, int C1, int D>
-__global__ void __launch_bounds__(256)
-k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, int nvox, bf16* __restrict__ out) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= nvox / 4 * (C / 4)) return;
+__device__ __forceinline__ void to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, int e,
+                                         bf16* __restrict__ out) {
     const int q = e / (C / 4), c = 4 * (e % (C / 4));
     uint2 w[4];
 #pragma unroll
@@ -473,6 +471,7 @@ k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, int nvox, b
         w[j] = *reinterpret_cast<const uint2*>(p);
     }
     // channel c + i of voxel 4q + j is half (i & 1) of word (i >> 1) of w[j]
+    uint2 o[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         uint32_t h[4];
@@ -481,8 +480,22 @@ k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, int nvox, b
             const uint32_t word = (i >> 1) ? w[j].y : w[j].x;
             h[j] = (i & 1) ? (word >> 16) : (word & 0xffffu);
         }
-        *reinterpret_cast<uint2*>(out + ((size_t)q * C + c + i) * 4) = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
+        o[i] = make_uint2(h[0] | (h[1] << 16), h[2] | (h[3] << 16));
     }
+    uint4* const dst = reinterpret_cast<uint4*>(out + ((size_t)q * C + c) * 4);
+    dst[0] = make_uint4(o[0].x, o[0].y, o[1].x, o[1].y);
+    dst[1] = make_uint4(o[2].x, o[2].y, o[3].x, o[3].y);
+}
+
+// Both operands of a layer's weight pass: its input (CI channels, C1 of them
+// from `up`) and its output gradient (CO channels).
+template <int CI, int C1, int CO, int D>
+__global__ void __launch_bounds__(256)
+k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, const bf16* __restrict__ dz, int nvox,
+           bf16* __restrict__ inQ, bf16* __restrict__ dzQ) {
+    const int e = blockIdx.x * 256 + threadIdx.x, ni = nvox / 4 * (CI / 4), nd = nvox / 4 * (CO / 4);
+    if (e < ni) to_quads<CI, C1, D>(in, up, e, inQ);
+    else if (e < ni + nd) to_quads<CO, 0, D>(dz, nullptr, e - ni, dzQ);
 }
 
 // Backward weights and bias from voxel-quad interleaved copies inQ
@@ -503,7 +516,9 @@ k_conv_bwdw(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* _
             int nvox, int nsplit) {
     constexpr int NT = COUT / 16, KW = 27 * CIN, Vs = D * D * D;
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-    const int s = blockIdx.x % nsplit, unit = blockIdx.x / nsplit;
+    // the units of a split next to each other on one XCD: they read the same dz
+    // and, three at a time, the same input rows, so all but one find them in its L2
+    const int lb = xcd_block(blockIdx.x, gridDim.x), nu = gridDim.x / nsplit, s = lb / nu, unit = lb % nu;
     const int g = unit / 3, pz = unit % 3;
     const bool bias_unit = unit == 1;   // g = 0, z offset 0
     const int nK = nvox / 16, chunk = (nK + nsplit - 1) / nsplit;
@@ -624,7 +639,9 @@ k_conv_bwdw_col(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, floa
     constexpr int NT = COUT / 16, KW = 27 * CIN, Vs = D * D * D, XS = D / 16;
     static_assert(D % 16 == 0, "a column step is 16 voxels of one x row");
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
-    const int s = blockIdx.x % nsplit, unit = blockIdx.x / nsplit;
+    // the units of a split next to each other on one XCD: they read the same dz
+    // and, three at a time, the same input rows, so all but one find them in its L2
+    const int lb = xcd_block(blockIdx.x, gridDim.x), nu = gridDim.x / nsplit, s = lb / nu, unit = lb % nu;
     const int g = unit / 3, pz = unit % 3, ci = g * 16 + m;
     const bool bias_unit = unit == 1;   // g = 0, z offset 0
     const int c0 = s * chunk, c1 = min(ncol, c0 + chunk);   // chunk: columns per split, a multiple of 4
@@ -722,13 +739,24 @@ k_conv_bwdw_col(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, floa
     }
 }
 
-// out[i] = sum over the nsplit partials of entry i: 16 interleaved groups of
-// splits summed in split order, then the groups in a fixed tree order
-// (deterministic). A block covers 64 entries with 1024 threads.
+// out[i] = sum over the nsplit partials of entry i, for every layer in one
+// launch: 16 interleaved groups of splits summed in split order, then the
+// groups in a fixed tree order (deterministic). A block covers 64 entries of
+// a layer with 1024 threads. (A launch a layer: 5.7 us each, most of it drain.)
+constexpr int kLayers = 7;
+struct SplitSums {
+    const float* partial[kLayers];
+    float* out[kLayers];
+    int nsplit[kLayers], n[kLayers], block0[kLayers + 1];
+};
 __global__ void __launch_bounds__(1024)
-k_sum_splits(const float* __restrict__ partial, int nsplit, int n, float* __restrict__ out) {
+k_sum_splits(SplitSums a) {
     __shared__ float red[16][64];
-    const int e = threadIdx.x & 63, q = threadIdx.x >> 6, i = blockIdx.x * 64 + e;
+    int li = 0;
+    while (li < kLayers - 1 && (int)blockIdx.x >= a.block0[li + 1]) ++li;
+    const float* const partial = a.partial[li];
+    const int nsplit = a.nsplit[li], n = a.n[li];
+    const int e = threadIdx.x & 63, q = threadIdx.x >> 6, i = ((int)blockIdx.x - a.block0[li]) * 64 + e;
     float sum = 0.f;
     if (i < n)
         for (int k = q; k < nsplit; k += 16) sum += partial[(long)k * n + i];
@@ -738,7 +766,7 @@ k_sum_splits(const float* __restrict__ partial, int nsplit, int n, float* __rest
         if (q < h) red[q][e] += red[q + h][e];
         __syncthreads();
     }
-    if (q == 0 && i < n) out[i] = red[0][e];
+    if (q == 0 && i < n) a.out[li][i] = red[0][e];
 }
 
 // 2x2x2 average pooling (fine side D), C channels
@@ -961,6 +989,7 @@ struct NetLayer {
     int cin, cout, side;
     bool relu;
     size_t w_off, b_off;   // offsets into the parameter vector (floats)
+    size_t p_off;          // of its partials of the weight pass (floats)
     bf16* wt = nullptr;    // forward layout
     bf16* wtb = nullptr;   // backward-data layout
 };
@@ -1064,14 +1093,17 @@ int conv_z(const bf16* in, const bf16* up, const bf16* wt, const float* bias, co
     return PETGEM_OK;
 }
 
-// up: null, or the coarse half of an upsampling concatenation
-int to_quads(int c, const bf16* in, const bf16* up, int nvox, bf16* out, hipStream_t s) {
-#define PG_TQ(C, C1, D)                                                                                            \
-    if (c == C && (up != nullptr) == (C1 > 0)) {                                                                   \
-        hipLaunchKernelGGL((k_to_quads<C, C1, D>), g1(nvox / 4 * (C / 4)), dim3(256), 0, s, in, up, nvox, out);      \
-        return PETGEM_OK;                                                                                          \
+// up: the coarse half of a concatenated input
+int quads(int cin, int cout, const bf16* in, const bf16* up, const bf16* dz, int nvox, int D, bf16* inQ, bf16* dzQ,
+          hipStream_t s) {
+#define PG_TQ(A, A1, B, SIDE)                                                                                    \
+    if (cin == A && cout == B && D == SIDE) {                                                                    \
+        hipLaunchKernelGGL((k_to_quads<A, A1, B, SIDE>), g1(nvox / 16 * (A + B)), dim3(256), 0, s, in, up, dz, nvox, \
+                           inQ, dzQ);                                                                            \
+        return PETGEM_OK;                                                                                        \
     }
-    PG_TQ(16, 0, 32) PG_TQ(32, 0, 16) PG_TQ(48, 32, 32) PG_TQ(64, 0, 8) PG_TQ(96, 64, 16)
+    PG_TQ(16, 0, 16, 32) PG_TQ(16, 0, 32, 16) PG_TQ(32, 0, 64, 8) PG_TQ(64, 0, 64, 8) PG_TQ(96, 64, 32, 16)
+    PG_TQ(48, 32, 16, 32)
 #undef PG_TQ
     set_error("unsupported channel count");
     return PETGEM_INVALID_ARG;
@@ -1159,12 +1191,8 @@ int forward(petgem_net* n, const bf16* X, int B, float* Y, hipStream_t s) {
 int layer_grads(petgem_net* n, int li, const bf16* in, const bf16* up, const bf16* dz, int nvox, int D,
                 hipStream_t s) {
     const NetLayer& l = n->L[li];
-    PG_TRY(to_quads(l.cin, in, up, nvox, n->tin, s));
-    PG_TRY(to_quads(l.cout, dz, nullptr, nvox, n->tdz, s));
-    const int ns = bwdw_splits(l.cin, nvox, D);
-    PG_TRY(conv_bwdw(l.cin, l.cout, n->tin, n->tdz, n->wpart, nvox, D, ns, s));
-    const int nw = (27 * l.cin + 1) * l.cout;
-    hipLaunchKernelGGL(k_sum_splits, dim3(ceil_div(nw, 64)), dim3(1024), 0, s, n->wpart, ns, nw, n->Gr + l.w_off);
+    PG_TRY(quads(l.cin, l.cout, in, up, dz, nvox, D, n->tin, n->tdz, s));
+    PG_TRY(conv_bwdw(l.cin, l.cout, n->tin, n->tdz, n->wpart + l.p_off, nvox, D, bwdw_splits(l.cin, nvox, D), s));
     PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }
@@ -1209,6 +1237,16 @@ int backward(petgem_net* n, const bf16* X, int B, hipStream_t s) {
                        dz);
     // c1
     PG_TRY(layer_grads(n, 0, X, nullptr, dz, v32, 32, s));
+    SplitSums a{};
+    for (int li = 0; li < kLayers; ++li) {
+        const NetLayer& l = n->L[li];
+        a.partial[li] = n->wpart + l.p_off;
+        a.out[li] = n->Gr + l.w_off;
+        a.nsplit[li] = bwdw_splits(l.cin, (long)B * l.side * l.side * l.side, l.side);
+        a.n[li] = (27 * l.cin + 1) * l.cout;
+        a.block0[li + 1] = a.block0[li] + ceil_div(a.n[li], 64);
+    }
+    hipLaunchKernelGGL(k_sum_splits, dim3(a.block0[kLayers]), dim3(1024), 0, s, a);
     PG_HIP(hipGetLastError());
     return PETGEM_OK;
 }
@@ -1222,7 +1260,8 @@ int input_of(petgem_net* n, const void* x_dev, int B, const bf16** X, hipStream_
     return PETGEM_OK;
 }
 
-int loss_and_grads(petgem_net* n, const void* x_dev, const float* T, int B, hipStream_t s, double* loss) {
+int loss_and_grads(petgem_net* n, const void* x_dev, const float* T, int B, hipStream_t s, double* loss,
+                   float* grad_host = nullptr) {
     const bf16* X = nullptr;
     PG_TRY(input_of(n, x_dev, B, &X, s));
     PG_TRY(forward(n, X, B, n->Y, s));
@@ -1231,6 +1270,8 @@ int loss_and_grads(petgem_net* n, const void* x_dev, const float* T, int B, hipS
     hipLaunchKernelGGL(k_mse, dim3(nb), dim3(256), 0, s, n->Y, T, nv, 1.0 / ((double)nv * kOutUsed), n->dzb, n->lpart);
     PG_TRY(backward(n, X, B, s));
     PG_HIP(hipMemcpyAsync(n->lpart_h, n->lpart, sizeof(double) * nb, hipMemcpyDeviceToHost, s));
+    if (grad_host)
+        PG_HIP(hipMemcpyAsync(grad_host, n->Gr, sizeof(float) * n->nparam, hipMemcpyDeviceToHost, s));
     PG_HIP(hipStreamSynchronize(s));
     double sum = 0.0;
     for (int i = 0; i < nb; ++i) sum += n->lpart_h[i];
@@ -1351,10 +1392,14 @@ int petgem_net_create(int32_t batch_max, uint64_t seed, petgem_net** out) {
         (rc = dalloc(&n->scal, (size_t)batch_max)) || (rc = dalloc(&n->vsrc, (size_t)batch_max)) ||
         (rc = dalloc(&n->bn, (size_t)batch_max)))
         return fail(rc);
-    size_t wp = 0;   // the largest split count over every batch size up to batch_max
-    for (auto& l : n->L)
+    size_t wp = 0;   // of each layer the largest split count over every batch size up to batch_max
+    for (auto& l : n->L) {
+        size_t most = 0;
         for (int bb = 1; bb <= batch_max; ++bb)
-            wp = std::max(wp, wpart_floats(l.cin, l.cout, (long)bb * l.side * l.side * l.side, l.side));
+            most = std::max(most, wpart_floats(l.cin, l.cout, (long)bb * l.side * l.side * l.side, l.side));
+        l.p_off = wp;
+        wp += most;
+    }
     if ((rc = dalloc(&n->wpart, wp)) || (rc = dalloc(&n->tin, v32 * 48)) || (rc = dalloc(&n->tdz, v32 * 16)) || (rc = dalloc(&n->lpart, (size_t)ceil_div((int64_t)v32, 256))))
         return fail(rc);
     if (hipHostMalloc(reinterpret_cast<void**>(&n->lpart_h), sizeof(double) * ceil_div((int64_t)v32, 256)) != hipSuccess)
@@ -1412,12 +1457,7 @@ int petgem_net_loss_grad(petgem_net* n, const void* x_dev, const void* t_dev, in
                          double* loss, float* grad_host) {
     if (!n || !x_dev || !t_dev || B <= 0 || B > n->batch_max) { set_error("net loss: bad arguments"); return PETGEM_INVALID_ARG; }
     hipStream_t s = static_cast<hipStream_t>(stream);
-    PG_TRY(loss_and_grads(n, x_dev, static_cast<const float*>(t_dev), B, s, loss));
-    if (grad_host) {
-        PG_HIP(hipMemcpyAsync(grad_host, n->Gr, sizeof(float) * n->nparam, hipMemcpyDeviceToHost, s));
-        PG_HIP(hipStreamSynchronize(s));
-    }
-    return PETGEM_OK;
+    return loss_and_grads(n, x_dev, static_cast<const float*>(t_dev), B, s, loss, grad_host);
 }
 
 int petgem_net_train_step(petgem_net* n, const void* x_dev, const void* t_dev, int32_t B, float lr, void* stream,
