@@ -498,6 +498,21 @@ k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, const bf16*
     else if (e < ni + nd) to_quads<CO, 0, D>(dz, nullptr, e - ni, dzQ);
 }
 
+// The same channel's word of the quad to the left (lanes 16 lower) and to the
+// right (16 higher): by row and half swaps of registers, where loading the
+// neighbouring words took six of a step's eleven load instructions, which
+// bound the pass. Lanes 0..15 (48..63) have no such neighbour and get any.
+__device__ __forceinline__ uint32_t quad_left(uint32_t v, int kq) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);          // rows 0 0 2 2, 1 1 3 3
+    const auto t = __builtin_amdgcn_permlane32_swap(r[1], r[1], false, false);    // 1 1 1 1
+    return kq == 2 ? t[0] : r[0];
+}
+__device__ __forceinline__ uint32_t quad_right(uint32_t v, int kq) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    const auto t = __builtin_amdgcn_permlane32_swap(r[0], r[0], false, false);    // second: 2 2 2 2
+    return kq == 1 ? t[1] : r[1];
+}
+
 // Backward weights and bias from voxel-quad interleaved copies inQ
 // [B D^3 / 4][CIN][4] and dzQ [B D^3 / 4][COUT][4]:
 //   partial[s][tap * CIN + ci][co] = sum over the voxels of split s of
@@ -508,14 +523,20 @@ k_to_quads(const bf16* __restrict__ in, const bf16* __restrict__ up, const bf16*
 // block is one (16-channel input group, z offset) unit and one voxel split;
 // its 4 waves take alternate K steps and are summed through LDS in wave
 // order, so the result does not depend on timing. A wave keeps the 9 (y, x)
-// offsets x all output tiles in registers: one 16-byte load per input row
-// (x0-2 .. x0+5 of one channel) yields the three x shifts by funnel shifts.
+// offsets x all output tiles in registers: one 8-byte load per input row (x0
+// .. x0+3 of one channel) and its neighbours' words in the wave yield the three
+// x shifts by funnel shifts. Three steps are in flight behind the one
+// computed. us for 16 samples, with the step handed from slot to slot (which waited
+// for its loads) and now: 16 -> 32 11.9, 10.9; 32 -> 64 13.7, 12.8; 64 -> 64 14.5,
+// 13.3; 96 -> 32 38, 38 (five steps a wave at side 8, 18 at the last: the start and
+// the sums over waves weigh as much as the products).
 template <int CIN, int COUT, int D>
 __global__ void __launch_bounds__(256)
 k_conv_bwdw(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* __restrict__ partial,
             int nvox, int nsplit) {
     constexpr int NT = COUT / 16, KW = 27 * CIN, Vs = D * D * D;
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
     // the units of a split next to each other on one XCD: they read the same dz
     // and, three at a time, the same input rows, so all but one find them in its L2
     const int lb = xcd_block(blockIdx.x, gridDim.x), nu = gridDim.x / nsplit, s = lb / nu, unit = lb % nu;
@@ -533,41 +554,44 @@ k_conv_bwdw(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* _
             for (int c = 0; c < 3; ++c) acc[a][c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const bf16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
-    // operands of one K step: dz fragments and, per y offset, the row words
-    // x0-2 .. x0+5 of this lane's input channel
+    // A K step k is 16 / D rows of one z plane: b, z and the first row are the
+    // same for the wave (scalar arithmetic), a lane's row among them and x0
+    // never change. Operands: dz fragments and, per y offset, the quad x0 ..
+    // x0+3 of this lane's input channel (the row's neighbouring quads are in
+    // the wave). Loads are unconditional (clamped to the tensor), what is
+    // outside the grid is zeroed when it is used.
+    constexpr int RPS = 16 / D, SP = D / RPS;   // rows of a step, steps of a plane
+    const int rl = 4 * kq / D, x0 = 4 * kq % D, ci = g * 16 + m, nrow = nvox / D;
+    const bool lok = x0 > 0, rok = x0 + 4 < D;
+    const int lane_in = (x0 / 4 * CIN + ci) * 4, lane_dz = ((rl * D + x0) / 4 * COUT + m) * 4;
     struct Step {
         bf16x4 w[NT];
-        uint32_t dp[3], d0[3], d1[3], dn[3];
+        uint2 c[3];
     };
     auto load = [&](int k, Step& st) {
-        const int v = 16 * k + 4 * kq;
-        const int b = v / Vs, r = v % Vs;
-        const int z = r / (D * D), y = (r / D) % D, x0 = r % D;
+        const int kc = min(k, nK - 1), z = kc / SP % D, zz = min(max(z + pz - 1, 0), D - 1);
+        const bf16* const pd = dzQ + (size_t)kc * 16 * COUT;
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-            st.w[t] = *reinterpret_cast<const bf16x4*>(dzQ + ((long)(v / 4) * COUT + t * 16 + m) * 4);
-        const int zz = z + pz - 1, ci = g * 16 + m;
+        for (int t = 0; t < NT; ++t) st.w[t] = *reinterpret_cast<const bf16x4*>(pd + lane_dz + 64 * t);
+        const int row0 = kc * RPS + (zz - z) * D;
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy) {
-            const int yy = y + dy - 1;
-            st.dp[dy] = st.d0[dy] = st.d1[dy] = st.dn[dy] = 0;
-            if (zz >= 0 && zz < D && yy >= 0 && yy < D) {
-                const long q = ((long)b * Vs + ((long)zz * D + yy) * D + x0) / 4;   // quad of x0 .. x0+3
-                const uint2 c = *reinterpret_cast<const uint2*>(inQ + (q * CIN + ci) * 4);
-                st.d0[dy] = c.x;
-                st.d1[dy] = c.y;
-                if (x0 > 0) st.dp[dy] = *reinterpret_cast<const uint32_t*>(inQ + ((q - 1) * CIN + ci) * 4 + 2);
-                if (x0 + 4 < D) st.dn[dy] = *reinterpret_cast<const uint32_t*>(inQ + ((q + 1) * CIN + ci) * 4);
-            }
+            const int row = min(max(row0 + (RPS > 1 ? rl : 0) + dy - 1, 0), nrow - 1);
+            st.c[dy] = *reinterpret_cast<const uint2*>(inQ + (size_t)row * (D * CIN) + lane_in);
         }
     };
-    auto compute = [&](const Step& st) {
+    auto compute = [&](int k, const Step& st) {
+        const int y = k % SP * RPS + (RPS > 1 ? rl : 0), zz = k / SP % D + pz - 1;
+        const bool zok = zz >= 0 && zz < D;
 #pragma unroll
         for (int dy = 0; dy < 3; ++dy) {
-            const uint32_t dp = st.dp[dy], d0 = st.d0[dy], d1 = st.d1[dy], dn = st.dn[dy];
+            const bool ok = zok && y + dy - 1 >= 0 && y + dy - 1 < D;
+            const uint32_t d0 = ok ? st.c[dy].x : 0u, d1 = ok ? st.c[dy].y : 0u;
+            const uint32_t l1 = quad_left(d1, kq), r0 = quad_right(d0, kq);
+            const uint32_t dp = lok ? l1 : 0u, dn = rok ? r0 : 0u;
             // voxels x0-1..x0+2, x0..x0+3, x0+1..x0+4 of this row
-            const uint32_t lo[3] = {(dp >> 16) | (d0 << 16), d0, (d0 >> 16) | (d1 << 16)};
-            const uint32_t hi[3] = {(d0 >> 16) | (d1 << 16), d1, (d1 >> 16) | (dn << 16)};
+            const uint32_t mid = (d0 >> 16) | (d1 << 16);
+            const uint32_t lo[3] = {(dp >> 16) | (d0 << 16), d0, mid}, hi[3] = {mid, d1, (d1 >> 16) | (dn << 16)};
 #pragma unroll
             for (int dx = 0; dx < 3; ++dx) {
                 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -583,32 +607,37 @@ k_conv_bwdw(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* _
                 accb[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, st.w[t], accb[t], 0, 0, 0);
         }
     };
-    // the loads of the next two K steps are in flight during the MFMAs of this one
-    Step s0, s1;
+    // NS - 1 steps' loads are in flight behind the step computed. The slots
+    // have fixed names in the unrolled loop: handing a slot on by a copy would
+    // wait for its loads.
+    constexpr int NS = NT >= 4 ? 3 : 4;
+    Step st[NS];
     int k = k0 + wave;
-    if (k < k1) load(k, s0);
-    if (k + 4 < k1) load(k + 4, s1);
-    for (; k < k1; k += 4) {
-        Step s2 = s1;
-        if (k + 8 < k1) load(k + 8, s2);
-        compute(s0);
-        s0 = s1;
-        s1 = s2;
+#pragma unroll
+    for (int u = 0; u < NS - 1; ++u) load(k + 4 * u, st[u]);
+    // (whole rounds without a condition: across one the compiler waits for
+    // every load)
+    for (; k + 4 * (NS - 1) < k1; k += 4 * NS) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            load(k + 4 * (u + NS - 1), st[(u + NS - 1) % NS]);
+            compute(k + 4 * u, st[u]);
+        }
     }
+#pragma unroll
+    for (int u = 0; u < NS - 1; ++u)
+        if (k + 4 * u < k1) compute(k + 4 * u, st[u]);
     // wave-ordered sum of the 4 waves, one output tile column at a time;
     // lane holds D[row ci = 4 kq + j][col co = m]
-    __shared__ float red[4][10][256];
+    __shared__ __align__(16) float red[4][10][256];
     float* base = partial + (long)s * (KW + 1) * COUT;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) red[wave][3 * a + c][4 * l + j] = acc[a][c][t][j];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) red[wave][9][4 * l + j] = accb[t][j];
+            for (int c = 0; c < 3; ++c) *reinterpret_cast<f32x4*>(&red[wave][3 * a + c][4 * l]) = acc[a][c][t];
+        *reinterpret_cast<f32x4*>(&red[wave][9][4 * l]) = accb[t];
         __syncthreads();
         for (int e = threadIdx.x; e < 10 * 256; e += 256) {
             const int tile = e / 256, ln = (e / 4) % 64, j = e % 4;
@@ -630,15 +659,19 @@ k_conv_bwdw(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* _
 // along y. A column is (sample, z, 16-voxel x segment); a wave walks a
 // column's D output rows and keeps the input rows y-1, y, y+1 of its z plane
 // in registers, so each step loads one new input row (and the next row of
-// dz) instead of three. Same units, splits, LDS reduction and partial layout
-// as k_conv_bwdw; the bias unit adds the ones-operand MFMA.
+// dz) instead of three, shifts it once for the three steps that use it, and has
+// the next four on the way. Same units, splits, LDS reduction and partial
+// layout as k_conv_bwdw; the bias unit adds the ones-operand MFMA. us for 16
+// samples, with one row ahead and two more loads a row, and now: 48 -> 16
+// 64.6, 47; 16 -> 16 22.3, 15.9 (matrix cores 17 and 6).
 template <int CIN, int COUT, int D>
 __global__ void __launch_bounds__(256)
 k_conv_bwdw_col(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, float* __restrict__ partial,
                 int ncol, int nsplit, int chunk) {
     constexpr int NT = COUT / 16, KW = 27 * CIN, Vs = D * D * D, XS = D / 16;
     static_assert(D % 16 == 0, "a column step is 16 voxels of one x row");
-    const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = threadIdx.x & 63, m = l & 15, kq = l >> 4;
     // the units of a split next to each other on one XCD: they read the same dz
     // and, three at a time, the same input rows, so all but one find them in its L2
     const int lb = xcd_block(blockIdx.x, gridDim.x), nu = gridDim.x / nsplit, s = lb / nu, unit = lb % nu;
@@ -655,74 +688,86 @@ k_conv_bwdw_col(const bf16* __restrict__ inQ, const bf16* __restrict__ dzQ, floa
             for (int c = 0; c < 3; ++c) acc[a][c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     const bf16x4 ones = {0x3f80, 0x3f80, 0x3f80, 0x3f80};
-    struct Row { uint32_t dp, d0, d1, dn; };   // x0-2 .. x0+5 of this lane's channel
+    struct Raw { uint2 c; uint32_t e; };             // x0 .. x0+3 of this lane's channel; the word beside the 16 voxels
+    struct Row { uint32_t s0, d0, mid, d1, s2; };    // its three x shifts: {s0, mid}, {d0, d1}, {mid, s2}
     struct Frag { bf16x4 w[NT]; };
+    constexpr int PD = 4;   // rows in flight; the slots have fixed names in the unrolled loop
+    static_assert(D % PD == 0, "whole rounds of slots");
     for (int col = c0 + wave; col < c1; col += 4) {
         const int xs = col % XS, bz = col / XS, z = bz % D, b = bz / D;
         const int x0 = xs * 16 + 4 * kq, zz = z + pz - 1;
-        const bool zok = zz >= 0 && zz < D;
-        auto row = [&](int yy) {
-            Row r{0u, 0u, 0u, 0u};
-            if (zok && yy >= 0 && yy < D) {
-                const long q = ((long)b * Vs + ((long)zz * D + yy) * D + x0) / 4;   // quad of x0 .. x0+3
-                const uint2 c = *reinterpret_cast<const uint2*>(inQ + (q * CIN + ci) * 4);
-                r.d0 = c.x;
-                r.d1 = c.y;
-                if (x0 > 0) r.dp = *reinterpret_cast<const uint32_t*>(inQ + ((q - 1) * CIN + ci) * 4 + 2);
-                if (x0 + 4 < D) r.dn = *reinterpret_cast<const uint32_t*>(inQ + ((q + 1) * CIN + ci) * 4);
-            }
-            return r;
+        const bool zok = zz >= 0 && zz < D, lok = x0 > 0, rok = x0 + 4 < D;
+        const bf16* const pi = inQ + (((long)b * Vs + (long)(zok ? zz : 0) * D * D + x0) / 4 * CIN + ci) * 4;
+        const bf16* const pd = dzQ + (((long)b * Vs + (long)z * D * D + x0) / 4 * COUT + m) * 4;
+        const int edge = kq == 0 && lok ? 2 - 4 * CIN : kq == 3 && rok ? 4 * CIN : 0;
+        // loads are unconditional (clamped), what is outside is zeroed by finish
+        auto load = [&](int y, Raw& r) {
+            const bf16* const p = pi + min(y, D - 1) * (D * CIN);
+            r.c = *reinterpret_cast<const uint2*>(p);
+            r.e = *reinterpret_cast<const uint32_t*>(p + edge);
         };
-        auto frag = [&](int y) {
-            Frag f;
-            const long q = ((long)b * Vs + ((long)z * D + y) * D + x0) / 4;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) f.w[t] = *reinterpret_cast<const bf16x4*>(dzQ + (q * COUT + t * 16 + m) * 4);
-            return f;
+        auto finish = [&](int y, const Raw& r) {
+            const bool ok = zok && y < D;
+            const uint32_t d0 = ok ? r.c.x : 0u, d1 = ok ? r.c.y : 0u, e = ok ? r.e : 0u;
+            const uint32_t l1 = quad_left(d1, kq), r0 = quad_right(d0, kq);
+            const uint32_t dp = kq > 0 ? l1 : lok ? e : 0u, dn = kq < 3 ? r0 : rok ? e : 0u;
+            return Row{(dp >> 16) | (d0 << 16), d0, (d0 >> 16) | (d1 << 16), d1, (d1 >> 16) | (dn << 16)};
         };
-        Row ra{0u, 0u, 0u, 0u}, rb = row(0), rc = row(1);
-        Frag fc = frag(0);
-        for (int y = 0; y < D; ++y) {
-            const Row rn = row(y + 2);                        // zero past the last row
-            const Frag fn = y + 1 < D ? frag(y + 1) : fc;
-            const Row* rows[3] = {&ra, &rb, &rc};             // input rows y-1, y, y+1
+        auto frag = [&](int y, Frag& f) {
+            const bf16* const p = pd + min(y, D - 1) * (D * COUT);
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy) {
-                const uint32_t dp = rows[dy]->dp, d0 = rows[dy]->d0, d1 = rows[dy]->d1, dn = rows[dy]->dn;
-                const uint32_t lo[3] = {(dp >> 16) | (d0 << 16), d0, (d0 >> 16) | (d1 << 16)};
-                const uint32_t hi[3] = {(d0 >> 16) | (d1 << 16), d1, (d1 >> 16) | (dn << 16)};
+            for (int t = 0; t < NT; ++t) f.w[t] = *reinterpret_cast<const bf16x4*>(p + 64 * t);
+        };
+        Raw raw[PD];     // row y in slot y % PD
+        Frag fr[PD];
+        Raw r0;
+        load(0, r0);
 #pragma unroll
-                for (int dx = 0; dx < 3; ++dx) {
-                    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                    const bf16x4 a = __builtin_bit_cast(bf16x4, (u32x2{lo[dx], hi[dx]}));
+        for (int u = 0; u < PD; ++u) {
+            frag(u, fr[u]);
+            load(u + 1, raw[(u + 1) % PD]);
+        }
+        Row ra{0u, 0u, 0u, 0u, 0u}, rb = finish(0, r0);
+        for (int y0 = 0; y0 < D; y0 += PD) {
+#pragma unroll
+            for (int u = 0; u < PD; ++u) {
+                const int y = y0 + u;
+                const Row rc = finish(y + 1, raw[(u + 1) % PD]);
+                load(y + 1 + PD, raw[(u + 1) % PD]);
+                const Row* rows[3] = {&ra, &rb, &rc};             // input rows y-1, y, y+1
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const uint32_t lo[3] = {rows[dy]->s0, rows[dy]->d0, rows[dy]->mid};
+                    const uint32_t hi[3] = {rows[dy]->mid, rows[dy]->d1, rows[dy]->s2};
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) {
+                        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                        const bf16x4 a = __builtin_bit_cast(bf16x4, (u32x2{lo[dx], hi[dx]}));
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+                            acc[dy][dx][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, fr[u].w[t], acc[dy][dx][t], 0, 0, 0);
+                    }
+                }
+                if (bias_unit) {
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
-                        acc[dy][dx][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, fc.w[t], acc[dy][dx][t], 0, 0, 0);
+                        accb[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, fr[u].w[t], accb[t], 0, 0, 0);
                 }
+                frag(y + PD, fr[u]);
+                ra = rb;
+                rb = rc;
             }
-            if (bias_unit) {
-#pragma unroll
-                for (int t = 0; t < NT; ++t)
-                    accb[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ones, fc.w[t], accb[t], 0, 0, 0);
-            }
-            ra = rb;
-            rb = rc;
-            rc = rn;
-            fc = fn;
         }
     }
-    __shared__ float red[4][10][256];
+    __shared__ __align__(16) float red[4][10][256];
     float* base = partial + (long)s * (KW + 1) * COUT;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) red[wave][3 * a + c][4 * l + j] = acc[a][c][t][j];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) red[wave][9][4 * l + j] = accb[t][j];
+            for (int c = 0; c < 3; ++c) *reinterpret_cast<f32x4*>(&red[wave][3 * a + c][4 * l]) = acc[a][c][t];
+        *reinterpret_cast<f32x4*>(&red[wave][9][4 * l]) = accb[t];
         __syncthreads();
         for (int e = threadIdx.x; e < 10 * 256; e += 256) {
             const int tile = e / 256, ln = (e / 4) % 64, j = e % 4;
@@ -1185,9 +1230,9 @@ int forward(petgem_net* n, const bf16* X, int B, float* Y, hipStream_t s) {
     return PETGEM_OK;
 }
 
-// weight and bias gradients of layer li from its input `in` and dz (bf16,
-// channels-last; up: the coarse half of a concatenated input); the bias gradient lands right after the weights (b_off =
-// w_off + 27 cin cout)
+// partials of the weight and bias gradients of layer li from its input `in`
+// (up: the coarse half of a concatenated one) and dz (bf16, channels-last);
+// the bias gradient's come right after the weights' (b_off = w_off + 27 cin cout)
 int layer_grads(petgem_net* n, int li, const bf16* in, const bf16* up, const bf16* dz, int nvox, int D,
                 hipStream_t s) {
     const NetLayer& l = n->L[li];
