@@ -170,6 +170,8 @@ def cpu_baseline_cfg2(model, budget_iters: int):
 def kernel_name(form, shape):
     """Name of the sparse kernel a solve used (its spmv_shape stat)."""
     if form == "plain":
+        if shape == 1:
+            return "k_gm_solve complex128 (A D^-1), all cycles in one launch"
         return f"k_spmv<{shape}, false> complex128 CSR (A D^-1)"
     kind, a, b = shape // 10000, (shape // 100) % 100, shape % 100
     if kind == 7:

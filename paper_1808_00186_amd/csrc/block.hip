@@ -192,14 +192,11 @@ __device__ __forceinline__ void step_beta(ColState& S, double2 rz, double r2) {
     } else if (plateau_now(S, r2)) {
         S.active = 0;
         S.stalled += 1;
-    } else if (wander_now(S, r2)) {
-        S.active = 0;
-        S.stalled += 1;
     } else if (czero(S.rho)) {
         S.active = 0;
         S.breakdown = 1;
     } else {
-        S.beta = cdiv(rz, S.rho);
+        S.beta = wander_now(S, r2) ? make_double2(0.0, 0.0) : cdiv(rz, S.rho);
         S.rho = rz;
     }
 }
@@ -226,7 +223,7 @@ __device__ void apply_red(ColState& S, int mode, int first, double2 a, double2 b
         S.rn2_0 = mode == RED_INIT_REL ? b.x : 1.0;   // else normalised: |r| = 1
         S.rn2_best = b.x;
         S.k_best = 0;
-        S.k_mark = 0;
+        S.k_mark = S.k_start = S.restarts = S.n_mark = 0;
         S.kin = 0;
         S.beta = make_double2(0.0, 0.0);
         S.active = S.outer && cfinite(a) && !czero(a);
@@ -2307,7 +2304,7 @@ __global__ void k_init_state(ColState* st, int nsc, double inner_rtol, int sqmr)
     S.kin = 0;
     S.stepped = 0;
     S.k_best = 0;
-    S.k_mark = 0;
+    S.k_mark = S.k_start = S.restarts = S.n_mark = 0;
     S.stalled = 0;
     S.tau2 = 0.0;
     S.cq = 0.0;

@@ -49,6 +49,9 @@ struct ColState {
     double tmark;      // tau^2 (COCG: |r|^2) at the last halving of tau (|r|)
     int sqmr;          // this solve is SQMR
     int k_mark;        // inner iteration of tmark (COCG)
+    int k_start;       // inner iteration of the latest restart of the directions
+    int restarts;      // of them in this inner solve
+    int n_mark;        // halvings of |r| since then
 };
 
 // Stagnation guard of the inner COCG, which has no minimisation property: a
@@ -97,28 +100,40 @@ __device__ __forceinline__ bool plateau_now(const ColState& S, double r2) {
     const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;   // that one has its own rule
     return !last_step && S.kin - S.k_best >= max(kPlateauIters, S.k_best) && r2 <= 0.01 * S.rn2_0;
 }
-// A column that wanders: it has descended once, then |r| has not halved for
-// twice the iterations it had taken by its last halving (at least
-// kWanderIters). It stops, in any refinement step, at the first iterate whose
-// |r|^2 is at most kWanderRn2 of the step's start, and restarts from the true
-// residual there. The rules above miss it when the best |r| creeps down: one
-// of 96 3,032-unknown models, |r^T z| a millionth of |r|^2 at the start of its
-// third step, halved |r| last at iteration 52 and then stayed between 0.1 and
-// 9 for 19,000 iterations, with a new best every few hundred; with this rule
-// it takes 1,182 in all steps together. The slowest of 96 models takes 811 to
-// 1,212 over 41 such batches (860 to 1,232 kernel by kernel without the rule).
-// At most kWanderStops stops a column, so that one which needs the longer run
-// still gets it.
-constexpr int kWanderIters = 400, kWanderStops = 4;
-constexpr double kWanderRn2 = 0.1;
+// A column that wanders: its |r| has not halved for kWanderRate times the
+// iterations a halving took on average since the (re)start (at least
+// kWanderIters). Its directions have lost their conjugacy; it restarts in
+// place, with p = z, from the residual it has, at most kWanderStarts times an
+// inner solve. The rules above and below miss it while the best |r| creeps
+// down: one of 96 3,032-unknown models, |r^T z| a millionth of |r|^2 at the
+// start of its third step, stayed between 0.1 and 9 for 19,000 iterations. It
+// takes 905 in all with this rule, 1,182 where it stopped instead at an iterate
+// of at most 0.3, 977 where it restarted after twice its descent. On the 6.9M-unknown
+// survey (16 columns, SSOR) one block at 0.5 Hz takes 14,894 iterations without
+// the rule, 3,217 with the stop, 2,414 with this one, one at 0.25 Hz 5,172, 5,172 and
+// 3,226. Of 41 batches of small models and 7 uneven ones no other column was
+// affected.
+constexpr int kWanderIters = 200, kWanderRate = 8, kWanderStarts = 4;
+__device__ __forceinline__ bool wander_test(const ColState& S) {   // since the last halving
+    const int since = S.kin - S.k_mark;
+    return (S.n_mark > 0) | (S.restarts > 0) ? (S.restarts < kWanderStarts) &
+                                                   (since >= (S.n_mark > 0 ? kWanderIters : 2 * kWanderIters)) &
+                                                   (since * S.n_mark >= kWanderRate * (S.k_mark - S.k_start))
+                                             : false;
+}
 __device__ __forceinline__ bool wander_now(ColState& S, double r2) {
     if (r2 < 0.25 * S.tmark) {
         S.tmark = r2;
         S.k_mark = S.kin;
+        S.n_mark += 1;
         return false;
     }
-    return S.stalled < kWanderStops && r2 <= kWanderRn2 * S.rn2_0 &&
-           S.kin - S.k_mark >= max(kWanderIters, 2 * S.k_mark);
+    if (!wander_test(S)) return false;
+    S.tmark = r2;
+    S.k_mark = S.k_start = S.kin;
+    S.n_mark = 0;
+    S.restarts += 1;
+    return true;
 }
 __device__ __forceinline__ bool relaxed_now(const ColState& S, double r2) {
     const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;
@@ -154,24 +169,25 @@ __device__ __forceinline__ void fused_scalars(ColState& S, const double2* t) {
     const bool relax = last_step & (r2 <= S.inner_tol2 * S.rn2_0 / (0.3 * 0.3)) & (since >= max(kRelaxIters, kb / 2));
     const bool plateau = !last_step & (since >= max(kPlateauIters, kb)) & (r2 <= 0.01 * S.rn2_0);
     const bool mark = on & (r2 < 0.25 * S.tmark);
-    const int km = mark ? S.kin : S.k_mark;
-    const bool wander = !mark & (S.stalled < kWanderStops) & (r2 <= kWanderRn2 * S.rn2_0) &
-                        (S.kin - km >= max(kWanderIters, 2 * km));
+    const bool wander = on & !mark & wander_test(S);
     const bool zero = czero(rz);
-    const bool stop = on & (bad | conv | stall | relax | plateau | wander | zero);
+    const bool stop = on & (bad | conv | stall | relax | plateau | zero);
     const bool go = (S.active != 0) & !stop;
     const bool ok = go & cfinite(pq) & !czero(pq) & cfinite(be);
     S.rn2 = on ? r2 : S.rn2;
     S.rn2_best = best;
     S.k_best = kb;
-    S.tmark = mark ? r2 : S.tmark;
-    S.k_mark = km;
-    S.stalled += on & !bad & !conv & (stall | (!relax & (plateau | wander)));
-    S.breakdown |= (on & (bad | (!conv & !stall & !relax & !plateau & !wander & zero))) | (go & !ok);
+    S.tmark = mark | wander ? r2 : S.tmark;
+    S.k_mark = mark | wander ? S.kin : S.k_mark;
+    S.k_start = wander ? S.kin : S.k_start;
+    S.n_mark = wander ? 0 : S.n_mark + mark;
+    S.restarts += wander;
+    S.stalled += on & !bad & !conv & (stall | (!relax & plateau));
+    S.breakdown |= (on & (bad | (!conv & !stall & !relax & !plateau & zero))) | (go & !ok);
     S.rho = pick(on & !stop, rz, S.rho);
     S.active = ok;
     S.alpha = pick(ok, al, S.alpha);
-    S.beta = pick(ok, be, S.beta);
+    S.beta = pick(ok, pick(wander, make_double2(0.0, 0.0), be), S.beta);
     S.iters += ok;
     S.kin += ok;
 }
