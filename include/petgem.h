@@ -345,7 +345,8 @@ int petgem_get_dof_edges(const petgem_system* sys, int32_t* edges);
 int petgem_get_csr(const petgem_system* sys, int32_t* row_ptr, int32_t* col,
                    double* K, double* Ms, void* stream);
 /* y = A(freq) x for device complex128 vectors of length n_dof, in double
- * precision on the assembled K and M_s. */
+ * precision on the assembled K and M_s. x and y may be the same vector or
+ * overlap (x is then copied into a vector the system keeps). */
 int petgem_spmv(petgem_system* sys, double freq, const void* x_dev, void* y_dev,
                 void* stream);
 /* Host-only preprocessing (no GPU call): the interior-edge numbering and the

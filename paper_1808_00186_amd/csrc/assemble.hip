@@ -209,6 +209,14 @@ int launch_freq_prep(petgem_system* sys, double freq, hipStream_t s) {
 
 int launch_spmv(petgem_system* sys, double freq, const double2* x, double2* y, hipStream_t s) {
     const int n = sys->n_dof;
+    // a block writes y while others still read x: vectors that overlap are
+    // multiplied from a copy
+    const uintptr_t a = reinterpret_cast<uintptr_t>(x), b = reinterpret_cast<uintptr_t>(y);
+    if (a < b + sizeof(double2) * n && b < a + sizeof(double2) * n) {
+        if (!sys->xtmp) PG_TRY(dalloc(&sys->xtmp, (size_t)n));
+        PG_HIP(hipMemcpyAsync(sys->xtmp, x, sizeof(double2) * n, hipMemcpyDeviceToDevice, s));
+        x = sys->xtmp;
+    }
     hipLaunchKernelGGL(k_spmv_km, dim3(ceil_div((int64_t)n * 8, 256)), dim3(256), 0, s, n, 2.0 * kPi * freq * kMu0,
                        sys->row_ptr, sys->col, sys->K, sys->Ms, x, y);
     PG_HIP(hipGetLastError());

@@ -84,7 +84,7 @@ void release_system(petgem_system* sys) {
     sys->res[0].release();
     sys->res[1].release();
     dfree(sys->K32); dfree(sys->Ms32); dfree(sys->Ahat); dfree(sys->dvec); dfree(sys->dinv);
-    dfree(sys->Rst); dfree(sys->hot); dfree(sys->dflag);
+    dfree(sys->Rst); dfree(sys->hot); dfree(sys->dflag); dfree(sys->xtmp);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);
     sys->gw.release();
     sys->gres.release();

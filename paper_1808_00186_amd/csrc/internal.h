@@ -265,6 +265,7 @@ struct petgem_system {
     int rst_copies = 0;
     int* hot = nullptr;                   // layered background: count, then the elements with dsigma != 0
     int* dflag = nullptr;                 // device error flags
+    double2* xtmp = nullptr;              // [n] copy of the operand of a product that overlaps its result
     // voxel grid of the learned initial guess (cached at first use)
     int32_t* vox_tet = nullptr;           // [32^3] element containing each voxel centre
     int32_t* vox_dof = nullptr;           // [32^3][6]
