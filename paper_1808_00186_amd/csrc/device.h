@@ -90,16 +90,16 @@ __device__ __forceinline__ void dipole_E(const double x[3], const double src[3],
                                          double2 E[3]) {
     double d0 = x[0] - src[0], d1 = x[1] - src[1], d2 = x[2] - src[2];
     double r2 = d0 * d0 + d1 * d1 + d2 * d2;
-    double ir = rsqrt(r2), ir2 = ir * ir;
-    double kr = kappa * (r2 * ir);
+    double r = sqrt(r2);
+    double kr = kappa * r;
     double s, c;
     sincos(kr, &s, &c);
-    double a = pref * exp(-kr) * (ir2 * ir);
+    double a = pref * exp(-kr) / (r2 * r);
     double2 ph = make_double2(a * c, a * s);
     // A = 3 + 3 kr - i (3 kr + 2 kr^2);  B = -(1 + kr) + i (kr + 2 kr^2)
     double2 A = make_double2(3.0 + 3.0 * kr, -(3.0 * kr + 2.0 * kr * kr));
     double2 B = make_double2(-(1.0 + kr), kr + 2.0 * kr * kr);
-    double dp = (d0 * p[0] + d1 * p[1] + d2 * p[2]) * ir2;
+    double dp = (d0 * p[0] + d1 * p[1] + d2 * p[2]) / r2;
     double2 Ad = cmul(ph, cscale(A, dp));
     double2 Bp = cmul(ph, B);
     E[0] = make_double2(Ad.x * d0 + Bp.x * p[0], Ad.y * d0 + Bp.y * p[0]);

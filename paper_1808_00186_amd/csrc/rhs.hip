@@ -70,9 +70,10 @@ SrcParams make_src(const petgem_source& s, double sigma_bg) {
     return p;
 }
 
-// (256, 3): 136 registers, three waves per SIMD; the four points unrolled
-// without the bound take 256 and two.
-__global__ void __launch_bounds__(256, 3)
+// 177 registers, two waves per SIMD; (256, 3) spills. Sums by vertex instead of
+// by point and rsqrt instead of sqrt and a division take 136 registers and a
+// quarter less time, but leave a larger error against exact arithmetic.
+__global__ void __launch_bounds__(256)
 k_rhs_elem(RhsJobs jobs, int ns) {
     const int c = (int)blockIdx.y % ns;
     const RhsJob& job = jobs.j[blockIdx.y / ns];
@@ -90,50 +91,41 @@ k_rhs_elem(RhsJobs jobs, int ns) {
     }
     TetGeom G;
     tet_geometry(job.xyz, job.tets[t], G);
-    // 4-point degree-2 rule: barycentric (a,b,b,b) and permutations, weights
-    // V/4. N_i = s_i l_i (lambda_a grad lambda_b - lambda_b grad lambda_a), so
-    // sum_q N_i(x_q) . E_q = s_i l_i (grad lambda_b . S_a - grad lambda_a . S_b)
-    // with S_v = sum_q lambda_v(x_q) E_q = qb sum_q E_q + (qa - qb) E_v
+    // 4-point degree-2 rule: barycentric (a,b,b,b) and permutations, weights V/4
     const double qa = 0.58541019662496845446;   // (5 + 3 sqrt 5) / 20
     const double qb = 0.13819660112501051518;   // (5 - sqrt 5) / 20
-    double xs[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) xs[k] = qb * (G.X[0][k] + G.X[1][k] + G.X[2][k] + G.X[3][k]);
-    bool singular = false;
     const SrcParams& sp = job.sp[c];
-    double2 S[4][3], sum[3];
+    double2 R[6];
 #pragma unroll
-    for (int k = 0; k < 3; ++k) sum[k] = make_double2(0.0, 0.0);
+    for (int i = 0; i < 6; ++i) R[i] = make_double2(0.0, 0.0);
+    bool singular = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        double lam[4] = {qb, qb, qb, qb};
+        lam[q] = qa;
         double x[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) x[k] = xs[k] + (qa - qb) * G.X[q][k];
-        const double d0 = x[0] - sp.pos[0], d1 = x[1] - sp.pos[1], d2 = x[2] - sp.pos[2];
+        for (int k = 0; k < 3; ++k)
+            x[k] = lam[0] * G.X[0][k] + lam[1] * G.X[1][k] + lam[2] * G.X[2][k] + lam[3] * G.X[3][k];
+        double d0 = x[0] - sp.pos[0], d1 = x[1] - sp.pos[1], d2 = x[2] - sp.pos[2];
         if (d0 * d0 + d1 * d1 + d2 * d2 <= r_min * r_min) singular = true;
-        dipole_E(x, sp.pos, sp.dir, sp.kappa, sp.pref, S[q]);
+        double2 E[3];
+        dipole_E(x, sp.pos, sp.dir, sp.kappa, sp.pref, E);
 #pragma unroll
-        for (int k = 0; k < 3; ++k) sum[k] = cadd(sum[k], S[q][k]);
+        for (int i = 0; i < 6; ++i) {
+            const int a = kE0[i], b = kE1[i];
+            double n0 = G.sl[i] * (lam[a] * G.g[b][0] - lam[b] * G.g[a][0]);
+            double n1 = G.sl[i] * (lam[a] * G.g[b][1] - lam[b] * G.g[a][1]);
+            double n2 = G.sl[i] * (lam[a] * G.g[b][2] - lam[b] * G.g[a][2]);
+            R[i].x += n0 * E[0].x + n1 * E[1].x + n2 * E[2].x;
+            R[i].y += n0 * E[0].y + n1 * E[1].y + n2 * E[2].y;
+        }
     }
-#pragma unroll
-    for (int v = 0; v < 4; ++v)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) S[v][k] = cadd(cscale(sum[k], qb), cscale(S[v][k], qa - qb));
+    if (singular) atomicOr(job.flag, 1);
     // i w mu0 dsigma (V/4) R  ->  multiply by i: (x, y) -> (-y, x)
     const double f = job.wmu[c] * ds * G.vol * 0.25;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        const int a = kE0[i], b = kE1[i];
-        double2 R = make_double2(0.0, 0.0);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            R.x += G.g[b][k] * S[a][k].x - G.g[a][k] * S[b][k].x;
-            R.y += G.g[b][k] * S[a][k].y - G.g[a][k] * S[b][k].y;
-        }
-        const double fl = f * G.sl[i];
-        Rst[((size_t)i * T + t) * ns] = make_double2(-fl * R.y, fl * R.x);
-    }
-    if (singular) atomicOr(job.flag, 1);
+    for (int i = 0; i < 6; ++i) Rst[((size_t)i * T + t) * ns] = make_double2(-f * R[i].y, f * R[i].x);
 }
 
 template <int NS>
