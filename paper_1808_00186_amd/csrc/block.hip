@@ -125,82 +125,6 @@ __device__ __forceinline__ void step_alpha(ColState& S, double2 pq) {
     }
 }
 
-// convergence test on |r|^2 and beta = rho' / rho for an active column
-// (counting the update that produced r)
-// The scalar step of SQMR (Section 5.3 names SQMR with SOR as the paper's
-// single-process solver). Its recurrence is COCG's (rho, beta as in
-// step_beta); the quasi-minimal-residual smoothing of the iterate takes, from
-// the new residual norm |r|^2 = r2, theta^2 = r2 / tau^2, c^2 = 1 / (1 +
-// theta^2) and tau^2 <- tau^2 theta^2 c^2, and the smoothed iterate is
-// x_Q = (1 - c^2) x_Q + c^2 x (written by the update kernels). tau falls
-// monotonically, so the inner solve stops once tau is within the target, or
-// once tau has not halved for as many iterations as its last halving took
-// (at least kPlateauIters). tau bounds the smoothed residual only when the
-// residuals are orthogonal; COCG's are orthogonal in the bilinear form, not
-// in the Euclidean one, and where the unsmoothed residual diverges tau still
-// falls while the smoothed residual does not (a refinement step then gains
-// nothing).
-__device__ __forceinline__ void sqmr_beta(ColState& S, double2 rz, double r2) {
-    S.iters += 1;
-    S.kin += 1;
-    S.rn2 = r2;
-    if (!isfinite(r2) || !cfinite(rz)) {
-        S.active = 0;
-        S.breakdown = 1;
-        return;
-    }
-    const double th2 = S.tau2 > 0.0 ? r2 / S.tau2 : 0.0;
-    const double c2 = 1.0 / (1.0 + th2);
-    S.tau2 = S.tau2 * th2 * c2;
-    S.cq = c2;
-    S.rn2_best = S.tau2;
-    if (S.tau2 <= S.inner_tol2 * S.rn2_0) {
-        S.active = 0;
-        return;
-    }
-    if (S.tau2 <= 0.25 * S.tmark) {
-        S.tmark = S.tau2;
-        S.k_best = S.kin;
-    } else if (S.kin - S.k_best >= max(kPlateauIters, S.k_best)) {
-        S.active = 0;
-        S.stalled += 1;
-        return;
-    }
-    if (czero(S.rho)) {
-        S.active = 0;
-        S.breakdown = 1;
-        return;
-    }
-    S.beta = cdiv(rz, S.rho);
-    S.rho = rz;
-}
-
-__device__ __forceinline__ void step_beta(ColState& S, double2 rz, double r2) {
-    S.iters += 1;
-    S.kin += 1;
-    S.rn2 = r2;
-    if (!isfinite(r2) || !cfinite(rz)) {
-        S.active = 0;
-        S.breakdown = 1;
-    } else if (r2 <= S.inner_tol2 * S.rn2_0) {
-        S.active = 0;
-    } else if (stalled_now(S, r2)) {
-        S.active = 0;
-        S.stalled += 1;
-    } else if (relaxed_now(S, r2)) {
-        S.active = 0;
-    } else if (plateau_now(S, r2)) {
-        S.active = 0;
-        S.stalled += 1;
-    } else if (czero(S.rho)) {
-        S.active = 0;
-        S.breakdown = 1;
-    } else {
-        S.beta = wander_now(S, r2) ? make_double2(0.0, 0.0) : cdiv(rz, S.rho);
-        S.rho = rz;
-    }
-}
-
 // The true residual norm rn of the current iterate is known: the outer
 // convergence test and the next refinement step's inner tolerance.
 __device__ __forceinline__ void res_step(ColState& S, double rn, int first) {
@@ -223,7 +147,9 @@ __device__ void apply_red(ColState& S, int mode, int first, double2 a, double2 b
         S.rn2_0 = mode == RED_INIT_REL ? b.x : 1.0;   // else normalised: |r| = 1
         S.rn2_best = b.x;
         S.k_best = 0;
-        S.k_mark = S.k_start = S.restarts = S.n_mark = 0;
+        S.k_mark = S.restarts = 0;
+        S.k_prev = S.iters - S.it_start;
+        S.it_start = S.iters;
         S.kin = 0;
         S.beta = make_double2(0.0, 0.0);
         S.active = S.outer && cfinite(a) && !czero(a);
@@ -2304,7 +2230,7 @@ __global__ void k_init_state(ColState* st, int nsc, double inner_rtol, int sqmr)
     S.kin = 0;
     S.stepped = 0;
     S.k_best = 0;
-    S.k_mark = S.k_start = S.restarts = S.n_mark = 0;
+    S.k_mark = S.restarts = S.it_start = S.k_prev = 0;
     S.stalled = 0;
     S.tau2 = 0.0;
     S.cq = 0.0;

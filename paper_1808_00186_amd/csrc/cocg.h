@@ -1,8 +1,10 @@
-// The state of one column of the mixed-precision COCG and its scalar step,
-// shared by the kernels of block.hip (one kernel per phase) and resident.hip
-// (the whole inner solve in one kernel).
+// The state of one column of the mixed-precision COCG, its stop rules and its
+// scalar steps, shared by the kernels of block.hip (one kernel per phase) and
+// resident.hip (the whole inner solve in one kernel). Plain arithmetic only, so
+// that a test compiles it for the host and compares the two statements of the
+// rules.
 #pragma once
-#include "device.h"
+#include "cplx.h"
 
 namespace petgem {
 
@@ -49,9 +51,9 @@ struct ColState {
     double tmark;      // tau^2 (COCG: |r|^2) at the last halving of tau (|r|)
     int sqmr;          // this solve is SQMR
     int k_mark;        // inner iteration of tmark (COCG)
-    int k_start;       // inner iteration of the latest restart of the directions
-    int restarts;      // of them in this inner solve
-    int n_mark;        // halvings of |r| since then
+    int restarts;      // of the directions in this inner solve
+    int it_start;      // iters at the start of this inner solve
+    int k_prev;        // inner iterations of the one before (0: this is the first)
 };
 
 // Stagnation guard of the inner COCG, which has no minimisation property: a
@@ -100,38 +102,34 @@ __device__ __forceinline__ bool plateau_now(const ColState& S, double r2) {
     const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;   // that one has its own rule
     return !last_step && S.kin - S.k_best >= max(kPlateauIters, S.k_best) && r2 <= 0.01 * S.rn2_0;
 }
-// A column that wanders: its |r| has not halved for kWanderRate times the
-// iterations a halving took on average since the (re)start (at least
-// kWanderIters). Its directions have lost their conjugacy; it restarts in
-// place, with p = z, from the residual it has, at most kWanderStarts times an
-// inner solve. The rules above and below miss it while the best |r| creeps
-// down: one of 96 3,032-unknown models, |r^T z| a millionth of |r|^2 at the
-// start of its third step, stayed between 0.1 and 9 for 19,000 iterations. It
-// takes 905 in all with this rule, 1,182 where it stopped instead at an iterate
-// of at most 0.3, 977 where it restarted after twice its descent. On the 6.9M-unknown
-// survey (16 columns, SSOR) one block at 0.5 Hz takes 14,894 iterations without
-// the rule, 3,217 with the stop, 2,414 with this one, one at 0.25 Hz 5,172, 5,172 and
-// 3,226. Of 41 batches of small models and 7 uneven ones no other column was
-// affected.
-constexpr int kWanderIters = 200, kWanderRate = 8, kWanderStarts = 4;
+// A column that wanders: its |r| has not halved for as many iterations as the
+// whole refinement step before took (at least kWanderIters). Its directions
+// have lost their conjugacy; it restarts in place, with p = z, from the residual
+// it has, at most kWanderStarts times an inner solve. The rules above and below
+// miss it while the best |r| creeps down: one of 96 3,032-unknown models, |r^T z|
+// a millionth of |r|^2 at the start of its third step, stayed between 0.1 and 9 for
+// 19,000 iterations.
+// The measure is the step before because a column that converges has long
+// plateaus too, the longer the larger the mesh and the lower the frequency: over
+// 180 inner solves of 3,000 to 80,000 unknowns at 0.25 to 1.3 Hz (a mirror of this
+// recurrence) the longest one was 465 iterations, and at most 0.47 of the step
+// before; a wandering one went 22 of them. (Eight times the average
+// halving so far, at least 200, fired on 21 of the 180 and made their columns up to
+// 29 % slower, 172 columns by 2 %, where this changes none of them.) The first step
+// has no measure and keeps to the stagnation guard.
+constexpr int kWanderIters = 200, kWanderStarts = 4;
 __device__ __forceinline__ bool wander_test(const ColState& S) {   // since the last halving
-    const int since = S.kin - S.k_mark;
-    return (S.n_mark > 0) | (S.restarts > 0) ? (S.restarts < kWanderStarts) &
-                                                   (since >= (S.n_mark > 0 ? kWanderIters : 2 * kWanderIters)) &
-                                                   (since * S.n_mark >= kWanderRate * (S.k_mark - S.k_start))
-                                             : false;
+    return (S.k_prev > 0) & (S.restarts < kWanderStarts) & (S.kin - S.k_mark >= max(kWanderIters, S.k_prev));
 }
 __device__ __forceinline__ bool wander_now(ColState& S, double r2) {
     if (r2 < 0.25 * S.tmark) {
         S.tmark = r2;
         S.k_mark = S.kin;
-        S.n_mark += 1;
         return false;
     }
     if (!wander_test(S)) return false;
     S.tmark = r2;
-    S.k_mark = S.k_start = S.kin;
-    S.n_mark = 0;
+    S.k_mark = S.kin;
     S.restarts += 1;
     return true;
 }
@@ -139,6 +137,82 @@ __device__ __forceinline__ bool relaxed_now(const ColState& S, double r2) {
     const bool last_step = S.inner_tol2 > S.inner_rtol * S.inner_rtol;
     return last_step && r2 <= S.inner_tol2 * S.rn2_0 / (0.3 * 0.3) &&
            S.kin - S.k_best >= max(kRelaxIters, S.k_best / 2);
+}
+
+// The scalar step of SQMR (Section 5.3 names SQMR with SOR as the paper's
+// single-process solver). Its recurrence is COCG's (rho, beta as in
+// step_beta); the quasi-minimal-residual smoothing of the iterate takes, from
+// the new residual norm |r|^2 = r2, theta^2 = r2 / tau^2, c^2 = 1 / (1 +
+// theta^2) and tau^2 <- tau^2 theta^2 c^2, and the smoothed iterate is
+// x_Q = (1 - c^2) x_Q + c^2 x (written by the update kernels). tau falls
+// monotonically, so the inner solve stops once tau is within the target, or
+// once tau has not halved for as many iterations as its last halving took
+// (at least kPlateauIters). tau bounds the smoothed residual only when the
+// residuals are orthogonal; COCG's are orthogonal in the bilinear form, not
+// in the Euclidean one, and where the unsmoothed residual diverges tau still
+// falls while the smoothed residual does not (a refinement step then gains
+// nothing).
+__device__ __forceinline__ void sqmr_beta(ColState& S, double2 rz, double r2) {
+    S.iters += 1;
+    S.kin += 1;
+    S.rn2 = r2;
+    if (!isfinite(r2) || !cfinite(rz)) {
+        S.active = 0;
+        S.breakdown = 1;
+        return;
+    }
+    const double th2 = S.tau2 > 0.0 ? r2 / S.tau2 : 0.0;
+    const double c2 = 1.0 / (1.0 + th2);
+    S.tau2 = S.tau2 * th2 * c2;
+    S.cq = c2;
+    S.rn2_best = S.tau2;
+    if (S.tau2 <= S.inner_tol2 * S.rn2_0) {
+        S.active = 0;
+        return;
+    }
+    if (S.tau2 <= 0.25 * S.tmark) {
+        S.tmark = S.tau2;
+        S.k_best = S.kin;
+    } else if (S.kin - S.k_best >= max(kPlateauIters, S.k_best)) {
+        S.active = 0;
+        S.stalled += 1;
+        return;
+    }
+    if (czero(S.rho)) {
+        S.active = 0;
+        S.breakdown = 1;
+        return;
+    }
+    S.beta = cdiv(rz, S.rho);
+    S.rho = rz;
+}
+
+// convergence test on |r|^2 and beta = rho' / rho for an active column
+// (counting the update that produced r)
+__device__ __forceinline__ void step_beta(ColState& S, double2 rz, double r2) {
+    S.iters += 1;
+    S.kin += 1;
+    S.rn2 = r2;
+    if (!isfinite(r2) || !cfinite(rz)) {
+        S.active = 0;
+        S.breakdown = 1;
+    } else if (r2 <= S.inner_tol2 * S.rn2_0) {
+        S.active = 0;
+    } else if (stalled_now(S, r2)) {
+        S.active = 0;
+        S.stalled += 1;
+    } else if (relaxed_now(S, r2)) {
+        S.active = 0;
+    } else if (plateau_now(S, r2)) {
+        S.active = 0;
+        S.stalled += 1;
+    } else if (czero(S.rho)) {
+        S.active = 0;
+        S.breakdown = 1;
+    } else {
+        S.beta = wander_now(S, r2) ? make_double2(0.0, 0.0) : cdiv(rz, S.rho);
+        S.rho = rz;
+    }
 }
 
 // The scalar step of the fused step for one column, from the five sums t:
@@ -168,10 +242,10 @@ __device__ __forceinline__ void fused_scalars(ColState& S, const double2* t) {
     const bool stall = !better & (since > 2 * kb + kStallIters);
     const bool relax = last_step & (r2 <= S.inner_tol2 * S.rn2_0 / (0.3 * 0.3)) & (since >= max(kRelaxIters, kb / 2));
     const bool plateau = !last_step & (since >= max(kPlateauIters, kb)) & (r2 <= 0.01 * S.rn2_0);
-    const bool mark = on & (r2 < 0.25 * S.tmark);
-    const bool wander = on & !mark & wander_test(S);
     const bool zero = czero(rz);
     const bool stop = on & (bad | conv | stall | relax | plateau | zero);
+    const bool mark = on & !stop & (r2 < 0.25 * S.tmark);
+    const bool wander = on & !stop & !mark & wander_test(S);
     const bool go = (S.active != 0) & !stop;
     const bool ok = go & cfinite(pq) & !czero(pq) & cfinite(be);
     S.rn2 = on ? r2 : S.rn2;
@@ -179,8 +253,6 @@ __device__ __forceinline__ void fused_scalars(ColState& S, const double2* t) {
     S.k_best = kb;
     S.tmark = mark | wander ? r2 : S.tmark;
     S.k_mark = mark | wander ? S.kin : S.k_mark;
-    S.k_start = wander ? S.kin : S.k_start;
-    S.n_mark = wander ? 0 : S.n_mark + mark;
     S.restarts += wander;
     S.stalled += on & !bad & !conv & (stall | (!relax & plateau));
     S.breakdown |= (on & (bad | (!conv & !stall & !relax & !plateau & zero))) | (go & !ok);

@@ -1,29 +1,11 @@
-// Device-side helpers for the gfx950 kernels: complex arithmetic on
-// double2/float2, the XCD-aware block remap, wavefront reductions and the
-// whole-space dipole field.
+// Device-side helpers for the gfx950 kernels: the XCD-aware block remap,
+// wavefront reductions and the whole-space dipole field.
 #pragma once
-#include <hip/hip_runtime.h>
+#include "cplx.h"
 
 namespace petgem {
 
 constexpr int kWave = 64;
-
-__device__ __forceinline__ double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
-__device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// conj(a) * b
-__device__ __forceinline__ double2 cmulc(double2 a, double2 b) {
-    return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
-}
-__device__ __forceinline__ double2 cscale(double2 a, double s) { return make_double2(a.x * s, a.y * s); }
-__device__ __forceinline__ double cabs2(double2 a) { return a.x * a.x + a.y * a.y; }
-__device__ __forceinline__ double2 cdiv(double2 a, double2 b) {
-    double d = 1.0 / (b.x * b.x + b.y * b.y);
-    return make_double2((a.x * b.x + a.y * b.y) * d, (a.y * b.x - a.x * b.y) * d);
-}
-__device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
 
 // Workgroups are dispatched round-robin over the 8 XCDs (block b runs on XCD
 // b % 8). Remap so that each XCD works on one contiguous range of logical

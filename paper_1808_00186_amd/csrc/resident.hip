@@ -519,7 +519,9 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
                     S.rho = sums[3];
                     S.rn2 = S.rn2_best = S.tau2 = S.tmark = sums[4].x;
                     S.rn2_0 = 1.0;
-                    S.k_best = S.k_mark = S.k_start = S.restarts = S.n_mark = S.kin = 0;
+                    S.k_best = S.k_mark = S.restarts = S.kin = 0;
+                    S.k_prev = S.iters - S.it_start;
+                    S.it_start = S.iters;
                     S.beta = make_double2(0.0, 0.0);
                     S.active = S.outer && cfinite(sums[3]) && !czero(sums[3]);
                     S.breakdown = S.stepped = 0;
