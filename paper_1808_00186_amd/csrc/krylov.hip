@@ -11,8 +11,9 @@
 //   k_update v_{j+1} = (w - sum_k h_k v_k) / beta
 // Classical Gram-Schmidt with the norm from Pythagoras costs one pass over
 // the basis for the dots and one for the update; when cancellation makes the
-// Pythagorean norm unreliable (beta^2 <= eta |w|^2) the step requests a
-// second Gram-Schmidt pass, whose kernels otherwise exit at once. All
+// Pythagorean norm unreliable (beta^2 <= eta |w|^2), or the cycle has brought
+// its residual down by 1e6, the step requests a second Gram-Schmidt pass, whose
+// kernels otherwise exit at once. All
 // reductions use a fixed partition and order, so the solve is bitwise
 // reproducible. A mesh whose rows fit the resident layout runs the same steps
 // in one launch (k_gm_solve in resident.hip); the kernels here serve larger
@@ -39,7 +40,6 @@ namespace {
 
 constexpr int kDotMaxBlocks = 1024;
 constexpr int kChunk = 16;        // coefficients accumulated per pass of k_mdot
-constexpr double kEta = 1e-2;     // re-orthogonalise when beta^2 <= eta |w|^2
 
 // y = Ahat x, or y = b - Ahat x when RES. G lanes cooperate on one row.
 template <int G, bool RES>
@@ -224,7 +224,8 @@ k_fin(int j, int nb, const double2* __restrict__ partial, GmresCtl* __restrict__
         if (!isfinite(nrm2) || !isfinite(hh)) {
             c->nonfinite = 1;
             c->done = 1;
-        } else if (pass == 0 && nrm2 - hh <= kEta * nrm2) {   // cancellation: second pass
+        } else if (pass == 0 && (nrm2 - hh <= kGmEta * nrm2 ||
+                                 cabs2(c->g[j]) <= kGmDrop * kGmDrop * c->rnorm * c->rnorm)) {   // second pass
             c->reorth = 1;
             c->scale = 1.0;
             accept = 2;   // store the unrotated column for the second pass

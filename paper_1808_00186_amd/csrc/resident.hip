@@ -585,7 +585,7 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
 // through its caches; v_j with its halo, w and the iterate are in LDS.
 //   step j: w = Ahat v_j; c_k = v_k^H w, |w|^2 (one exchange of 2 j + 3
 //   doubles); v_{j+1} = (w - sum c_k v_k) / beta with beta by Pythagoras,
-//   after a second pass where cancellation makes that unreliable; one thread
+//   after a second pass where that is unreliable (kGmEta, kGmDrop); one thread
 //   of every workgroup runs the Givens recurrence while v_{j+1} travels.
 // A solve to 1e-12 of 3k unknowns took 12.6 ms with the kernels and takes 5.5
 // (11.7 us a step); of 434k unknowns 108 and 77 ms, 70 us a step, in which the
@@ -593,7 +593,6 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
 constexpr int kGmMax = 31;                    // longest restart: 2 m + 1 sums in 64
 constexpr int kGmVals = 64;
 constexpr int kGmArea = kGmVals * 32 + 32;    // words from one area to the next
-constexpr double kGmEta = 1e-2;               // second pass when beta^2 <= eta |w|^2
 
 struct GmArgs {
     int G, n, rw, rwcap, hcap, hmax, m, max_iter;
@@ -929,7 +928,8 @@ k_gm_solve(GmArgs a) {
                         if (!isfinite(nrm2) || !isfinite(hh)) {
                             nonfinite = 1;
                             action = 0;
-                        } else if (pass == 0 && b2 <= kGmEta * nrm2) {
+                        } else if (pass == 0 && (b2 <= kGmEta * nrm2 ||
+                                                 cabs2(gv[j]) <= kGmDrop * kGmDrop * rnorm_s * rnorm_s)) {
                             action = 2;
                             scale_s = 1.0;
                         } else {
