@@ -119,12 +119,13 @@ struct Resident {
     int state = 0;                // 0 not built, 1 usable, -1 the mesh does not fit
     int G = 0, rw = 0, rwcap = 0; // workgroups; rows of each; their LDS slots
     int hcap = 0, hmax = 0;       // most outer neighbours of a workgroup; stride of halo
+    char* pattern = nullptr;      // one allocation that holds the next five
     int32_t* rows = nullptr;      // [G][rwcap] matrix row of each slot (-1: none)
     int32_t* wend = nullptr;      // [G][8][4] chunks of a wave's row slots, cumulative
     int32_t* halo = nullptr;      // [G][hmax] exchange place of each outer neighbour
     int32_t* nh = nullptr;        // [G]
     uint64_t* idx = nullptr;      // [G][8][chunks][64] four LDS indices
-    float* K = nullptr;           // [G][8][chunks][64][4] (built when the COCG first needs them)
+    float* K = nullptr;           // [G][8][chunks][64][4], then M (built when the COCG first needs them)
     float* M = nullptr;
     bool values = false;          // K, M current
     double2* A = nullptr;         // [G][8][chunks][4][64] A D^-1 of the plain GMRES at a_freq

@@ -138,16 +138,33 @@ __device__ __forceinline__ bool wait_words(const u64* const* a, const int* abort
 }
 
 // ------------------------------------------------------------ the layout
+// One layout to build; its G workgroups are blocks block0 .. of both kernels,
+// so the layouts of a whole batch are two launches (one at a time, 200 small
+// meshes took 20 ms: eight workgroups do not fill the chip).
+struct ResLay {
+    int block0, n, rw, rwcap, hmax;
+    const int32_t *rp, *col;
+    int32_t *rows, *wend, *halo, *nh, *pos;
+    uint2* idx;
+    int* stat;
+};
+
 // Workgroup g takes rows [g rw, g rw + rw), ordered by length (longest first,
 // then by index). wend[g][wave][k]: the chunk at which the wave's row slot k
 // ends. stat[0]: most chunks of a wave.
 __global__ void __launch_bounds__(1024)
-k_res_sort(int n, int rw, int rwcap, const int32_t* __restrict__ rp, int32_t* __restrict__ rows,
-           int32_t* __restrict__ wend, int32_t* __restrict__ pos, int* __restrict__ stat) {
+k_res_sort(const ResLay* __restrict__ lays, const int* __restrict__ blk) {
+    const ResLay& y = lays[blk[blockIdx.x]];
+    const int n = y.n, rw = y.rw, rwcap = y.rwcap;
+    const int32_t* __restrict__ rp = y.rp;
+    int32_t* __restrict__ rows = y.rows;
+    int32_t* __restrict__ wend = y.wend;
+    int32_t* __restrict__ pos = y.pos;
+    int* __restrict__ stat = y.stat;
     // lengths as 16 bits, eight to a read: the ranks of 1,516 rows in 20 us, not 86
     __shared__ __align__(16) uint16_t len[kResRows];
     __shared__ int slen[kResRows];
-    const int g = blockIdx.x, r0 = g * rw, R = min(n - r0, rw), t = threadIdx.x;
+    const int g = (int)blockIdx.x - y.block0, r0 = g * rw, R = min(n - r0, rw), t = threadIdx.x;
     for (int i = t; i < kResRows; i += 1024) len[i] = i < R ? (uint16_t)min(rp[r0 + i + 1] - rp[r0 + i], 0xffff) : 0;
     for (int s = R + t; s < rwcap; s += 1024) rows[(size_t)g * rwcap + s] = -1;
     __syncthreads();
@@ -184,15 +201,20 @@ k_res_sort(int n, int rw, int rwcap, const int32_t* __restrict__ rp, int32_t* __
 // entry (8 bytes a row: own rows first, then the halo from rwcap on). A bitmap of all rows
 // finds the distinct columns. stat[1]: most halo rows of a workgroup.
 __global__ void __launch_bounds__(1024)
-k_res_halo(int n, int rw, int rwcap, int hmax, const int32_t* __restrict__ rp, const int32_t* __restrict__ col,
-           const int32_t* __restrict__ rows, const int32_t* __restrict__ wend, const int32_t* __restrict__ pos,
-           int32_t* __restrict__ halo, int32_t* __restrict__ nh, uint2* __restrict__ idx, int* __restrict__ stat) {
+k_res_halo(const ResLay* __restrict__ lays, const int* __restrict__ blk) {
+    const ResLay& y = lays[blk[blockIdx.x]];
+    const int n = y.n, rw = y.rw, rwcap = y.rwcap, hmax = y.hmax;
+    const int32_t *__restrict__ rp = y.rp, *__restrict__ col = y.col;
+    const int32_t *__restrict__ rows = y.rows, *__restrict__ wend = y.wend, *__restrict__ pos = y.pos;
+    int32_t *__restrict__ halo = y.halo, *__restrict__ nh = y.nh;
+    uint2* __restrict__ idx = y.idx;
+    int* __restrict__ stat = y.stat;
     extern __shared__ unsigned lds_u[];
     __shared__ int scan[1024];
     const int nw = (n + 31) / 32, t = threadIdx.x;
     unsigned* bm = lds_u;
     unsigned* pre = lds_u + nw;
-    const int g = blockIdx.x, r0 = g * rw, R = min(n - r0, rw);
+    const int g = (int)blockIdx.x - y.block0, r0 = g * rw, R = min(n - r0, rw);
     for (int i = t; i < nw; i += 1024) bm[i] = 0u;
     __syncthreads();
     const int e0 = rp[r0], e1 = rp[r0 + R];
@@ -1083,8 +1105,10 @@ k_gm_solve(GmArgs a) {
 
 // ------------------------------------------------------------ host side
 void Resident::release() {
-    dfree(rows); dfree(wend); dfree(halo); dfree(nh);
-    dfree(idx); dfree(K); dfree(M); dfree(A);
+    dfree(pattern); dfree(K); dfree(A);
+    rows = wend = halo = nh = nullptr;
+    idx = nullptr;
+    M = nullptr;
     a_freq = -1.0;
     G = 0;
     state = 0;
@@ -1113,55 +1137,119 @@ int res_rows(int n, int target, int ncu) {
     return rw <= kResRows ? rw : 0;
 }
 
-// Builds the layout of a mesh for rw rows per workgroup (once; the pattern
-// does not change). state: 1 usable, -1 the mesh does not fit.
-int res_build(petgem_system* sys, Resident& L, int rw, hipStream_t s) {
-    if (L.state != 0 && L.rw == rw) return PETGEM_OK;
-    L.release();
-    L.rw = rw;
-    L.state = -1;
-    const int n = sys->n_dof;
-    if (rw == 0) return PETGEM_OK;
-    L.rwcap = rw;
-    L.G = ceil_div(n, rw);
-    const int hmax = std::min((kResLds - 48 * rw) / 12, 65536 / 8 - rw) / 64 * 64;
-    const size_t ent = (size_t)L.G * kResW * kResCh * 64;
-    int32_t* pos = nullptr;
-    int* stat = nullptr;
+// Parts of one device allocation, each at a multiple of 256 bytes; with a null
+// base it only adds up the size.
+struct Carve {
+    char* base = nullptr;
+    size_t size = 0;
+    template <class T>
+    T* part(size_t count) {
+        T* p = base ? reinterpret_cast<T*>(base + size) : nullptr;
+        size += (count * sizeof(T) + 255) / 256 * 256;
+        return p;
+    }
+};
+
+// A layout and the split it is wanted for.
+struct ResWant {
+    petgem_system* sys;
+    Resident* L;
+    int rw;                       // rows per workgroup
+};
+
+// Builds the layouts that are not there yet (once per mesh and split; the
+// pattern does not change). state: 1 usable, -1 the mesh does not fit. All of
+// them together take two launches, a temporary allocation and a readback, and each
+// an allocation: with two launches, ten allocations, two copies and a wait for each
+// the first solve of a batch of 200 small meshes took 76 ms, with these 37
+// (kernel by kernel 49; 11 once the layouts are there).
+int res_build(const std::vector<ResWant>& want, hipStream_t s) {
+    std::vector<ResWant> todo;
+    for (const ResWant& w : want) {
+        if (w.L->state != 0 && w.L->rw == w.rw) continue;   // (a mesh named twice: 2, set below)
+        w.L->release();
+        w.L->rw = w.rw;
+        w.L->state = w.rw == 0 ? -1 : 2;
+        if (w.rw != 0) todo.push_back(w);
+    }
+    if (todo.empty()) return PETGEM_OK;
+    const size_t nt = todo.size();
+    char* tmp = nullptr;
+    std::vector<int> got(2 * nt, 0);
+    auto hmax_of = [](int rw) { return std::min((kResLds - 48 * rw) / 12, 65536 / 8 - rw) / 64 * 64; };
     auto go = [&]() -> int {
-        PG_TRY(dalloc(&pos, (size_t)n));
-        PG_TRY(dalloc(&stat, 2));
-        PG_TRY(dalloc(&L.rows, (size_t)L.G * rw));
-        PG_TRY(dalloc(&L.wend, (size_t)L.G * kResW * kResK));
-        PG_TRY(dalloc(&L.halo, (size_t)L.G * hmax));
-        PG_TRY(dalloc(&L.nh, (size_t)L.G));
-        PG_TRY(dalloc(&L.idx, ent));
-        const int zero[2] = {0, 0};
-        int got[2] = {0, 0};
-        PG_HIP(hipMemcpyAsync(stat, zero, sizeof(zero), hipMemcpyHostToDevice, s));
-        hipLaunchKernelGGL(k_res_sort, dim3(L.G), dim3(1024), 0, s, n, rw, rw, sys->row_ptr, L.rows, L.wend, pos, stat);
-        const size_t lds = (size_t)2 * ceil_div(n, 32) * sizeof(unsigned);
+        std::vector<ResLay> lays(nt);
+        std::vector<int> blk;
+        size_t rows = 0;
+        int most = 0;
+        for (size_t k = 0; k < nt; ++k) {
+            petgem_system* sys = todo[k].sys;
+            Resident& L = *todo[k].L;
+            const int n = sys->n_dof, rw = L.rw, hmax = hmax_of(rw);
+            L.rwcap = rw;
+            L.G = ceil_div(n, rw);
+            auto parts = [&](Carve& p) {
+                L.rows = p.part<int32_t>((size_t)L.G * rw);
+                L.wend = p.part<int32_t>((size_t)L.G * kResW * kResK);
+                L.halo = p.part<int32_t>((size_t)L.G * hmax);
+                L.nh = p.part<int32_t>((size_t)L.G);
+                L.idx = p.part<uint64_t>((size_t)L.G * kResW * kResCh * 64);
+            };
+            Carve need;
+            parts(need);
+            PG_TRY(dalloc(&L.pattern, need.size));
+            Carve have{L.pattern};
+            parts(have);
+            lays[k] = ResLay{(int)blk.size(), n, rw, rw, hmax, sys->row_ptr, sys->col, L.rows, L.wend, L.halo, L.nh,
+                             nullptr, reinterpret_cast<uint2*>(L.idx), nullptr};
+            blk.insert(blk.end(), (size_t)L.G, (int)k);
+            rows += (size_t)n;
+            most = std::max(most, n);
+        }
+        int *pos = nullptr, *stat = nullptr, *blk_d = nullptr;
+        ResLay* lays_d = nullptr;
+        auto parts = [&](Carve& p) {
+            pos = p.part<int>(rows);
+            stat = p.part<int>(2 * nt);
+            blk_d = p.part<int>(blk.size());
+            lays_d = p.part<ResLay>(nt);
+        };
+        Carve need;
+        parts(need);
+        PG_TRY(dalloc(&tmp, need.size));
+        Carve have{tmp};
+        parts(have);
+        for (size_t k = 0, r = 0; k < nt; r += (size_t)lays[k].n, ++k) {
+            lays[k].pos = pos + r;
+            lays[k].stat = stat + 2 * k;
+        }
+        PG_HIP(hipMemcpyAsync(stat, got.data(), sizeof(int) * got.size(), hipMemcpyHostToDevice, s));
+        PG_HIP(hipMemcpyAsync(blk_d, blk.data(), sizeof(int) * blk.size(), hipMemcpyHostToDevice, s));
+        PG_HIP(hipMemcpyAsync(lays_d, lays.data(), sizeof(ResLay) * nt, hipMemcpyHostToDevice, s));
+        hipLaunchKernelGGL(k_res_sort, dim3(blk.size()), dim3(1024), 0, s, lays_d, blk_d);
+        const size_t lds = (size_t)2 * ceil_div(most, 32) * sizeof(unsigned);
         PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_halo),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        hipLaunchKernelGGL(k_res_halo, dim3(L.G), dim3(1024), lds, s, n, rw, rw, hmax, sys->row_ptr, sys->col,
-                           L.rows, L.wend, pos, L.halo, L.nh, reinterpret_cast<uint2*>(L.idx), stat);
+        hipLaunchKernelGGL(k_res_halo, dim3(blk.size()), dim3(1024), lds, s, lays_d, blk_d);
         PG_HIP(hipGetLastError());
-        PG_HIP(hipMemcpyAsync(got, stat, sizeof(got), hipMemcpyDeviceToHost, s));
+        PG_HIP(hipMemcpyAsync(got.data(), stat, sizeof(int) * got.size(), hipMemcpyDeviceToHost, s));
         PG_HIP(hipStreamSynchronize(s));
-        if (got[0] > kResCh || got[1] > hmax) return PETGEM_OK;   // too many entries or outer neighbours
-        L.hmax = hmax;
-        L.hcap = (got[1] + 63) / 64 * 64;
-        L.state = 1;
         return PETGEM_OK;
     };
     const int rc = go();
-    dfree(pos);
-    dfree(stat);
-    if (L.state != 1) {
-        const int st = rc == PETGEM_OK ? -1 : 0;
-        L.release();
-        L.rw = rw;
-        L.state = st;
+    dfree(tmp);
+    for (size_t k = 0; k < nt; ++k) {
+        Resident& L = *todo[k].L;
+        const int rw = L.rw, hmax = hmax_of(rw);
+        if (rc == PETGEM_OK && got[2 * k] <= kResCh && got[2 * k + 1] <= hmax) {
+            L.hmax = hmax;
+            L.hcap = (got[2 * k + 1] + 63) / 64 * 64;
+            L.state = 1;
+        } else {   // too many entries or outer neighbours; or an error, and it may be tried again
+            L.release();
+            L.rw = rw;
+            L.state = rc == PETGEM_OK ? -1 : 0;
+        }
     }
     return rc;
 }
@@ -1188,16 +1276,21 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
     }
     const int which = fine <= ncu ? 0 : 1;
     std::vector<Resident*> L(items.size());
-    bool stale = false;
+    std::vector<ResWant> want(items.size());
     for (size_t k = 0; k < items.size(); ++k) {
         petgem_system* sys = items[k].sys;
         L[k] = &sys->res[which];
-        PG_TRY(res_build(sys, *L[k], res_rows(sys->n_dof, which ? kResCoarse : kResFine, ncu), s));
-        if (L[k]->state != 1) return PETGEM_OK;
-        const size_t ent = (size_t)L[k]->G * kResW * kResCh * 64;
-        if (!L[k]->K) PG_TRY(dalloc(&L[k]->K, 4 * ent));
-        if (!L[k]->M) PG_TRY(dalloc(&L[k]->M, 4 * ent));
-        stale = stale || !L[k]->values;
+        want[k] = ResWant{sys, L[k], res_rows(sys->n_dof, which ? kResCoarse : kResFine, ncu)};
+    }
+    PG_TRY(res_build(want, s));
+    for (const Resident* l : L)
+        if (l->state != 1) return PETGEM_OK;
+    bool stale = false;
+    for (Resident* l : L) {
+        const size_t ent = (size_t)l->G * kResW * kResCh * 64;
+        if (!l->K) PG_TRY(dalloc(&l->K, 8 * ent));
+        l->M = l->K + 4 * ent;
+        stale = stale || !l->values;
     }
     // rounds of domains that are resident together, the largest first
     std::vector<size_t> order(items.size());
@@ -1317,7 +1410,7 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
     if (!coop) return PETGEM_OK;
     const int n = sys->n_dof, which = ceil_div(n, kResFine) <= ncu ? 0 : 1;
     Resident& L = sys->res[which];
-    PG_TRY(res_build(sys, L, res_rows(n, which ? kResCoarse : kResFine, ncu), s));
+    PG_TRY(res_build({ResWant{sys, &L, res_rows(n, which ? kResCoarse : kResFine, ncu)}}, s));
     if (L.state != 1) return PETGEM_OK;
     const size_t lds = (size_t)16 * (L.rwcap + L.hcap) + (size_t)32 * L.rwcap + (size_t)16 * restart * (restart + 1) +
                        (size_t)4 * L.hcap;

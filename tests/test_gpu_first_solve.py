@@ -1,0 +1,44 @@
+"""The first solve of a batch of new meshes. Marked `gpu`.
+
+The layouts of the one-launch form are built in it. Beside what the
+kernel-by-kernel form does in its own first solve (its operator copy, without a
+tuning here) they must not cost more than that form's iterations take longer:
+the batch's first solve is to take no longer than by kernels. Each form gets new systems
+every time; the least of three times of each is compared.
+"""
+import time
+
+import numpy as np
+import pytest
+
+from paper_1808_00186_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def test_first_solve_of_many_new_meshes(capsys):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1808_00186_amd import petgem as pg
+    models = []
+    for k in range(200):
+        xyz, tets = synth.kuhn_mesh(12, -5000.0, 5000.0, 100 + k)
+        sig = synth.marine_sigma(synth.centroids(xyz, tets), ((-2000, 2000), (-2000, 2000), (-1500, -1300)), 0.02)
+        models.append(synth.Model("first", xyz, tets, sig, 3.3, [synth.Dipole((30.0, 0.0, 50.0), 1.0)],
+                                  np.zeros((1, 3)), 12, (-5000.0, 5000.0)))
+    srcs = [m.sources[0] for m in models]
+    print("[case] first solve of 200 meshes", flush=True)
+
+    def first(**kw):
+        systems = [pg.System.from_model(m) for m in models]
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        _, st, rc = pg.solve_many(systems, srcs, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=1e-10, **kw))
+        torch.cuda.synchronize()
+        assert rc == pg.OK
+        return time.perf_counter() - t0
+    first()
+    one, kernels = min(first() for _ in range(3)), min(first(spmm_shape=50104) for _ in range(3))
+    print(f"  {1e3 * one:.1f} ms, by kernels {1e3 * kernels:.1f} ms", flush=True)
+    assert one <= kernels
