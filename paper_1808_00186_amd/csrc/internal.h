@@ -18,11 +18,13 @@ constexpr int kMaxRestart = 64;
 // GMRES, both forms: an Arnoldi step takes a second Gram-Schmidt pass when
 // beta^2 <= kGmEta |w|^2 (cancellation), and once the cycle has brought its residual
 // down by kGmDrop. One pass loses orthogonality as 1e-16 times the square of
-// that reduction; beyond 1e6 the estimate of the residual no longer follows it. On 26
-// unknowns to 1e-9 in one cycle six roundings of b took 17 to 27 steps with the
-// first rule alone, 17 each with both; a cycle of a larger mesh brings its
-// residual down by 1e1 to 1e3, and its steps are the same.
-constexpr double kGmEta = 1e-2, kGmDrop = 1e-6;
+// that reduction; beyond 1e7 (a loss of 1e-2) the estimate of the residual no longer
+// follows it. Steps of six roundings of b, with the first rule alone and with both
+// (in a mirror): 26 unknowns to 1e-9 in one cycle 17 to 27, and 17; 3,000 to 1e-8 with
+// restart 60 53 to 59, and 52; 600 to 1e-12 with restart 64 64 to 159, and 44. 1e-6
+// takes the same steps and more second passes, 3e-8 leaves them uneven. A cycle of a
+// larger mesh brings its residual down by 1e1 to 1e3, and its steps are as before.
+constexpr double kGmEta = 1e-2, kGmDrop = 1e-7;
 
 void set_error(const std::string& msg);
 

@@ -12,7 +12,7 @@
 // Classical Gram-Schmidt with the norm from Pythagoras costs one pass over
 // the basis for the dots and one for the update; when cancellation makes the
 // Pythagorean norm unreliable (beta^2 <= eta |w|^2), or the cycle has brought
-// its residual down by 1e6, the step requests a second Gram-Schmidt pass, whose
+// its residual down by 1e7, the step requests a second Gram-Schmidt pass, whose
 // kernels otherwise exit at once. All
 // reductions use a fixed partition and order, so the solve is bitwise
 // reproducible. A mesh whose rows fit the resident layout runs the same steps
