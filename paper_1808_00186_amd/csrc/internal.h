@@ -192,7 +192,8 @@ struct ResWork {
     int* blk = nullptr;           // domain of each logical block
     unsigned long long *words = nullptr, *pex = nullptr;
     int *abort = nullptr, *abort_h = nullptr;
-    double2* V = nullptr;         // GMRES: basis, in the layout's order
+    Resident* L = nullptr;        // GMRES: the layout of the plan
+    double2* V = nullptr;         // basis, in the layout's order
     double2 *b = nullptr, *u = nullptr;
     GmOut* out = nullptr;
     GmHost* host = nullptr;       // pinned
@@ -361,8 +362,9 @@ int ensure_fp32(petgem_system* sys, hipStream_t s);
 // it *W.abort is non-zero if a wait ran out.
 int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits);
 int res_run(ResWork& W, int max_inner, hipStream_t s);
-int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, const double2* b,
-           double2* u, GmOut* out, hipStream_t s, bool* fits);
+// The plain GMRES in one launch: room for it, then the solve of W.b into W.u, W.out
+int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits);
+int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, hipStream_t s);
 // the multicolour split of the operator (pattern built once, values gathered
 // again after every reassembly); ssor_apply: z = M^-1 r of one complex64
 // column at one frequency (device vectors of n_dof)

@@ -587,17 +587,14 @@ int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_op
     Timer t_all;
     *done = false;
     ResWork& w = sys->gres;
-    if (!w.b) PG_TRY(dalloc(&w.b, (size_t)n));
-    if (!w.u) PG_TRY(dalloc(&w.u, (size_t)n));
-    if (!w.out) PG_TRY(dalloc(&w.out, 1));
-    if (!w.host) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.host), sizeof(GmHost)));
+    bool fits = false;
+    PG_TRY(gm_plan(sys, w, o.restart, s, &fits));
+    if (!fits) return PETGEM_OK;
     PG_TRY(launch_diag(sys, src.freq_hz, s));
     Timer t_rhs;
     PG_TRY(launch_rhs(sys, &src, 1, w.b, 0, 1, s));
     const double trhs = t_rhs.ms();
-    bool fits = false;
-    PG_TRY(gm_run(sys, w, src.freq_hz, o.restart, o.max_iter, o.rtol, w.b, w.u, w.out, s, &fits));
-    if (!fits) return PETGEM_OK;
+    PG_TRY(gm_run(sys, w, src.freq_hz, o.restart, o.max_iter, o.rtol, s));
     PG_HIP(hipMemcpyAsync(&w.host->out, w.out, sizeof(GmOut), hipMemcpyDeviceToHost, s));
     PG_HIP(hipMemcpyAsync(&w.host->abort, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
     PG_HIP(hipMemcpyAsync(&w.host->flag, sys->dflag, sizeof(int), hipMemcpyDeviceToHost, s));

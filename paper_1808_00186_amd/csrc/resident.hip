@@ -1397,32 +1397,33 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
     return PETGEM_OK;
 }
 
-// The whole plain GMRES of one source from a zero guess; *fits false: the mesh
-// or the restart does not fit. D^-1 (sys->dinv) is current and b is set.
-int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, const double2* b,
-           double2* u, GmOut* out, hipStream_t s, bool* fits) {
+// Dynamic LDS of k_gm_solve; its static part and this fill a compute unit's.
+constexpr int kGmLds = 160 * 1024 - 9216;
+static size_t gm_lds(const Resident& L, int restart) {
+    return (size_t)16 * (L.rwcap + L.hcap) + (size_t)32 * L.rwcap + (size_t)16 * restart * (restart + 1) +
+           (size_t)4 * L.hcap;
+}
+
+// Lays the mesh out and makes room for the plain GMRES of one source in one
+// launch; *fits false: the mesh or the restart does not fit, and nothing was
+// done that such a solve would have to pay for.
+int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits) {
     *fits = false;
-    if (restart > kGmMax) return PETGEM_OK;
+    const int n = sys->n_dof;
     int dev = 0, ncu = 0, coop = 0;
     PG_HIP(hipGetDevice(&dev));
     PG_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
     PG_HIP(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev));
-    if (!coop) return PETGEM_OK;
-    const int n = sys->n_dof, which = ceil_div(n, kResFine) <= ncu ? 0 : 1;
+    const int which = ceil_div(n, kResFine) <= ncu ? 0 : 1, rw = res_rows(n, which ? kResCoarse : kResFine, ncu);
+    if (restart > kGmMax || !coop || rw == 0) return PETGEM_OK;
     Resident& L = sys->res[which];
-    PG_TRY(res_build({ResWant{sys, &L, res_rows(n, which ? kResCoarse : kResFine, ncu)}}, s));
-    if (L.state != 1) return PETGEM_OK;
-    const size_t lds = (size_t)16 * (L.rwcap + L.hcap) + (size_t)32 * L.rwcap + (size_t)16 * restart * (restart + 1) +
-                       (size_t)4 * L.hcap;
-    if (lds + 9216 > 160 * 1024) return PETGEM_OK;
-    const size_t ent = (size_t)L.G * kResW * kResCh * 256, ldv = (size_t)L.G * L.rwcap;
-    if (!L.A) PG_TRY(dalloc(&L.A, ent));
-    if (L.a_freq != freq) {
-        hipLaunchKernelGGL(k_gm_vals, dim3(2 * L.G), dim3(256), 0, s, n, L.rw, L.rwcap, 2.0 * kPi * freq * kMu0,
-                           sys->row_ptr, sys->col, L.rows, L.wend, sys->K, sys->Ms, sys->dinv, L.A);
-        PG_HIP(hipGetLastError());
-        L.a_freq = freq;
-    }
+    PG_TRY(res_build({ResWant{sys, &L, rw}}, s));
+    if (L.state != 1 || gm_lds(L, restart) > (size_t)kGmLds) return PETGEM_OK;
+    if (!L.A) PG_TRY(dalloc(&L.A, (size_t)L.G * kResW * kResCh * 256));
+    const size_t ldv = (size_t)L.G * L.rwcap;
+    W.L = &L;
+    W.n_words = 3 * gm_words(L.G);
+    W.n_pex = 6 * ldv;
     auto grow = [&](auto& p, size_t& cap, size_t need) -> int {
         if (cap >= need) return PETGEM_OK;
         dfree(p);
@@ -1431,12 +1432,29 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
         cap = need;
         return PETGEM_OK;
     };
-    W.n_words = 3 * gm_words(L.G);
-    W.n_pex = 6 * ldv;
     PG_TRY(grow(W.words, W.cap_words, W.n_words));
     PG_TRY(grow(W.pex, W.cap_pex, W.n_pex));
     PG_TRY(grow(W.V, W.cap_v, (size_t)(restart + 1) * ldv));
     if (!W.abort) PG_TRY(dalloc(&W.abort, 1));
+    if (!W.b) PG_TRY(dalloc(&W.b, (size_t)n));
+    if (!W.u) PG_TRY(dalloc(&W.u, (size_t)n));
+    if (!W.out) PG_TRY(dalloc(&W.out, 1));
+    if (!W.host) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.host), sizeof(GmHost)));
+    *fits = true;
+    return PETGEM_OK;
+}
+
+// The whole plain GMRES of the source whose right-hand side is in W.b, from a
+// zero guess, after gm_plan; D^-1 (sys->dinv) is current.
+int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_iter, double rtol, hipStream_t s) {
+    Resident& L = *W.L;
+    const int n = sys->n_dof;
+    if (L.a_freq != freq) {
+        hipLaunchKernelGGL(k_gm_vals, dim3(2 * L.G), dim3(256), 0, s, n, L.rw, L.rwcap, 2.0 * kPi * freq * kMu0,
+                           sys->row_ptr, sys->col, L.rows, L.wend, sys->K, sys->Ms, sys->dinv, L.A);
+        PG_HIP(hipGetLastError());
+        L.a_freq = freq;
+    }
     const size_t m = std::max(W.n_words, W.n_pex);
     hipLaunchKernelGGL(k_res_clear, dim3(ceil_div(m, 256)), dim3(256), 0, s, W.n_words, W.words, W.n_pex, W.pex,
                        W.abort);
@@ -1457,20 +1475,20 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
     a.nh = L.nh;
     a.idx = reinterpret_cast<const uint2*>(L.idx);
     a.A = L.A;
-    a.b = b;
-    a.u = u;
+    a.b = W.b;
+    a.u = W.u;
     a.V = W.V;
     a.words = W.words;
     a.pex = W.pex;
     a.abort = W.abort;
-    a.out = out;
+    a.out = W.out;
     void* args[1] = {&a};
     const void* fn = L.rw <= kResT ? reinterpret_cast<const void*>(k_gm_solve<1>)
                      : L.rw <= 2 * kResT ? reinterpret_cast<const void*>(k_gm_solve<2>)
                                          : reinterpret_cast<const void*>(k_gm_solve<4>);
+    const size_t lds = gm_lds(L, restart);
     PG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     PG_HIP(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
-    *fits = true;
     return PETGEM_OK;
 }
 
