@@ -361,6 +361,17 @@ int petgem_mesh_pattern(const petgem_mesh* mesh, int32_t* n_dof, int64_t* nnz,
  * in no element. pts host [n_pts][3], elem host [n_pts]. */
 int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, double tol,
                   int32_t* elem);
+/* Device memory that only makes a system faster: the layouts and buffers of the
+ * solves that run in one launch (about 0.4 GB for the double-precision and 0.2 GB
+ * for the mixed form of a 434,000-unknown mesh) and right-hand side staging beyond one
+ * source's. Where the device has no more of it, or beyond the limit set here
+ * (bytes; -1, the default: none), solves run kernel by kernel and right-hand
+ * sides one source at a time, with the same results to rounding. Setting it gives
+ * all such memory of the system back; it is taken again as solves need it, and a
+ * solve that finds too little of it does not ask again until the limit is set anew
+ * (a batch: of its first system). petgem_spare_bytes: what the system holds. */
+int petgem_set_spare_limit(petgem_system* sys, int64_t bytes);
+int64_t petgem_spare_bytes(const petgem_system* sys);
 /* Autotuner choices of a system: lanes per row of the double-precision CSR
  * SpMV (4, 8 or 16; 0 before the first GMRES solve) and the measured per-launch
  * times of the three variants in ms (host float [3], may be NULL). */

@@ -2463,6 +2463,7 @@ void release_block_work(BlockWork*& w) {
     delete w;
     w = nullptr;
 }
+ResWork* block_res(BlockWork* w) { return w ? &w->res : nullptr; }
 
 // (Re)build the sliced-ELLPACK copy of a complex64 operator of nrows rows
 // (a multiple of the 256-row tile; rows from nrow_valid on are empty). The
@@ -2914,6 +2915,7 @@ int ensure_work(BlockWork*& w, size_t rows, int C, int nsc, int ntiles) {
     if (w->cap_rows >= rows && w->cap_C == C && w->cap_nsc >= nsc && w->cap_tiles >= ntiles) return PETGEM_OK;
     // keep the concatenated operator, reallocate the vectors
     w->release_graph();
+    w->cap_rows = 0;   // until all of them are there
     dfree(w->X64); dfree(w->R64); dfree(w->B64); dfree(w->Xi); dfree(w->R); dfree(w->Z); dfree(w->P);
     dfree(w->Q);
     dfree(w->p0); dfree(w->p1); dfree(w->p2); dfree(w->st); dfree(w->st2); dfree(w->tmap); dfree(w->flags); dfree(w->wmu); dfree(w->seg_tile); dfree(w->tile_seg);
@@ -3445,7 +3447,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         int inner = 0;
         if (resident) {
             PG_TRY(res_run(w->res, o.max_iter - total_inner, s));
-            PG_HIP(hipMemcpyAsync(w->res.abort_h, w->res.abort, sizeof(int), hipMemcpyDeviceToHost, s));
+            PG_HIP(hipMemcpyAsync(&w->res.host->abort, w->res.abort, sizeof(int), hipMemcpyDeviceToHost, s));
         } else {
         // inner complex64 COCG on A d = r64 / |r64|
         hipLaunchKernelGGL(k_inner_init, dim3(op.ntiles), dim3(256), 0, s, op, CP, w->R64, w->st, dinv, w->Xi,
@@ -3563,7 +3565,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         PG_TRY(residual(0));
         PG_TRY(read_state());
         if (resident) {
-            if (*w->res.abort_h) return kResAborted;
+            if (w->res.host->abort) return kResAborted;
             for (int k = 0; k < nsc; ++k)
                 if (live[k]) inner = std::max(inner, w->st_h[k].kin);
         }
@@ -4262,6 +4264,7 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
     BlockWork* w = owner->bw;
     // (re)build the concatenated operator
     if (w->cat_rows < rows || w->cat_nnz < (size_t)nnz) {
+        w->cat_rows = w->cat_nnz = 0;   // until all of them are there
         dfree(w->rp); dfree(w->col); dfree(w->K64); dfree(w->M64); dfree(w->K32); dfree(w->M32);
         dfree(w->Kd); dfree(w->Md);
         PG_TRY(dalloc(&w->rp, rows + 1));

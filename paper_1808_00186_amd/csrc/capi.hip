@@ -81,8 +81,7 @@ void release_system(petgem_system* sys) {
     dfree(sys->KMst); dfree(sys->K); dfree(sys->Ms); dfree(sys->Kd); dfree(sys->Msd);
     sys->sell32.release();
     sys->ssor32.release();
-    sys->res[0].release();
-    sys->res[1].release();
+    release_spare(sys);
     dfree(sys->K32); dfree(sys->Ms32); dfree(sys->Ahat); dfree(sys->dvec); dfree(sys->dinv);
     dfree(sys->Rst); dfree(sys->hot); dfree(sys->dflag); dfree(sys->xtmp);
     dfree(sys->vox_tet); dfree(sys->vox_dof); dfree(sys->dof_mid); dfree(sys->dof_tan);
@@ -248,6 +247,16 @@ int petgem_set_background(petgem_system* sys, const petgem_background* bg) {
     sys->layers.s_dn = bg->sigma_below;
     return PETGEM_OK;
 }
+
+int petgem_set_spare_limit(petgem_system* sys, int64_t bytes) {
+    PG_TRY(check_sys(sys));
+    if (bytes < -1) { set_error("spare limit: bytes, or -1 for none"); return PETGEM_INVALID_ARG; }
+    release_spare(sys);
+    sys->spare.limit = bytes;
+    return PETGEM_OK;
+}
+
+int64_t petgem_spare_bytes(const petgem_system* sys) { return sys ? sys->spare.used : -1; }
 
 int petgem_rhs(petgem_system* sys, const petgem_source* src, int32_t n_src, void* b_dev, void* stream) {
     PG_TRY(check_sys(sys));

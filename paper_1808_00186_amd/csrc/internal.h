@@ -50,6 +50,7 @@ inline int dalloc(T** p, size_t count) {
     if (count == 0) return PETGEM_OK;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(p), count * sizeof(T));
     if (e != hipSuccess) {
+        (void)hipGetLastError();   // else the next launch's check would report it
         set_error(std::string("hipMalloc of ") + std::to_string(count * sizeof(T)) + " bytes: " +
                   hipGetErrorString(e));
         return e == hipErrorOutOfMemory ? PETGEM_OUT_OF_MEMORY : PETGEM_HIP_ERROR;
@@ -61,6 +62,33 @@ inline void dfree(T*& p) {
     if (p) (void)hipFree(p);
     p = nullptr;
 }
+
+// Device memory of a system that only makes it faster: the layouts and buffers
+// of the one-launch solves, right-hand side staging beyond one source's. A caller may
+// bound it (petgem_set_spare_limit); beyond that, as where the device has no more, the
+// forms that do without are taken.
+struct Spare {
+    int64_t limit = -1;           // -1: none
+    int64_t used = 0;
+    bool room(int64_t bytes) const { return limit < 0 || bytes <= limit - used; }
+    template <class T>
+    int take(T** p, size_t count, int64_t& held) {
+        *p = nullptr;
+        const int64_t bytes = (int64_t)(count * sizeof(T));
+        if (!room(bytes)) {
+            set_error("beyond the limit of spare device memory");
+            return PETGEM_OUT_OF_MEMORY;
+        }
+        PG_TRY(dalloc(p, count));
+        used += bytes;
+        held += bytes;
+        return PETGEM_OK;
+    }
+    void back(int64_t& held) {
+        used -= held;
+        held = 0;
+    }
+};
 
 // Sliced-ELLPACK copy of the complex64 operator (the pattern and the real K,
 // M_sigma values): slices of 64 rows, stored column-major inside a slice so a
@@ -132,7 +160,8 @@ struct Resident {
     bool values = false;          // K, M current
     double2* A = nullptr;         // [G][8][chunks][4][64] A D^-1 of the plain GMRES at a_freq
     double a_freq = -1.0;
-    void release();
+    int64_t held = 0;             // bytes of all of it
+    void release(Spare& spare);
 };
 
 // Background of the primary field: the whole space sigma_bg, or two
@@ -184,20 +213,27 @@ struct GmHost {
     GmOut out;
     int abort, flag;
 };
-// Device tables and exchange buffers of one solve's resident launches.
+// Device tables and exchange buffers of one solve's resident launches, in one
+// allocation that a plan lays out.
 struct ResWork {
     struct Round { int blk0 = 0, nblk = 0; size_t lds = 0; };
     std::vector<Round> rounds;    // one launch each
+    bool off = false;             // kernel by kernel from now on: there was no room
+    Spare* spare = nullptr;       // of the system that holds it
+    char* buf = nullptr;
+    int64_t held = 0;             // its bytes
     char* doms = nullptr;
     int* blk = nullptr;           // domain of each logical block
     unsigned long long *words = nullptr, *pex = nullptr;
-    int *abort = nullptr, *abort_h = nullptr;
+    size_t n_words = 0, n_pex = 0;
+    int* abort = nullptr;
     Resident* L = nullptr;        // GMRES: the layout of the plan
     double2* V = nullptr;         // basis, in the layout's order
     double2 *b = nullptr, *u = nullptr;
     GmOut* out = nullptr;
-    GmHost* host = nullptr;       // pinned
-    size_t cap_doms = 0, cap_blk = 0, cap_words = 0, cap_pex = 0, cap_v = 0, n_words = 0, n_pex = 0;
+    GmHost* host = nullptr;       // pinned; the COCG uses its abort only
+    int room(size_t bytes);       // buf of at least so many
+    void give_back();             // buf
     void release();
 };
 // One mesh of a solve: its rows start at row_off of the block vectors, its C
@@ -288,6 +324,9 @@ struct petgem_system {
     int spmv_group = 8;                   // lanes per CSR row (autotuned)
     bool spmv_tuned = false;
     float spmv_tune_ms[3] = {0.f, 0.f, 0.f};  // measured 4/8/16-lane SpMV times
+    petgem::Spare spare;
+    int64_t rst_held = 0;                 // of it, in Rst
+    bool rst_one = false;                 // no room for more than one source's staging
     petgem::GmresWork gw;
     petgem::ResWork gres;                 // tables and exchange buffers of the resident GMRES
     petgem::BlockWork* bw = nullptr;
@@ -356,6 +395,9 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
                 const petgem_opts& o, const void* const* x0, petgem_solution** sols, hipStream_t s,
                 petgem_stats* st);
 int ensure_fp32(petgem_system* sys, hipStream_t s);
+// gives back all spare memory of a system and lets it be tried again
+void release_spare(petgem_system* sys);
+ResWork* block_res(BlockWork* w);   // null: no workspace
 // Resident COCG: lays the meshes out and fills the launch tables (*fits false:
 // some mesh is too large, use the kernel-per-phase form); then one inner solve
 // of every column whose state is `outer`, at most max_inner iterations. After

@@ -476,8 +476,6 @@ int ensure_gmres_work(petgem_system* sys, int m) {
     const int n = sys->n_dof;
     if (w.n == n && w.m == m) return PETGEM_OK;
     w.release();
-    w.n = n;
-    w.m = m;
     w.nb_dot = std::min(kDotMaxBlocks, ceil_div(n, 256));
     PG_TRY(dalloc(&w.V, (size_t)(m + 1) * n));
     PG_TRY(dalloc(&w.u, (size_t)n));
@@ -485,6 +483,8 @@ int ensure_gmres_work(petgem_system* sys, int m) {
     PG_TRY(dalloc(&w.partial, (size_t)2 * (m + 2) * w.nb_dot + 16));
     PG_TRY(dalloc(&w.ctl, 1));
     PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&w.ctl_host), sizeof(GmresCtl) + 64));
+    w.n = n;   // all of it is there
+    w.m = m;
     return PETGEM_OK;
 }
 

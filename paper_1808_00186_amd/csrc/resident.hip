@@ -1104,8 +1104,9 @@ k_gm_solve(GmArgs a) {
 }  // namespace
 
 // ------------------------------------------------------------ host side
-void Resident::release() {
+void Resident::release(Spare& spare) {
     dfree(pattern); dfree(K); dfree(A);
+    spare.back(held);
     rows = wend = halo = nh = nullptr;
     idx = nullptr;
     M = nullptr;
@@ -1115,14 +1116,37 @@ void Resident::release() {
     values = false;
 }
 
+int ResWork::room(size_t bytes) {
+    if (!host) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&host), sizeof(GmHost)));
+    if ((size_t)held >= bytes) return PETGEM_OK;
+    give_back();
+    return spare->take(&buf, bytes, held);
+}
+
+void ResWork::give_back() {
+    dfree(buf);
+    if (spare) spare->back(held);
+}
+
 void ResWork::release() {
-    dfree(doms); dfree(blk); dfree(words); dfree(pex); dfree(abort); dfree(V); dfree(b); dfree(u); dfree(out);
+    give_back();
     if (host) (void)hipHostFree(host);
     host = nullptr;
-    if (abort_h) (void)hipHostFree(abort_h);
-    abort_h = nullptr;
-    cap_doms = cap_blk = cap_words = cap_pex = cap_v = 0;
-    rounds.clear();
+}
+
+void release_spare(petgem_system* sys) {
+    for (Resident& L : sys->res) L.release(sys->spare);
+    for (ResWork* w : {&sys->gres, block_res(sys->bw)})
+        if (w) {
+            w->give_back();
+            w->off = false;
+        }
+    if (sys->rst_held > 0) {
+        dfree(sys->Rst);
+        sys->spare.back(sys->rst_held);
+        sys->rst_copies = 0;
+    }
+    sys->rst_one = false;
 }
 
 namespace {
@@ -1167,7 +1191,7 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
     std::vector<ResWant> todo;
     for (const ResWant& w : want) {
         if (w.L->state != 0 && w.L->rw == w.rw) continue;   // (a mesh named twice: 2, set below)
-        w.L->release();
+        w.L->release(w.sys->spare);
         w.L->rw = w.rw;
         w.L->state = w.rw == 0 ? -1 : 2;
         if (w.rw != 0) todo.push_back(w);
@@ -1197,7 +1221,7 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
             };
             Carve need;
             parts(need);
-            PG_TRY(dalloc(&L.pattern, need.size));
+            PG_TRY(sys->spare.take(&L.pattern, need.size, L.held));
             Carve have{L.pattern};
             parts(have);
             lays[k] = ResLay{(int)blk.size(), n, rw, rw, hmax, sys->row_ptr, sys->col, L.rows, L.wend, L.halo, L.nh,
@@ -1246,7 +1270,7 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
             L.hcap = (got[2 * k + 1] + 63) / 64 * 64;
             L.state = 1;
         } else {   // too many entries or outer neighbours; or an error, and it may be tried again
-            L.release();
+            L.release(todo[k].sys->spare);
             L.rw = rw;
             L.state = rc == PETGEM_OK ? -1 : 0;
         }
@@ -1262,8 +1286,17 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
 // 1,024 on 61k; the coarser split lets more domains be resident at once.
 constexpr int kResFine = 512, kResCoarse = 1536;
 
-int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits) {
-    *fits = false;
+// Out of memory in a plan: what it took is given back, and the workspace's
+// solves run kernel by kernel from now on, without building layouts in vain
+// before each (until the limit is set anew).
+static int without_room(ResWork& W, petgem_system* sys) {
+    for (Resident& L : sys->res) L.release(sys->spare);
+    W.give_back();
+    W.off = true;
+    return PETGEM_OK;
+}
+
+static int res_plan_(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits) {
     int dev = 0, ncu = 0, coop = 0;
     PG_HIP(hipGetDevice(&dev));
     PG_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1286,9 +1319,10 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
     for (const Resident* l : L)
         if (l->state != 1) return PETGEM_OK;
     bool stale = false;
-    for (Resident* l : L) {
+    for (const ResWant& w : want) {
+        Resident* l = w.L;
         const size_t ent = (size_t)l->G * kResW * kResCh * 64;
-        if (!l->K) PG_TRY(dalloc(&l->K, 8 * ent));
+        if (!l->K) PG_TRY(w.sys->spare.take(&l->K, 8 * ent, l->held));
         l->M = l->K + 4 * ent;
         stale = stale || !l->values;
     }
@@ -1360,20 +1394,18 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
         out.nblk = b;
         W.rounds.push_back(out);
     }
-    auto grow = [&](auto& p, size_t& cap, size_t need) -> int {
-        if (cap >= need) return PETGEM_OK;
-        dfree(p);
-        cap = 0;
-        PG_TRY(dalloc(&p, need));
-        cap = need;
-        return PETGEM_OK;
+    auto parts = [&](Carve& c) {
+        W.abort = c.part<int>(1);
+        W.doms = c.part<char>(doms.size() * sizeof(ResDom));
+        W.blk = c.part<int>(blk.size());
+        W.words = c.part<u64>(nw);
+        W.pex = c.part<u64>(np);
     };
-    PG_TRY(grow(W.doms, W.cap_doms, doms.size() * sizeof(ResDom)));
-    PG_TRY(grow(W.blk, W.cap_blk, blk.size()));
-    PG_TRY(grow(W.words, W.cap_words, nw));
-    PG_TRY(grow(W.pex, W.cap_pex, np));
-    if (!W.abort) PG_TRY(dalloc(&W.abort, 1));
-    if (!W.abort_h) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.abort_h), sizeof(int)));
+    Carve need;
+    parts(need);
+    PG_TRY(W.room(need.size));
+    Carve have{W.buf};
+    parts(have);
     W.n_words = nw;
     W.n_pex = np;
     for (size_t k = 0; k < doms.size(); ++k) {
@@ -1397,6 +1429,16 @@ int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v,
     return PETGEM_OK;
 }
 
+int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits) {
+    *fits = false;
+    W.spare = &items[0].sys->spare;   // whose workspace it is
+    if (W.off) return PETGEM_OK;
+    const int rc = res_plan_(W, items, v, s, fits);
+    if (rc != PETGEM_OUT_OF_MEMORY) return rc;
+    for (const ResItem& it : items) (void)without_room(W, it.sys);
+    return PETGEM_OK;
+}
+
 // Dynamic LDS of k_gm_solve; its static part and this fill a compute unit's.
 constexpr int kGmLds = 160 * 1024 - 9216;
 static size_t gm_lds(const Resident& L, int restart) {
@@ -1405,10 +1447,9 @@ static size_t gm_lds(const Resident& L, int restart) {
 }
 
 // Lays the mesh out and makes room for the plain GMRES of one source in one
-// launch; *fits false: the mesh or the restart does not fit, and nothing was
-// done that such a solve would have to pay for.
-int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits) {
-    *fits = false;
+// launch; *fits false: the mesh or the restart does not fit (and nothing was
+// done that such a solve would have to pay for), or there is no room.
+static int gm_plan_(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits) {
     const int n = sys->n_dof;
     int dev = 0, ncu = 0, coop = 0;
     PG_HIP(hipGetDevice(&dev));
@@ -1419,29 +1460,35 @@ int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fi
     Resident& L = sys->res[which];
     PG_TRY(res_build({ResWant{sys, &L, rw}}, s));
     if (L.state != 1 || gm_lds(L, restart) > (size_t)kGmLds) return PETGEM_OK;
-    if (!L.A) PG_TRY(dalloc(&L.A, (size_t)L.G * kResW * kResCh * 256));
+    if (!L.A) PG_TRY(sys->spare.take(&L.A, (size_t)L.G * kResW * kResCh * 256, L.held));
     const size_t ldv = (size_t)L.G * L.rwcap;
     W.L = &L;
     W.n_words = 3 * gm_words(L.G);
     W.n_pex = 6 * ldv;
-    auto grow = [&](auto& p, size_t& cap, size_t need) -> int {
-        if (cap >= need) return PETGEM_OK;
-        dfree(p);
-        cap = 0;
-        PG_TRY(dalloc(&p, need));
-        cap = need;
-        return PETGEM_OK;
+    auto parts = [&](Carve& c) {
+        W.abort = c.part<int>(1);
+        W.out = c.part<GmOut>(1);
+        W.words = c.part<u64>(W.n_words);
+        W.pex = c.part<u64>(W.n_pex);
+        W.V = c.part<double2>((size_t)(restart + 1) * ldv);
+        W.b = c.part<double2>((size_t)n);
+        W.u = c.part<double2>((size_t)n);
     };
-    PG_TRY(grow(W.words, W.cap_words, W.n_words));
-    PG_TRY(grow(W.pex, W.cap_pex, W.n_pex));
-    PG_TRY(grow(W.V, W.cap_v, (size_t)(restart + 1) * ldv));
-    if (!W.abort) PG_TRY(dalloc(&W.abort, 1));
-    if (!W.b) PG_TRY(dalloc(&W.b, (size_t)n));
-    if (!W.u) PG_TRY(dalloc(&W.u, (size_t)n));
-    if (!W.out) PG_TRY(dalloc(&W.out, 1));
-    if (!W.host) PG_HIP(hipHostMalloc(reinterpret_cast<void**>(&W.host), sizeof(GmHost)));
+    Carve need;
+    parts(need);
+    PG_TRY(W.room(need.size));
+    Carve have{W.buf};
+    parts(have);
     *fits = true;
     return PETGEM_OK;
+}
+
+int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits) {
+    *fits = false;
+    W.spare = &sys->spare;
+    if (W.off) return PETGEM_OK;
+    const int rc = gm_plan_(sys, W, restart, s, fits);
+    return rc == PETGEM_OUT_OF_MEMORY ? without_room(W, sys) : rc;
 }
 
 // The whole plain GMRES of the source whose right-hand side is in W.b, from a

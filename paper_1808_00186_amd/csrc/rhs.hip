@@ -320,13 +320,28 @@ constexpr size_t kRhsStage = (size_t)128 << 20;
 int rhs_staging(petgem_system* sys, int n_src, int* copies) {
     const size_t one = (size_t)6 * sys->n_tets;
     const int fit = (int)std::max<size_t>(2, kRhsStage / (one * sizeof(double2)));
-    *copies = std::min(std::min(n_src, 2 * kRhsJobs), fit);
-    if (sys->rst_copies < *copies) {
+    const int want = sys->rst_one ? 1 : std::min(std::min(n_src, 2 * kRhsJobs), fit);
+    if (sys->rst_copies < want) {
         dfree(sys->Rst);
+        sys->spare.back(sys->rst_held);
         sys->rst_copies = 0;
-        PG_TRY(dalloc(&sys->Rst, one * *copies));
-        sys->rst_copies = *copies;
+        // more than one source's is spare; without room for it one does
+        const int64_t more = (int64_t)((want - 1) * one * sizeof(double2));
+        if (want > 1 && sys->spare.room(more)) {
+            const int rc = dalloc(&sys->Rst, one * want);
+            if (rc != PETGEM_OK && rc != PETGEM_OUT_OF_MEMORY) return rc;
+        }
+        if (sys->Rst) {
+            sys->rst_copies = want;
+            sys->rst_held = more;
+            sys->spare.used += more;
+        } else {
+            sys->rst_one = want > 1;
+            PG_TRY(dalloc(&sys->Rst, one));
+            sys->rst_copies = 1;
+        }
     }
+    *copies = std::min(want, sys->rst_copies);
     return PETGEM_OK;
 }
 

@@ -97,6 +97,8 @@ _SIGS = {
     "petgem_get_csr": (C.c_int, [C.c_void_p, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                  C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "petgem_spmv": (C.c_int, [C.c_void_p, C.c_double, C.c_void_p, C.c_void_p, C.c_void_p]),
+    "petgem_set_spare_limit": (C.c_int, [C.c_void_p, C.c_int64]),
+    "petgem_spare_bytes": (C.c_int64, [C.c_void_p]),
     "petgem_setup_seconds": (C.c_double, [C.c_void_p]),
     "petgem_ssor_colors": (C.c_int32, [C.c_void_p, C.POINTER(C.c_int32), C.c_void_p]),
     "petgem_ssor_apply": (C.c_int, [C.c_void_p, C.c_double, C.c_double, C.c_void_p, C.c_void_p, C.c_void_p]),
@@ -326,6 +328,15 @@ class System:
         y = torch.empty_like(x)
         _check(lib().petgem_spmv(self.handle, freq, _ptr(x), _ptr(y), _stream(stream)))
         return y
+
+    def set_spare_limit(self, bytes: int = -1):
+        """Bound on the device memory that only makes this system faster (-1:
+        none); gives what it holds back."""
+        _check(lib().petgem_set_spare_limit(self.handle, bytes))
+
+    def spare_bytes(self) -> int:
+        """Device memory held that only makes this system faster."""
+        return lib().petgem_spare_bytes(self.handle)
 
     def ssor_colors(self, stream=None) -> np.ndarray:
         """Colour of every DOF of the multicolour SSOR (library DOF order)."""
