@@ -194,7 +194,10 @@ typedef struct {
                                recursive residual ten times its lowest) the
                                rest of iters ran as independent mixed COCG
                                columns from the block's iterate (0 otherwise) */
-    int32_t reserved;
+    int32_t one_launch;     /* 1: the solve (mixed: each refinement step's inner
+                               solves) ran in one launch; 0: kernel by kernel;
+                               2: a wait of the one-launch form ran out, and the
+                               solve ran again kernel by kernel                  */
 } petgem_stats;
 
 /* Fill *opts with the defaults: GMRES, FP64, restart 30, max_iter 20000,
@@ -367,11 +370,18 @@ int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, dou
  * source's. Where the device has no more of it, or beyond the limit set here
  * (bytes; -1, the default: none), solves run kernel by kernel and right-hand
  * sides one source at a time, with the same results to rounding. Setting it gives
- * all such memory of the system back; it is taken again as solves need it, and a
- * solve that finds too little of it does not ask again until the limit is set anew
- * (a batch: of its first system). petgem_spare_bytes: what the system holds. */
+ * all such memory of the system back; it is taken again as solves need it. After
+ * a solve that found too little of it the next 64 (of the system; of a batch's first
+ * system) do not ask, unless the limit is set anew. petgem_spare_bytes: what
+ * the system holds. */
 int petgem_set_spare_limit(petgem_system* sys, int64_t bytes);
 int64_t petgem_spare_bytes(const petgem_system* sys);
+/* Workgroups of a solve in one launch wait for each other's results. A wait looks
+ * for them at most `polls` times (0: the default, about a second), which only
+ * a device kept busy by others should exceed; the launch then ends, the solve runs
+ * again kernel by kernel (one_launch = 2 in its statistics), and so do the next 64
+ * unless the limit is set anew. Of a batch, the first system's limit holds. */
+int petgem_set_wait_limit(petgem_system* sys, int32_t polls);
 /* Autotuner choices of a system: lanes per row of the double-precision CSR
  * SpMV (4, 8 or 16; 0 before the first GMRES solve) and the measured per-launch
  * times of the three variants in ms (host float [3], may be NULL). */

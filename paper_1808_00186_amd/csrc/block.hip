@@ -3045,8 +3045,7 @@ int tune_spmm(BlockWork* w, const Op& op, int64_t nnz, hipStream_t s, SpmmTuned&
 // all of them when have_x0); only those can be rejected.
 // resident: the inner solves run in w->res's launches (planned by the caller)
 // instead of kernel by kernel; returns kResAborted, with nothing said about
-// the columns, if one of their waits ran out.
-constexpr int kResAborted = 1;
+// the columns, if one of them was refused or one of their waits ran out.
 int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hipStream_t s,
                std::vector<petgem_stats*>& stv, bool have_x0, const std::vector<int>* seg_tile_h = nullptr,
                const std::vector<char>* has_x0 = nullptr, const Ssor* sq = nullptr, bool resident = false) {
@@ -3620,6 +3619,7 @@ int mrhs_solve(BlockWork* w, const Op& op, int64_t nnz, const petgem_opts& o, hi
         st->t_solve_ms = t_solve;
         st->spmv_ms = spmv_ms;
         st->spmv_launches = spmv_n;
+        st->one_launch = resident;
         // the resident kernel runs the fused step's recurrence and reports its shape
         st->spmv_shape = resident && C == 1 ? (op.nseg == 1 ? 40104 : 50100 + seg_u)
                          : fused ? 40100 + fused_u : fused_seg ? 50100 + seg_u
@@ -4228,9 +4228,12 @@ int block_solve(petgem_system* sys, const petgem_source* src, int32_t n_src, con
     }
     int rc = mrhs_solve(w, op, sys->nnz, o, s, stv, x0 != nullptr, nullptr, nullptr, sq, resident);
     if (rc == kResAborted) {
+        w->res.skip = kResSkip;
         PG_TRY(need_fp32());
         start();
         rc = mrhs_solve(w, op, sys->nnz, o, s, stv, x0 != nullptr);
+        for (petgem_stats* p : stv)
+            if (p) p->one_launch = 2;
     }
     if (rc != PETGEM_OK && rc != PETGEM_NOT_CONVERGED && rc != PETGEM_NONFINITE) return rc;
     hipLaunchKernelGGL(k_cols_out, dim3(ceil_div((size_t)n * C, 256)), dim3(256), 0, s, n, C, (size_t)0,
@@ -4378,9 +4381,12 @@ int batch_solve(petgem_system* const* systems, const petgem_source* src, int32_t
         for (int k = 0; k < n_sys; ++k) { stv[k] = st + k; st[k].t_rhs_ms = trhs; }
     int rc = mrhs_solve(w, op, nnz, o, s, stv, have_x0, &seg_tile, &has_x0, nullptr, resident);
     if (rc == kResAborted) {
+        w->res.skip = kResSkip;
         PG_TRY(need_sell());
         PG_TRY(start());
         rc = mrhs_solve(w, op, nnz, o, s, stv, have_x0, &seg_tile, &has_x0);
+        for (petgem_stats* p : stv)
+            if (p) p->one_launch = 2;
     }
     if (rc != PETGEM_OK && rc != PETGEM_NOT_CONVERGED && rc != PETGEM_NONFINITE) return rc;
     hipLaunchKernelGGL(k_cat_x, dim3(bn * n_sys), dim3(256), 0, s, (const CatSeg*)w->cat_segs, bn,

@@ -256,6 +256,15 @@ int petgem_set_spare_limit(petgem_system* sys, int64_t bytes) {
     return PETGEM_OK;
 }
 
+int petgem_set_wait_limit(petgem_system* sys, int32_t polls) {
+    PG_TRY(check_sys(sys));
+    if (polls < 0) { set_error("wait limit: polls, or 0 for the default"); return PETGEM_INVALID_ARG; }
+    sys->wait_polls = polls;
+    for (ResWork* w : {&sys->gres, block_res(sys->bw)})
+        if (w) w->skip = 0;
+    return PETGEM_OK;
+}
+
 int64_t petgem_spare_bytes(const petgem_system* sys) { return sys ? sys->spare.used : -1; }
 
 int petgem_rhs(petgem_system* sys, const petgem_source* src, int32_t n_src, void* b_dev, void* stream) {

@@ -213,12 +213,18 @@ struct GmHost {
     GmOut out;
     int abort, flag;
 };
+// Solves that run kernel by kernel after one without room for the one-launch
+// form, or one in which a wait of it ran out: either is likely to come again
+// (a wait that runs out costs about a second), and may pass.
+constexpr int kResSkip = 64;
+constexpr int kResAborted = 1;    // a launch that the device refuses, or whose wait ran out
 // Device tables and exchange buffers of one solve's resident launches, in one
 // allocation that a plan lays out.
 struct ResWork {
     struct Round { int blk0 = 0, nblk = 0; size_t lds = 0; };
     std::vector<Round> rounds;    // one launch each
-    bool off = false;             // kernel by kernel from now on: there was no room
+    int skip = 0;                 // solves that run kernel by kernel before this form is tried again
+    int polls = 0;                // of one wait
     Spare* spare = nullptr;       // of the system that holds it
     char* buf = nullptr;
     int64_t held = 0;             // its bytes
@@ -324,6 +330,7 @@ struct petgem_system {
     int spmv_group = 8;                   // lanes per CSR row (autotuned)
     bool spmv_tuned = false;
     float spmv_tune_ms[3] = {0.f, 0.f, 0.f};  // measured 4/8/16-lane SpMV times
+    int wait_polls = 0;                   // polls of one wait of a one-launch solve (0: the default)
     petgem::Spare spare;
     int64_t rst_held = 0;                 // of it, in Rst
     bool rst_one = false;                 // no room for more than one source's staging

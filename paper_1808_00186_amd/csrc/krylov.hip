@@ -594,7 +594,8 @@ int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_op
     Timer t_rhs;
     PG_TRY(launch_rhs(sys, &src, 1, w.b, 0, 1, s));
     const double trhs = t_rhs.ms();
-    PG_TRY(gm_run(sys, w, src.freq_hz, o.restart, o.max_iter, o.rtol, s));
+    const int ran = gm_run(sys, w, src.freq_hz, o.restart, o.max_iter, o.rtol, s);
+    if (ran != PETGEM_OK && ran != kResAborted) return ran;
     PG_HIP(hipMemcpyAsync(&w.host->out, w.out, sizeof(GmOut), hipMemcpyDeviceToHost, s));
     PG_HIP(hipMemcpyAsync(&w.host->abort, w.abort, sizeof(int), hipMemcpyDeviceToHost, s));
     PG_HIP(hipMemcpyAsync(&w.host->flag, sys->dflag, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -602,7 +603,11 @@ int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_op
     PG_HIP(hipGetLastError());
     PG_HIP(hipStreamSynchronize(s));
     PG_TRY(check_flag(sys, w.host->flag));
-    if (w.host->abort) return PETGEM_OK;
+    if (ran == kResAborted || w.host->abort) {
+        w.skip = kResSkip;
+        if (st) st->one_launch = 2;
+        return PETGEM_OK;
+    }
     *done = true;
     const GmOut& r = w.host->out;
     const bool bad_b = !std::isfinite(r.bnorm);
@@ -613,6 +618,7 @@ int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_op
         st->iters = r.iters;
         st->ir_steps = r.cycles;
         st->spmv_shape = 1;
+        st->one_launch = 1;
         st->rel_residual = bad_b || r.bnorm == 0.0 ? 0.0 : r.rnorm / r.bnorm;
         st->status = r.status;
         st->t_solve_ms = t_all.ms();

@@ -40,7 +40,7 @@
 //     Everybody reading everybody's took 7.9 us a step at 251 workgroups (the
 //     polls of one small array queue at its memory channels), two levels
 //     through one array 5.8 us, this 4.3 us.
-// Every wait is bounded (kResSpin polls); one that runs out raises the
+// Every wait is bounded (kResSpin polls, or the caller's); one that runs out raises the
 // launch's abort flag, every workgroup then leaves, and the host solves again
 // with the kernel-per-phase form. All workgroups of a launch are resident
 // together: at most one per compute unit, launched cooperatively.
@@ -67,7 +67,7 @@ constexpr int kResCh = 18;          // chunks of 4 entries of a thread: 72 entri
 constexpr int kResMaxG = 256;       // workgroups of a domain: 8 groups of 32
 constexpr int kResV = 9;            // doubles summed per step
 constexpr int kResLds = 160 * 1024 - 2048;
-constexpr int kResSpin = 1 << 21;   // polls of one wait, about a second
+constexpr int kResSpin = 1 << 21;   // polls of one wait (default), about a second
 constexpr u64 kResEmpty = ~0ull;
 
 // The 64-row slice of wave w that its row slot k takes: slices are sorted by
@@ -125,13 +125,13 @@ __device__ __forceinline__ int fresh_thread() {
 // N words once all are written; false when the wait ran out. Words with no
 // address (null) are zero.
 template <int N>
-__device__ __forceinline__ bool wait_words(const u64* const* a, const int* abort, u64* v) {
+__device__ __forceinline__ bool wait_words(const u64* const* a, int polls, const int* abort, u64* v) {
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = a[i] ? get(a[i]) : 0ull;
 #pragma unroll
     for (int i = 0; i < N; ++i)
         for (int spin = 0; v[i] == kResEmpty; ++spin) {
-            if (spin >= kResSpin || ((spin & 1023) == 1023 && aborted(abort))) return false;
+            if (spin >= polls || ((spin & 1023) == 1023 && aborted(abort))) return false;
             v[i] = get(a[i]);
         }
     return true;
@@ -311,7 +311,8 @@ __global__ void k_res_clear(size_t n_words, u64* __restrict__ words, size_t n_pe
 
 // ------------------------------------------------------------ the solve
 __global__ void __launch_bounds__(kResT)
-k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int max_inner, int* __restrict__ abort) {
+k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int max_inner, int polls,
+           int* __restrict__ abort) {
     extern __shared__ double2 lds_d[];
     __shared__ double wsum[kResW][kResV];
     __shared__ double tot[kResV + 1];
@@ -415,7 +416,7 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
                     u64 v[4];
 #pragma unroll
                     for (int u = 0; u < 4; ++u) ad[u] = h0 + u * kResT < nh ? px + hl[h0 + u * kResT] : nullptr;
-                    if (!wait_words<4>(ad, abort, v)) bad = true;
+                    if (!wait_words<4>(ad, polls, abort, v)) bad = true;
 #pragma unroll
                     for (int u = 0; u < 4; ++u)
                         if (ad[u]) pl[rwcap + h0 + u * kResT] = unbits(v[u]);
@@ -514,7 +515,7 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
                 const int q = t & 31;
                 const u64* ad[1] = {32 * gr + q < G ? w1 + t : nullptr};
                 u64 x[1];
-                if (!wait_words<1>(ad, abort, x)) fail1 = 1;
+                if (!wait_words<1>(ad, polls, abort, x)) fail1 = 1;
                 const double a = sum32(__longlong_as_double((long long)x[0]));
                 if (ng == 1) {
                     if (q == 0) tot[t >> 5] = a;
@@ -525,7 +526,7 @@ k_res_cocg(const ResDom* __restrict__ doms, const int* __restrict__ blk_dom, int
             if (ng > 1 && t < kResV * 8) {
                 const u64* ad[1] = {(t & 7) < ng ? w2 + (size_t)gr * kResArea + t : nullptr};
                 u64 x[1];
-                if (!wait_words<1>(ad, abort, x)) fail1 = 1;
+                if (!wait_words<1>(ad, polls, abort, x)) fail1 = 1;
                 const double a = sum8(__longlong_as_double((long long)x[0]));
                 if ((t & 7) == 0) tot[t >> 3] = a;
             }
@@ -617,7 +618,7 @@ constexpr int kGmVals = 64;
 constexpr int kGmArea = kGmVals * 32 + 32;    // words from one area to the next
 
 struct GmArgs {
-    int G, n, rw, rwcap, hcap, hmax, m, max_iter;
+    int G, n, rw, rwcap, hcap, hmax, m, max_iter, polls;
     double rtol;
     const int32_t *rows, *wend, *halo, *nh;
     const uint2* idx;
@@ -733,7 +734,7 @@ k_gm_solve(GmArgs a) {
                 const u64* const p1 = h1 < nh ? px + 2 * (size_t)hl[h1] : nullptr;
                 const u64* ad[4] = {p0, p0 + 1, p1, p1 ? p1 + 1 : nullptr};
                 u64 v[4];
-                if (!wait_words<4>(ad, a.abort, v)) bad = true;
+                if (!wait_words<4>(ad, a.polls, a.abort, v)) bad = true;
                 z[rwcap + h0] = make_double2(__longlong_as_double((long long)v[0]), __longlong_as_double((long long)v[1]));
                 if (p1)
                     z[rwcap + h1] = make_double2(__longlong_as_double((long long)v[2]), __longlong_as_double((long long)v[3]));
@@ -789,7 +790,7 @@ k_gm_solve(GmArgs a) {
         if (lanes1 == 8) {   // up to eight workgroups: eight lanes to a value, all values at once
             const u64* ad[1] = {t < nv * 8 && (t & 7) < G ? w1 + t : nullptr};
             u64 x[1];
-            if (G > 1 && !wait_words<1>(ad, a.abort, x)) fail1 = 1;
+            if (G > 1 && !wait_words<1>(ad, a.polls, a.abort, x)) fail1 = 1;
             const double v = sum8(__longlong_as_double((long long)x[0]));
             if (G > 1 && t < nv * 8 && (t & 7) == 0) tot[t >> 3] = v;
         } else if (ng == 1 || (g & 31) == 0) {
@@ -798,7 +799,7 @@ k_gm_solve(GmArgs a) {
             u64 x[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r) ad[r] = 32 * gr + q < G && t + r * kResT < nv * 32 ? w1 + t + r * kResT : nullptr;
-            if (!wait_words<4>(ad, a.abort, x)) fail1 = 1;
+            if (!wait_words<4>(ad, a.polls, a.abort, x)) fail1 = 1;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const double v = sum32(__longlong_as_double((long long)x[r]));
@@ -814,7 +815,7 @@ k_gm_solve(GmArgs a) {
         if (ng > 1) {
             const u64* ad[1] = {t < nv * 8 && (t & 7) < ng ? w2 + (size_t)gr * kGmArea + t : nullptr};
             u64 x[1];
-            if (!wait_words<1>(ad, a.abort, x)) fail1 = 1;
+            if (!wait_words<1>(ad, a.polls, a.abort, x)) fail1 = 1;
             const double v = sum8(__longlong_as_double((long long)x[0]));
             if (t < nv * 8 && (t & 7) == 0) tot[t >> 3] = v;
         }
@@ -1139,7 +1140,7 @@ void release_spare(petgem_system* sys) {
     for (ResWork* w : {&sys->gres, block_res(sys->bw)})
         if (w) {
             w->give_back();
-            w->off = false;
+            w->skip = 0;
         }
     if (sys->rst_held > 0) {
         dfree(sys->Rst);
@@ -1286,14 +1287,20 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
 // 1,024 on 61k; the coarser split lets more domains be resident at once.
 constexpr int kResFine = 512, kResCoarse = 1536;
 
-// Out of memory in a plan: what it took is given back, and the workspace's
-// solves run kernel by kernel from now on, without building layouts in vain
-// before each (until the limit is set anew).
+// Out of memory in a plan: what it took is given back, and the workspace's next
+// solves run kernel by kernel without building layouts in vain before each.
 static int without_room(ResWork& W, petgem_system* sys) {
     for (Resident& L : sys->res) L.release(sys->spare);
     W.give_back();
-    W.off = true;
+    W.skip = kResSkip;
     return PETGEM_OK;
+}
+// whether the form is tried at all, with the polls its waits may take
+static bool res_try(ResWork& W, const petgem_system* sys) {
+    W.polls = sys->wait_polls > 0 ? sys->wait_polls : kResSpin;
+    if (W.skip == 0) return true;
+    --W.skip;
+    return false;
 }
 
 static int res_plan_(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits) {
@@ -1432,10 +1439,21 @@ static int res_plan_(ResWork& W, const std::vector<ResItem>& items, const ResVec
 int res_plan(ResWork& W, const std::vector<ResItem>& items, const ResVectors& v, hipStream_t s, bool* fits) {
     *fits = false;
     W.spare = &items[0].sys->spare;   // whose workspace it is
-    if (W.off) return PETGEM_OK;
+    if (!res_try(W, items[0].sys)) return PETGEM_OK;
     const int rc = res_plan_(W, items, v, s, fits);
     if (rc != PETGEM_OUT_OF_MEMORY) return rc;
     for (const ResItem& it : items) (void)without_room(W, it.sys);
+    return PETGEM_OK;
+}
+
+// The workgroups of a launch have to be resident together; a device that has
+// fewer compute units for it than it said refuses.
+static int launched(hipError_t e) {
+    if (e == hipErrorCooperativeLaunchTooLarge) {
+        (void)hipGetLastError();
+        return kResAborted;
+    }
+    PG_HIP(e);
     return PETGEM_OK;
 }
 
@@ -1486,7 +1504,7 @@ static int gm_plan_(petgem_system* sys, ResWork& W, int restart, hipStream_t s, 
 int gm_plan(petgem_system* sys, ResWork& W, int restart, hipStream_t s, bool* fits) {
     *fits = false;
     W.spare = &sys->spare;
-    if (W.off) return PETGEM_OK;
+    if (!res_try(W, sys)) return PETGEM_OK;
     const int rc = gm_plan_(sys, W, restart, s, fits);
     return rc == PETGEM_OUT_OF_MEMORY ? without_room(W, sys) : rc;
 }
@@ -1515,6 +1533,7 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
     a.hmax = L.hmax;
     a.m = restart;
     a.max_iter = max_iter;
+    a.polls = W.polls;
     a.rtol = rtol;
     a.rows = L.rows;
     a.wend = L.wend;
@@ -1535,8 +1554,7 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
                                          : reinterpret_cast<const void*>(k_gm_solve<4>);
     const size_t lds = gm_lds(L, restart);
     PG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    PG_HIP(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
-    return PETGEM_OK;
+    return launched(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
 }
 
 int res_run(ResWork& W, int max_inner, hipStream_t s) {
@@ -1549,10 +1567,11 @@ int res_run(ResWork& W, int max_inner, hipStream_t s) {
     for (const ResWork::Round& r : W.rounds) {
         const ResDom* doms = reinterpret_cast<const ResDom*>(W.doms);
         const int* blk = W.blk + r.blk0;
+        int polls = W.polls;
         int* abort = W.abort;
-        void* args[4] = {&doms, &blk, &max_inner, &abort};
-        PG_HIP(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_res_cocg), dim3(r.nblk), dim3(kResT), args,
-                                          (unsigned)r.lds, s));
+        void* args[5] = {&doms, &blk, &max_inner, &polls, &abort};
+        PG_TRY(launched(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_res_cocg), dim3(r.nblk), dim3(kResT),
+                                                   args, (unsigned)r.lds, s)));
     }
     return PETGEM_OK;
 }

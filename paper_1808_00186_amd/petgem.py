@@ -63,7 +63,7 @@ class Stats(C.Structure):
                 ("x0_rel_residual", C.c_double), ("t_rhs_ms", C.c_double),
                 ("t_solve_ms", C.c_double), ("spmv_ms", C.c_double),
                 ("spmv_launches", C.c_int32), ("spmv_shape", C.c_int32), ("b_norm", C.c_double),
-                ("block_iters", C.c_int32), ("reserved", C.c_int32)]
+                ("block_iters", C.c_int32), ("one_launch", C.c_int32)]
 
     def as_dict(self):
         return {k: getattr(self, k) for k, _ in self._fields_}
@@ -98,6 +98,7 @@ _SIGS = {
                                  C.POINTER(C.c_double), C.POINTER(C.c_double), C.c_void_p]),
     "petgem_spmv": (C.c_int, [C.c_void_p, C.c_double, C.c_void_p, C.c_void_p, C.c_void_p]),
     "petgem_set_spare_limit": (C.c_int, [C.c_void_p, C.c_int64]),
+    "petgem_set_wait_limit": (C.c_int, [C.c_void_p, C.c_int32]),
     "petgem_spare_bytes": (C.c_int64, [C.c_void_p]),
     "petgem_setup_seconds": (C.c_double, [C.c_void_p]),
     "petgem_ssor_colors": (C.c_int32, [C.c_void_p, C.POINTER(C.c_int32), C.c_void_p]),
@@ -333,6 +334,10 @@ class System:
         """Bound on the device memory that only makes this system faster (-1:
         none); gives what it holds back."""
         _check(lib().petgem_set_spare_limit(self.handle, bytes))
+
+    def set_wait_limit(self, polls: int = 0):
+        """How often a wait of a one-launch solve looks before it gives up (0: the default)."""
+        _check(lib().petgem_set_wait_limit(self.handle, polls))
 
     def spare_bytes(self) -> int:
         """Device memory held that only makes this system faster."""
