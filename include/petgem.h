@@ -383,8 +383,10 @@ int64_t petgem_spare_bytes(const petgem_system* sys);
  * unless the limit is set anew. Of a batch, the first system's limit holds. */
 int petgem_set_wait_limit(petgem_system* sys, int32_t polls);
 /* Autotuner choices of a system: lanes per row of the double-precision CSR
- * SpMV (4, 8 or 16; 0 before the first GMRES solve) and the measured per-launch
- * times of the three variants in ms (host float [3], may be NULL). */
+ * SpMV (4, 8 or 16; 0 before the first GMRES solve or product) and the measured
+ * per-launch times of the three variants in ms (host float [3], may be NULL). A
+ * solve in one launch and a product do not need the choice: it is then made here,
+ * on the default stream after everything queued on the device. */
 int petgem_tuning(const petgem_system* sys, int32_t* spmv_group, float* spmv_ms);
 /* Seconds spent in the host preprocessing of the last petgem_assemble. */
 double petgem_setup_seconds(const petgem_system* sys);

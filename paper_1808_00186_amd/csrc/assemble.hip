@@ -220,6 +220,7 @@ int launch_spmv(petgem_system* sys, double freq, const double2* x, double2* y, h
     hipLaunchKernelGGL(k_spmv_km, dim3(ceil_div((int64_t)n * 8, 256)), dim3(256), 0, s, n, 2.0 * kPi * freq * kMu0,
                        sys->row_ptr, sys->col, sys->K, sys->Ms, x, y);
     PG_HIP(hipGetLastError());
+    sys->tune_freq = freq;
     return PETGEM_OK;
 }
 

@@ -473,6 +473,14 @@ int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, dou
 
 int petgem_tuning(const petgem_system* sys, int32_t* spmv_group, float* spmv_ms) {
     PG_TRY(check_sys(sys));
+    if (!sys->spmv_tuned && sys->tune_freq > 0.0) {
+        // products and solves in one launch leave the tuning to whoever asks
+        // for it: what they queued, on whichever stream, comes first
+        petgem_system* own = const_cast<petgem_system*>(sys);
+        PG_HIP(hipDeviceSynchronize());
+        PG_TRY(launch_freq_prep(own, sys->tune_freq, nullptr));
+        PG_TRY(tune_spmv(own, nullptr));
+    }
     if (spmv_group) *spmv_group = sys->spmv_tuned ? sys->spmv_group : 0;
     if (spmv_ms)
         for (int i = 0; i < 3; ++i) spmv_ms[i] = sys->spmv_tune_ms[i];

@@ -329,6 +329,7 @@ struct petgem_system {
     double vox_h = 0.0, vox_L = 0.0;
     int spmv_group = 8;                   // lanes per CSR row (autotuned)
     bool spmv_tuned = false;
+    double tune_freq = 0.0;               // of the latest double-precision product or solve that did not tune
     float spmv_tune_ms[3] = {0.f, 0.f, 0.f};  // measured 4/8/16-lane SpMV times
     int wait_polls = 0;                   // polls of one wait of a one-launch solve (0: the default)
     petgem::Spare spare;

@@ -609,6 +609,7 @@ int gmres_resident(petgem_system* sys, const petgem_source& src, const petgem_op
         return PETGEM_OK;
     }
     *done = true;
+    sys->tune_freq = src.freq_hz;
     const GmOut& r = w.host->out;
     const bool bad_b = !std::isfinite(r.bnorm);
     if (st) {
