@@ -424,6 +424,15 @@ int ssor_apply1(petgem_system* sys, double freq, double omega, const float2* r, 
 // spmv_shape statistic); returns the count, writes at most cap codes
 int spmm_candidate_codes(int C, bool sliced, int32_t* out, int cap);
 
+// Lets a kernel be launched with up to `bytes` of dynamic LDS on the current
+// device: ahead of each launch (0.14 us), since the library keeps no record of
+// devices, and with the same number at each, so that threads that launch the
+// same kernel for different sizes do not lower each other's.
+template <class F>
+inline hipError_t allow_lds(F kernel, int bytes) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
 // Grid helpers
 inline int ceil_div(int64_t a, int64_t b) { return int((a + b - 1) / b); }
 

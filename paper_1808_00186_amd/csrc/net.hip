@@ -1128,9 +1128,7 @@ int conv_z(const bf16* in, const bf16* up, const bf16* wt, const float* bias, co
     constexpr int lds = 2 * ((TY + 2) * (D + 2) * (CIN + 8) + 48 * NTB * (9 * CIN + 8));
     static_assert(lds <= 160 * 1024, "one block's LDS");
     auto kernel = k_conv_z<CIN, COUT, C1, D, TY, NTB, NW, EPI>;
-    static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    PG_HIP(attr);
+    PG_HIP(allow_lds(kernel, lds));
     const int rows = B * (D / TY), outs = COUT / (16 * NTB);
     int TZ = CAP;
     while (TZ > 1 && rows * outs * (D / TZ) < 192 * 8 / NW) TZ /= 2;

@@ -70,6 +70,8 @@ constexpr int kResLds = 160 * 1024 - 2048;
 constexpr int kResSpin = 1 << 21;   // polls of one wait (default), about a second
 constexpr u64 kResEmpty = ~0ull;
 
+constexpr int kResHaloLds = kResMaxG * kResRows / 32 * 8;   // k_res_halo: two words for 32 rows of the largest mesh
+
 // The 64-row slice of wave w that its row slot k takes: slices are sorted by
 // row length, and alternating the direction evens out the waves' entries.
 __host__ __device__ constexpr int res_slice(int w, int k) { return k * kResW + ((k & 1) ? kResW - 1 - w : w); }
@@ -1253,8 +1255,7 @@ int res_build(const std::vector<ResWant>& want, hipStream_t s) {
         PG_HIP(hipMemcpyAsync(lays_d, lays.data(), sizeof(ResLay) * nt, hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(k_res_sort, dim3(blk.size()), dim3(1024), 0, s, lays_d, blk_d);
         const size_t lds = (size_t)2 * ceil_div(most, 32) * sizeof(unsigned);
-        PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_halo),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        PG_HIP(allow_lds(k_res_halo, kResHaloLds));
         hipLaunchKernelGGL(k_res_halo, dim3(blk.size()), dim3(1024), lds, s, lays_d, blk_d);
         PG_HIP(hipGetLastError());
         PG_HIP(hipMemcpyAsync(got.data(), stat, sizeof(int) * got.size(), hipMemcpyDeviceToHost, s));
@@ -1553,7 +1554,7 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
                      : L.rw <= 2 * kResT ? reinterpret_cast<const void*>(k_gm_solve<2>)
                                          : reinterpret_cast<const void*>(k_gm_solve<4>);
     const size_t lds = gm_lds(L, restart);
-    PG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    PG_HIP(allow_lds(fn, kGmLds));
     return launched(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
 }
 
@@ -1562,8 +1563,7 @@ int res_run(ResWork& W, int max_inner, hipStream_t s) {
     hipLaunchKernelGGL(k_res_clear, dim3(ceil_div(m, 256)), dim3(256), 0, s, W.n_words, W.words, W.n_pex, W.pex,
                        W.abort);
     PG_HIP(hipGetLastError());
-    PG_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_res_cocg), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kResLds));
+    PG_HIP(allow_lds(k_res_cocg, kResLds));
     for (const ResWork::Round& r : W.rounds) {
         const ResDom* doms = reinterpret_cast<const ResDom*>(W.doms);
         const int* blk = W.blk + r.blk0;

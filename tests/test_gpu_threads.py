@@ -1,0 +1,54 @@
+"""Two threads, each with its own systems, network and stream. Marked `gpu`.
+
+The same kernels run for unlike sizes side by side; every result is that of the
+thread alone, bit for bit.
+"""
+import threading
+
+import numpy as np
+import pytest
+
+from paper_1808_00186_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _work(pg, n, restart, batch, reps, out):
+    import torch
+    with torch.cuda.stream(torch.cuda.Stream()):
+        got = []
+        for r in range(reps):
+            xyz, tets = synth.kuhn_mesh(n, -3000.0, 3000.0, n)
+            sig = synth.marine_sigma(synth.centroids(xyz, tets), ((-1200, 1200), (-1200, 1200), (-1800, -600)), 0.02)
+            S = pg.System(xyz, tets, sig, 3.3)   # new layouts every time
+            src = [synth.Dipole((-50.0 + 90.0 * k, 10.0, 50.0), 1.0 + 0.3 * k) for k in range(2)]
+            x, st, _ = S.solve(src, pg.default_opts(rtol=1e-8, restart=restart))
+            y, su, _ = S.solve(src, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=1e-8))
+            assert {s["one_launch"] for s in st + su} == {1}
+            net = pg.Net(batch_max=batch, seed=n)
+            g = torch.Generator(device="cuda").manual_seed(n)
+            X = torch.randn((batch, pg.NET_VOX, pg.NET_IN), device="cuda", generator=g).to(torch.bfloat16)
+            got.append([t.cpu().numpy() for t in (torch.view_as_real(x.x()), torch.view_as_real(y.x()), net.forward(X))])
+        out.append(got)
+
+
+def test_two_threads_give_what_each_gives_alone():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1808_00186_amd import petgem as pg
+    print("[case] threads", flush=True)
+    jobs = [(10, 30, 2), (20, 7, 5)]
+    alone, both = [[], []], [[], []]
+    for k, j in enumerate(jobs):
+        _work(pg, *j, 1, alone[k])
+    ts = [threading.Thread(target=_work, args=(pg, *j, 4, both[k])) for k, j in enumerate(jobs)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k in range(2):
+        assert len(both[k]) == 1 and len(both[k][0]) == 4
+        for got in both[k][0]:
+            for a, b in zip(alone[k][0][0], got):
+                assert np.array_equal(a, b)
