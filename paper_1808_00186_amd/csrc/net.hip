@@ -149,10 +149,9 @@ k_conv(const bf16* __restrict__ in, const bf16* __restrict__ wt, const float* __
         // The plane's reduction index runs over its 9 taps x CIN channels,
         // tap-major (the order of a weight row), 32 at a time on
         // v_mfma_f32_16x16x32_bf16: lane kq takes indices 8 kq .. 8 kq + 7 of
-        // the chunk, 8 channels of one tap (CIN is a multiple of 16), for both
-        // operands; 9 CIN that is an odd multiple of 16 leaves 16, taken by
-        // v_mfma_f32_16x16x16_bf16 (4 per lane).
-        constexpr int KP = 9 * CIN, NK32 = KP / 32;
+        // the chunk, 8 channels of one tap, for both operands.
+        constexpr int NK32 = 9 * CIN / 32;
+        static_assert(9 * CIN % 32 == 0, "whole chunks");
         constexpr int UNR = CIN >= 48 ? 1 : 3;   // wider inputs: keep two waves per SIMD
 #pragma unroll UNR
         for (int kk = 0; kk < NK32; ++kk) {
@@ -168,20 +167,6 @@ k_conv(const bf16* __restrict__ in, const bf16* __restrict__ wt, const float* __
 #pragma unroll
                 for (int t = 0; t < NTB; ++t)
                     acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w[t], acc[i][t], 0, 0, 0);
-        }
-        if constexpr (KP % 32 != 0) {
-            const int idx = 32 * NK32 + 4 * kq, tap = idx / CIN, ch = idx % CIN;
-            const int sh = ((tap / 3) * (D + 2) + tap % 3) * HC + ch;
-            bf16x4 a[MT], w[NTB];
-#pragma unroll
-            for (int i = 0; i < MT; ++i) a[i] = *reinterpret_cast<const bf16x4*>(halo + aoff[i] + sh);
-#pragma unroll
-            for (int t = 0; t < NTB; ++t) w[t] = *reinterpret_cast<const bf16x4*>(wl + (t * 16 + m) * WK + idx);
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int t = 0; t < NTB; ++t)
-                    acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], w[t], acc[i][t], 0, 0, 0);
         }
         __syncthreads();
         if (pz < 2) {

@@ -1550,9 +1550,9 @@ int gm_run(petgem_system* sys, ResWork& W, double freq, int restart, int max_ite
     a.abort = W.abort;
     a.out = W.out;
     void* args[1] = {&a};
+    // the finer split has at most 512 rows to a workgroup, the coarser one more than 1,024
     const void* fn = L.rw <= kResT ? reinterpret_cast<const void*>(k_gm_solve<1>)
-                     : L.rw <= 2 * kResT ? reinterpret_cast<const void*>(k_gm_solve<2>)
-                                         : reinterpret_cast<const void*>(k_gm_solve<4>);
+                                   : reinterpret_cast<const void*>(k_gm_solve<4>);
     const size_t lds = gm_lds(L, restart);
     PG_HIP(allow_lds(fn, kGmLds));
     return launched(hipLaunchCooperativeKernel(fn, dim3(L.G), dim3(kResT), args, (unsigned)lds, s));
