@@ -1,8 +1,9 @@
 """A plain GMRES solve that the one-launch form does not take. Marked `gpu`.
 
 It is decided before anything is allocated or formed for that form: the first
-solve takes no vector of device memory more than a profiled one, which never
-asks for it (allocations come in 2 MiB, less than a vector of these meshes).
+solve does not take the two vectors that form needs beside its own more than a
+profiled one, which never asks for it (allocations come in 2 MiB, less than a
+vector of these meshes).
 """
 import numpy as np
 import pytest
@@ -34,4 +35,4 @@ def test_a_solve_that_does_not_fit_pays_for_its_own_form_only(n, restart):
     taken(1)
     (own, vector), (plain, _) = taken(1), taken(0)
     print(f"  {own} bytes, not profiled {plain}", flush=True)
-    assert vector > 2 << 20 and plain < own + vector
+    assert vector > 2 << 20 and plain < own + 2 * vector

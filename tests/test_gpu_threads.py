@@ -1,7 +1,9 @@
 """Two threads, each with its own systems, network and stream. Marked `gpu`.
 
-The same kernels run for unlike sizes side by side; every result is that of the
-thread alone, bit for bit.
+The same kernels run for unlike sizes side by side; GMRES and the network give
+what the thread alone gives, bit for bit, and the mixed solve (whose residual's
+summation order a tuner picks by time) its tolerance in the true residual, 1 % for
+the rounding of its own evaluation.
 """
 import threading
 
@@ -25,10 +27,14 @@ def _work(pg, n, restart, batch, reps, out):
             x, st, _ = S.solve(src, pg.default_opts(rtol=1e-8, restart=restart))
             y, su, _ = S.solve(src, pg.default_opts(method=pg.COCG, precision=pg.MIXED, rtol=1e-8))
             assert {s["one_launch"] for s in st + su} == {1}
+            b, v = S.rhs(src), y.x()
+            for k, d in enumerate(src):
+                r = b[k] - S.spmv(d.freq, v[k].contiguous())
+                assert float(r.norm() / b[k].norm()) <= 1.01e-8
             net = pg.Net(batch_max=batch, seed=n)
             g = torch.Generator(device="cuda").manual_seed(n)
             X = torch.randn((batch, pg.NET_VOX, pg.NET_IN), device="cuda", generator=g).to(torch.bfloat16)
-            got.append([t.cpu().numpy() for t in (torch.view_as_real(x.x()), torch.view_as_real(y.x()), net.forward(X))])
+            got.append([t.cpu().numpy() for t in (torch.view_as_real(x.x()), net.forward(X))])
         out.append(got)
 
 
