@@ -162,7 +162,8 @@ typedef struct {
     double  t_solve_ms;
     double  spmv_ms;        /* profile: summed duration of sparse-matrix kernels */
     int32_t spmv_launches;  /* profile: number of such launches                  */
-    int32_t spmv_shape;     /* COCG: the autotuned complex64 SpMM shape,
+    int32_t spmv_shape;     /* COCG: the autotuned complex64 SpMM shape (which
+                               a solve in one launch does not run),
                                10000 kind + 100 a + b with kind 0 = CSR column
                                lanes (a lanes per row, b columns per lane),
                                1 = CSR nonzero lanes (a lanes per row, b
@@ -365,7 +366,7 @@ int petgem_mesh_pattern(const petgem_mesh* mesh, int32_t* n_dof, int64_t* nnz,
 int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, double tol,
                   int32_t* elem);
 /* Device memory that only makes a system faster: the layouts and buffers of the
- * solves that run in one launch (about 0.4 GB for the double-precision and 0.2 GB
+ * solves that run in one launch (about 0.4 GB for the double-precision and 0.1 GB
  * for the mixed form of a 434,000-unknown mesh) and right-hand side staging beyond one
  * source's. Where the device has no more of it, or beyond the limit set here
  * (bytes; -1, the default: none), solves run kernel by kernel and right-hand
