@@ -373,8 +373,8 @@ int petgem_locate(const petgem_mesh* mesh, const double* pts, int32_t n_pts, dou
  * sides one source at a time, with the same results to rounding. Setting it gives
  * all such memory of the system back; it is taken again as solves need it. After
  * a solve that found too little of it the next 64 (of the system; of a batch's first
- * system) do not ask, unless the limit is set anew. petgem_spare_bytes: what
- * the system holds. */
+ * system) do not ask, unless the limit is set anew; right-hand sides do not ask
+ * again until it is. petgem_spare_bytes: what the system holds. */
 int petgem_set_spare_limit(petgem_system* sys, int64_t bytes);
 int64_t petgem_spare_bytes(const petgem_system* sys);
 /* Workgroups of a solve in one launch wait for each other's results. A wait looks
